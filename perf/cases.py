@@ -120,7 +120,7 @@ def _lowest(g, share):
     """Mask of the lowest values of g: a share of them that the seed does not change."""
     flat = g.reshape(-1)
     k = max(1, int(share * flat.numel()))
-    at = flat.kthvalue(k).values
+    at = flat.sort().values[k - 1]
     mask = flat < at
     mask[(flat == at).nonzero().reshape(-1)[: k - int(mask.sum())]] = True
     return mask.reshape(g.shape)
@@ -129,12 +129,13 @@ def _lowest(g, share):
 def _rock(nx, ny, nz, porosity, seed, corr=4.0):
     """Pore mask [nz, ny, nx] of a thresholded periodic Gaussian random field."""
     g = torch.randn((nz, ny, nx), generator=_generator(seed), device=DEV)
-    k2 = (torch.fft.fftfreq(nz, device=DEV)[:, None, None] ** 2
-          + torch.fft.fftfreq(ny, device=DEV)[None, :, None] ** 2
-          + torch.fft.rfftfreq(nx, device=DEV)[None, None, :] ** 2)
-    s = corr / math.sqrt(2.0)
-    g = torch.fft.irfftn(torch.fft.rfftn(g) * torch.exp(-2.0 * (math.pi * s) ** 2 * k2),
-                         s=(nz, ny, nx))
+    s = corr / math.sqrt(2.0)            # the filter's; the field's covariance has length corr
+    reach = int(4 * s)
+    for axis in range(3):
+        out = torch.zeros_like(g)
+        for k in range(-reach, reach + 1):
+            out.add_(torch.roll(g, k, axis), alpha=math.exp(-0.5 * (k / s) ** 2))
+        g = out
     return _lowest(g, porosity)
 
 
