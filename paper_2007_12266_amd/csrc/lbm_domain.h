@@ -115,7 +115,7 @@ struct lbm_domain {
     lbm::StepArgs args(int blk = 256, int sched = 1, int run = lbm::kXcdRun) const {
         lbm::StepArgs a{};
         a.N = (int32_t)pre.n_pore;
-        a.nblocks = (int32_t)((pre.n_pore + blk - 1) / blk);
+        a.block = blk;
         a.ld = pre.ld;
         a.nbr = nbr;
         a.phi = phi;
@@ -129,8 +129,13 @@ struct lbm_domain {
         a.alpha = p.alpha;
         a.beta = p.beta;
         for (int c = 0; c < 3; ++c) a.F[c] = p.force[c];
-        a.xcd_run = sched >= 2 ? run : 0;
-        a.reverse = sched == 3 ? 1 : 0;
+        const int64_t tiles = (pre.n_pore + blk - 1) / blk;
+        const int64_t whole = 8 * (int64_t)run;   // whole runs on every XCD
+        a.grid = (int32_t)(sched >= 2 ? (tiles + whole - 1) / whole * whole : tiles);
+        a.xcd_run = sched >= 2 ? run : 1;
+        a.xcd_mul = lbm::xcd_mul_of(a.xcd_run);
+        a.tile_first = sched == 3 ? a.grid - 1 : 0;
+        a.tile_sign = sched == 3 ? -1 : 1;
         a.coord = rank ? coord : nullptr;
         a.words = rank ? words : nullptr;
         a.cax = compact ? cax : nullptr;

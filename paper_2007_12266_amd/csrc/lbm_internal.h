@@ -25,7 +25,7 @@ constexpr int kRedThreads = 256;
 // Arguments of the step kernels (passed by value).
 struct StepArgs {
     int32_t N;          // pore voxels
-    int32_t nblocks;    // logical workgroups covering N
+    int32_t block;      // threads per workgroup of the step kernels (voxels per tile)
     int64_t ld;         // leading dimension of population arrays
     const int32_t* nbr; // [9][ld][2]: neighbours along (q, q + 1) for q = 1, 3, ..., 17
     void* phi;          // [N + n_tail] in the storage type; the tail holds phi_s
@@ -38,8 +38,11 @@ struct StepArgs {
     double nu_a, nu_b;  // kinematic viscosities
     double alpha, beta;
     double F[3];
-    int32_t xcd_run;    // 0: linear tile order; > 0: XCD-aware order, runs of this many tiles
-    int32_t reverse;    // 1: the tile order runs from the end of the pore list
+    int32_t grid;       // workgroups of a step kernel's launch
+    int32_t xcd_run;    // tiles per run of the XCD-aware order (1: launch order)
+    uint32_t xcd_mul;   // xcd_mul_of(xcd_run)
+    int32_t tile_first; // a workgroup takes tile tile_first + tile_sign * (its place in the
+    int32_t tile_sign;  //   order): 0 and 1, or grid - 1 and -1 for the order from the end
     int32_t prec;       // lbm_precision
     // Rank lookup of neighbours (used instead of nbr when words != null):
     const uint32_t* coord;   // [ld] packed (x, y, z) of each pore voxel
@@ -61,6 +64,10 @@ struct StepArgs {
 // the run length of the batched launches and the default of a domain's own launches, which may
 // choose any length up to kMaxXcdRun for each kernel and step parity (lbm_tuning).
 constexpr int kXcdRun = 16;
+// The factor whose product with j, shifted right by 31, is j / run (see xcd_run_tile).
+constexpr uint32_t xcd_mul_of(int run) {
+    return (uint32_t)(((uint64_t(1) << 31) + (uint32_t)run - 1) / (uint32_t)run);
+}
 constexpr int kMaxXcdRun = 64;
 
 // Steps in the captured chunk of the single-domain step loop (even, so every chunk starts and
@@ -71,6 +78,12 @@ constexpr int64_t kStepGraphChunk = 64;
 // (non-temporal) accesses: twice the MI355X Infinity Cache (256 MB), so that a domain the cache
 // holds from one step to the next keeps that reuse.
 constexpr int64_t kStreamBytes = int64_t(512) << 20;
+
+// Most pore voxels of a domain whose collide kernel issues all its loads first (EARLY in
+// lbm_kernels.hip): up to about four waves per SIMD. Above, other waves hide the round trip that
+// it saves, and its registers only cost occupancy. Measured as a whole pass: 20 thousand voxels
+// +6%, 65 thousand +7%, 524 thousand -0.2% (FP64) and -1.2% (FP32-dev, 110 registers for 76).
+constexpr int32_t kEarlyVoxels = 1 << 18;
 
 // Largest per-CU workgroup limit a launch configuration may ask for (lbm_tuning.*_wg).
 constexpr int kMaxWgPerCu = 16;

@@ -101,21 +101,43 @@ template <> struct Prec<LBM_FP32_MIXED> {
     static constexpr double kCMin = 1e-10;
 };
 
+// Neighbour lookup, fixed at compile time for the single-domain step kernels and chosen per
+// domain at run time (words != null selects the rank lookup, cax != null the compact one) where
+// domains of several kinds meet.
+enum { NB_DYN = 0, NB_TABLE = 1, NB_RANK = 2, NB_COMPACT = 3 };
+
 // Hardware block b runs on XCD b % 8 as that XCD's (b / 8)-th block; it takes logical tile
-// ((j / C) * 8 + x) * C + j % C (x = b % 8, j = b / 8, C = run length). With gridDim.x a
-// multiple of 8 C this is a bijection of [0, gridDim.x). b and C are uniform over the
-// workgroup, so the division is scalar work, once per workgroup.
-__device__ __forceinline__ int xcd_run_tile(int b, int C) {
-    const int x = b & 7, j = b >> 3;
-    return ((j / C) * 8 + x) * C + (j % C);
+// ((j / C) * 8 + x) * C + j % C (x = b % 8, j = b / 8, C = run length; C = 1 is launch order).
+// With gridDim.x a multiple of 8 C this is a bijection of [0, gridDim.x). j / C is a product with
+// m = ceil(2^31 / C): exact for j < 2^25, as m C - 2^31 < C <= 64 and a grid holds at most
+// 2^30 / 64 blocks.
+__device__ __forceinline__ int xcd_run_tile(int b, int C, uint32_t m) {
+    const uint32_t x = b & 7, j = (uint32_t)b >> 3;
+    const uint32_t r = (uint32_t)(((uint64_t)j * m) >> 31);
+    return (int)((r * 8 + x) * C + (j - r * C));
 }
 
-// Tile of this workgroup. With `reverse` the order runs from the end of the (padded) grid, so a
-// kernel launched after one in forward order starts on the tiles the other finished last, whose
-// lines may still be in the caches; on a padded grid the tiles beyond the pore list still exit.
-__device__ __forceinline__ int logical_block(const StepArgs& a) {
-    const int t = a.xcd_run ? xcd_run_tile((int)blockIdx.x, a.xcd_run) : (int)blockIdx.x;
-    return a.reverse ? (int)gridDim.x - 1 - t : t;
+// Has the arguments a step kernel's loads need in scalar registers from here on. Left alone, the
+// compiler loads each where it is first used, and the address of every next load waits for
+// another trip to the arguments (a quarter of a small kernel's time).
+template <int NB>
+__device__ __forceinline__ void load_args(const StepArgs& a) {
+    asm volatile("" ::"s"(a.N), "s"(a.ld), "s"(a.f), "s"(a.M), "s"(a.phi), "s"(a.ntot),
+                 "s"(a.fresh), "s"(a.face), "s"(a.block), "s"(a.xcd_run), "s"(a.xcd_mul),
+                 "s"(a.tile_first), "s"(a.tile_sign));
+    if (NB == NB_COMPACT)
+        asm volatile("" ::"s"(a.cwave), "s"(a.cax), "s"(a.cdg4), "s"(a.cdg2), "s"(a.cex));
+    if (NB == NB_TABLE) asm volatile("" ::"s"(a.nbr));
+}
+
+// First voxel of this workgroup's tile. In the order from the end (a.tile_sign = -1) the tiles
+// run from the end of the (padded) grid, so a kernel launched after one in forward order starts
+// on the tiles the other finished last, whose lines may still be in the caches; on a padded grid
+// the tiles beyond the pore list still exit. No branch and no value from outside the arguments:
+// the whole prologue waits for one load of them (it took four loads in turn).
+__device__ __forceinline__ int tile_start(const StepArgs& a) {
+    const int t = xcd_run_tile((int)blockIdx.x, a.xcd_run, a.xcd_mul);
+    return (a.tile_first + a.tile_sign * t) * a.block;
 }
 
 // The D3Q7 moment slots of a voxel are stored as four pairs, one row of 2*ld values per pair:
@@ -162,11 +184,6 @@ __device__ __forceinline__ void store_pair(S* __restrict__ M, size_t ld, int k, 
     v.y = y;
     store_once<STREAM>(v, reinterpret_cast<Vec2*>(M) + ((size_t)k * ld + i));
 }
-
-// Neighbour lookup, fixed at compile time for the single-domain step kernels and chosen per
-// domain at run time (words != null selects the rank lookup, cax != null the compact one) where
-// domains of several kinds meet.
-enum { NB_DYN = 0, NB_TABLE = 1, NB_RANK = 2, NB_COMPACT = 3 };
 
 template <int NB>
 __device__ __forceinline__ bool use_compact(const StepArgs& a) {
@@ -352,6 +369,12 @@ __global__ void __launch_bounds__(256) init_kernel(StepArgs a, const double* __r
     for (int k = 1; k < 4; ++k) store_pair<S>(M, a.ld, k, i, (S)0, (S)0);
 }
 
+// a b + c rounded once. The step's arithmetic states each fused operation: left to the compiler,
+// which product of a sum of two is rounded on its own depends on what surrounds it, and the
+// variants of a kernel (lookup, streaming, load order, batched) would differ in the last bit.
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
 // s + v with no contraction into a preceding product.
 __device__ __forceinline__ double add_rounded(double s, double v) {
 #pragma clang fp contract(off)
@@ -364,10 +387,10 @@ __device__ __forceinline__ double add_rounded(double s, double v) {
 // w = 1/9, cs^2 = 2/9.
 template <typename R>
 __device__ __forceinline__ void ab_out(R na, R nb, R uc, R gc, R sgn, R& ao, R& bo) {
-    const R eu = (R)4.5 * (sgn * uc);
+    const R eu = fused((R)4.5, sgn * uc, (R)1);
     const R en = sgn * gc;
-    ao = (R)(1.0 / 9.0) * (na * ((R)1 + eu) + en);
-    bo = (R)(1.0 / 9.0) * (nb * ((R)1 + eu) - en);
+    ao = (R)(1.0 / 9.0) * fused(na, eu, en);
+    bo = (R)(1.0 / 9.0) * fused(nb, eu, -en);
 }
 
 // The same for direction q (1..6) of voxel y, read from its moment slots.
@@ -396,38 +419,12 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, 
     using R = typename P::R;
     const S* M = (const S*)a.M;
     R ain[7], bin[7];
-    if (fresh) {
-        // The initial populations are w_q N at rest; summing them (rather than taking N) keeps
-        // the initial phase bitwise equal to a population-based evaluation.
-        const auto own = load_pair<S>(M, a.ld, 0, i);
-        const R n0 = (R)own.x, n1 = (R)own.y;
-#pragma unroll
-        for (int q = 0; q < 7; ++q) {
-            const R w = q == 0 ? (R)(1.0 / 3.0) : (R)(1.0 / 9.0);
-            ain[q] = w * n0;
-            bin[q] = w * n1;
-        }
-        na = 0.0;
-        nbv = 0.0;
-#pragma unroll
-        for (int q = 0; q < 7; ++q) {
-            na += (double)ain[q];
-            nbv += (double)bin[q];
-        }
-        return;
-    }
+    const auto own = load_pair<S>(M, a.ld, 0, i);
     const Pos pos = pos_of<NB, true, STREAM>(a, i);
     int up[7];
 #pragma unroll
     for (int q = 1; q < 7; ++q) up[q] = nb_stream<NB, STREAM>(a, OPP[q], i, pos);  // i - xi_q
-    if (a.face) {
-        const int fc = a.face[i];
-        if (fc) {
-            na = fc == 1 ? 1.0 : 0.0;
-            nbv = 1.0 - na;
-            return;
-        }
-    }
+    const int fc = a.face ? a.face[i] : 0;
     R sna[7], snb[7], suc[7], sgc[7];
 #pragma unroll
     for (int q = 1; q < 7; ++q) {
@@ -458,11 +455,9 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, 
         }
         ain[0] = (R)0;
         bin[0] = (R)0;
-        const auto own = load_pair<S>(M, a.ld, 0, i);
         na = (double)own.x - sa;
         nbv = (double)own.y - sb;
     } else {
-        const auto own = load_pair<S>(M, a.ld, 0, i);
         ain[0] = (R)(1.0 / 3.0) * (R)own.x;
         bin[0] = (R)(1.0 / 3.0) * (R)own.y;
         na = 0.0;
@@ -476,6 +471,29 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, 
     for (int q = 0; q < 7; ++q) {
         na = add_rounded(na, (double)ain[q]);
         nbv = add_rounded(nbv, (double)bin[q]);
+    }
+    // The exceptions come last, so that no load above waits for a face flag or the fresh flag.
+    if (fc) {
+        na = fc == 1 ? 1.0 : 0.0;
+        nbv = 1.0 - na;
+    }
+    if (fresh) {
+        // The initial populations are w_q N at rest; summing them (rather than taking N) keeps
+        // the initial phase bitwise equal to a population-based evaluation.
+        const R n0 = (R)own.x, n1 = (R)own.y;
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+            const R w = q == 0 ? (R)(1.0 / 3.0) : (R)(1.0 / 9.0);
+            ain[q] = w * n0;
+            bin[q] = w * n1;
+        }
+        na = 0.0;
+        nbv = 0.0;
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+            na += (double)ain[q];
+            nbv += (double)bin[q];
+        }
     }
 }
 
@@ -493,9 +511,10 @@ __device__ __forceinline__ void phase_voxel(const StepArgs& a, int i, bool fresh
     store_once<STREAM>((S)nt, (S*)a.ntot + i);
 }
 
-template <int PREC, bool ODD, int NB, bool STREAM>
+template <int PREC, int NB, bool STREAM>
 __global__ void __launch_bounds__(256) phase_kernel(StepArgs a) {
-    const int i = logical_block(a) * blockDim.x + threadIdx.x;
+    load_args<NB>(a);
+    const int i = tile_start(a) + (int)threadIdx.x;
     if (i < a.N) phase_voxel<PREC, NB, STREAM>(a, i, *a.fresh != 0);
 }
 
@@ -503,13 +522,33 @@ __global__ void __launch_bounds__(256) phase_kernel(StepArgs a) {
 // Fused colour gradient + MRT collision with interfacial terms and body force + recolouring +
 // AA streaming.
 // ------------------------------------------------------------------------------------------
-template <int PREC, bool ODD, int NB = NB_DYN, bool STREAM = false>
+// EARLY: every load of a voxel is issued before the first value is used: the even step's own
+// populations first, as they need no index, then (indices known) the neighbours' phi and the odd
+// step's populations. The scheduler otherwise issues the populations after the gradient has
+// waited for phi, one more round trip per voxel. That is time where a launch has few waves per
+// CU to hide it (32^3 bead pack in FP64, with load_args: 8.7 -> 8.1 us a step; 64^3 in
+// FP32-mixed 9.2 -> 8.5), nothing in a pool, and a loss where the waves in flight compete for the
+// L2 (256^3 FP64 -0.7%, 320^3 FP32-mixed -0.9%): on for domains up to kEarlyVoxels.
+template <int PREC, bool ODD, int NB, bool STREAM, bool EARLY>
 __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
+#pragma clang fp contract(off)
     using P = Prec<PREC>;
     using F = typename P::F;
     using S = typename P::S;
     using R = typename P::R;
     F* f = (F*)a.f;
+    const S* __restrict__ ph = (const S*)a.phi;
+
+    F fraw[19];
+    if (EARLY && !ODD) {
+#pragma unroll
+        for (int q = 0; q < 19; ++q) fraw[q] = load_in<ODD, F, STREAM>(f, a, q, i, 0);
+    }
+    S phi_own = 0, n_own = 0;
+    if (EARLY) {
+        phi_own = ph[i];
+        n_own = ((const S*)a.ntot)[i];
+    }
 
     int r[19];           // gradient neighbours (phi index)
     uint32_t mirror = 0; // bit q: streaming along q bounces back although r[q] is a pore index
@@ -530,44 +569,59 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
     // increasing q, one term at a time: every product is exact (a power of two times phi), so
     // the sum is the same correctly rounded chain in any implementation that keeps this order.
     // That matters where |C| is small, since n = C/|C| amplifies a rounding difference in C.
-    const S* __restrict__ ph = (const S*)a.phi;
+    S praw[19];
+#pragma unroll
+    for (int q = 1; q < 19; ++q) praw[q] = ph[r[q]];
+    if (EARLY && ODD) {
+#pragma unroll
+        for (int q = 0; q < 19; ++q)
+            fraw[q] = load_in<ODD, F, STREAM>(f, a, q, i, RS(OPP[q]));
+    }
+    if (EARLY) __builtin_amdgcn_sched_barrier(0);
     R p[19];
 #pragma unroll
-    for (int q = 1; q < 19; ++q) p[q] = (R)ph[r[q]];
+    for (int q = 1; q < 19; ++q) p[q] = (R)praw[q];
     R Cx = 0, Cy = 0, Cz = 0;
 #pragma unroll
     for (int q = 1; q < 19; ++q) {
         const R w = q < 7 ? (R)1 : (R)0.5;
-        if (CX[q]) Cx += (w * CX[q]) * p[q];
-        if (CY[q]) Cy += (w * CY[q]) * p[q];
-        if (CZ[q]) Cz += (w * CZ[q]) * p[q];
+        if (CX[q]) Cx = fused(w * CX[q], p[q], Cx);
+        if (CY[q]) Cy = fused(w * CY[q], p[q], Cy);
+        if (CZ[q]) Cz = fused(w * CZ[q], p[q], Cz);
     }
     // |C| <= kCMin is an unresolved gradient (a cancellation whose residue is rounding): it
     // counts as zero, so that n never takes a direction decided by rounding.
-    const R c2 = Cx * Cx + Cy * Cy + Cz * Cz;
+    const R c2 = fused(Cz, Cz, fused(Cy, Cy, Cx * Cx));
     const bool resolved = c2 > (R)(P::kCMin * P::kCMin);
     const R cm = resolved ? sqrt(c2) : (R)0;
     const R ic = resolved ? (R)1 / cm : (R)0;
     const R nx = Cx * ic, ny = Cy * ic, nz = Cz * ic;
 
     // Incoming populations (f, or f - t in deviation storage).
+    if (!EARLY) {
+#pragma unroll
+        for (int q = 0; q < 19; ++q)
+            fraw[q] = load_in<ODD, F, STREAM>(f, a, q, i, RS(OPP[q]));
+        phi_own = ph[i];
+        n_own = ((const S*)a.ntot)[i];
+    }
     R fl[19];
 #pragma unroll
-    for (int q = 0; q < 19; ++q) fl[q] = (R)load_in<ODD, F, STREAM>(f, a, q, i, RS(OPP[q]));
+    for (int q = 0; q < 19; ++q) fl[q] = (R)fraw[q];
 
     // rho (or rho - 1 in deviation storage) and j.
     R rho = 0, jx = 0, jy = 0, jz = 0;
 #pragma unroll
     for (int q = 0; q < 19; ++q) {
         rho += fl[q];
-        jx += CX[q] * fl[q];
-        jy += CY[q] * fl[q];
-        jz += CZ[q] * fl[q];
+        if (CX[q]) jx += CX[q] * fl[q];
+        if (CY[q]) jy += CY[q] * fl[q];
+        if (CZ[q]) jz += CZ[q] * fl[q];
     }
-    const R jj = jx * jx + jy * jy + jz * jz;
+    const R jj = fused(jz, jz, fused(jy, jy, jx * jx));
 
-    const R phi_i = (R)ph[i];
-    const R nt = (R)((const S*)a.ntot)[i];
+    const R phi_i = (R)phi_own;
+    const R nt = (R)n_own;
     // Recolouring with the flow velocity u = j + F/2 (rho0 = 1): the outgoing D3Q7 populations
     // are w_q [N_a (1 + u.xi_q/cs^2) + G.xi_q] and w_q [N_b (1 + u.xi_q/cs^2) - G.xi_q] with
     // G = beta (N_a N_b / N) n; their 8 defining numbers go to the voxel's own moment slots.
@@ -583,37 +637,40 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
     store_pair<S, STREAM>(M, ld, 2, i, (S)uy, (S)(seg * ny));
     store_pair<S, STREAM>(M, ld, 3, i, (S)uz, (S)(seg * nz));
 
-    const R nu = (R)0.5 * ((R)1 + phi_i) * (R)a.nu_a + (R)0.5 * ((R)1 - phi_i) * (R)a.nu_b;
-    const R sp = (R)1 / ((R)3 * nu + (R)0.5);
+    const R nu = fused((R)0.5 * ((R)1 + phi_i), (R)a.nu_a, (R)0.5 * ((R)1 - phi_i) * (R)a.nu_b);
+    const R sp = (R)1 / fused((R)3, nu, (R)0.5);
     const R sm = (R)8 * ((R)2 - sp) / ((R)8 - sp);
 
     // Image of the alpha|C| equilibrium-moment terms in population space (even in xi):
     // e-row -19 g, 3pxx (g/2)(3nx^2-1), pww (g/2)(ny^2-nz^2), pxy (g/2)nx ny, ... ; g = alpha|C|.
     const R g = (R)a.alpha * cm;
-    const R hxx = g * ((R)3 * nx * nx - (R)1);
-    const R hww = g * (ny * ny - nz * nz);
-    const R d_rest = g * (R)(5.0 / 21.0);
-    const R d_ax = g * (R)(11.0 / 126.0);
-    const R d_dg = -g * (R)(8.0 / 126.0);
-    const R dX = d_ax + hxx * (R)(1.0 / 36.0);
-    const R dY = d_ax - hxx * (R)(1.0 / 72.0) + hww * (R)(1.0 / 24.0);
-    const R dZ = d_ax - hxx * (R)(1.0 / 72.0) - hww * (R)(1.0 / 24.0);
-    const R dXY = d_dg + hxx * (R)(1.0 / 72.0) + hww * (R)(1.0 / 24.0);
-    const R dXZ = d_dg + hxx * (R)(1.0 / 72.0) - hww * (R)(1.0 / 24.0);
-    const R dYZ = d_dg - hxx * (R)(1.0 / 36.0);
+    const R hxx = g * fused((R)3 * nx, nx, (R)-1);
+    const R hww = g * fused(ny, ny, -(nz * nz));
+    const R hx36 = hxx * (R)(1.0 / 36.0), hx72 = hxx * (R)(1.0 / 72.0);
+    const R c_ax = (R)(11.0 / 126.0), c_dg = (R)(-8.0 / 126.0), c_w = (R)(1.0 / 24.0);
+    const R dX = fused(g, c_ax, hx36), dYZ = fused(g, c_dg, -hx36);
+    const R dY = fused(hww, c_w, fused(g, c_ax, -hx72));
+    const R dZ = fused(hww, -c_w, fused(g, c_ax, -hx72));
+    const R dXY = fused(hww, c_w, fused(g, c_dg, hx72));
+    const R dXZ = fused(hww, -c_w, fused(g, c_dg, hx72));
     const R gxy = g * nx * ny * (R)0.125, gxz = g * nx * nz * (R)0.125;
     const R gyz = g * ny * nz * (R)0.125;
 
     // Even equilibrium part (per velocity class) and odd part 3 t xi.j. The rest weight t_q
     // multiplies rho in the even part; with deviation storage both sides carry -t_q.
-    const R base = rho - (R)1.5 * jj;
+    const R base = fused((R)-1.5, jj, rho);
     R fs[19];
-    fs[0] = fl[0] - sp * (fl[0] - ((R)(1.0 / 3.0) * base + d_rest));
+    const R e0 = fused(g, (R)(5.0 / 21.0), (R)(1.0 / 3.0) * base);
+    fs[0] = fused(-sp, fl[0] - e0, fl[0]);
 #pragma unroll
     for (int q = 1; q < 19; q += 2) {
         const int qb = q + 1;
         const R t = (R)tw(q);
-        const R ej = CX[q] * jx + CY[q] * jy + CZ[q] * jz;
+        const R e3[3] = {CX[q] * jx, CY[q] * jy, CZ[q] * jz};
+        const R ej = CX[q] && CY[q] ? e3[0] + e3[1]
+                     : CX[q] && CZ[q] ? e3[0] + e3[2]
+                     : CY[q] && CZ[q] ? e3[1] + e3[2]
+                     : CX[q] ? e3[0] : CY[q] ? e3[1] : e3[2];
         const R ef = (R)(CX[q] * a.F[0] + CY[q] * a.F[1] + CZ[q] * a.F[2]);
         R dq;
         if (q == 1) dq = dX;
@@ -622,15 +679,12 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
         else if (q < 11) dq = dXY + gxy * (R)(CX[q] * CY[q]);
         else if (q < 15) dq = dXZ + gxz * (R)(CX[q] * CZ[q]);
         else dq = dYZ + gyz * (R)(CY[q] * CZ[q]);
-        const R ep = t * (base + (R)4.5 * ej * ej) + dq;
+        const R ep = fused(t, fused((R)4.5 * ej, ej, base), dq);
         const R em = (R)3 * t * ej;
-        const R fp = (R)0.5 * (fl[q] + fl[qb]);
-        const R fm = (R)0.5 * (fl[q] - fl[qb]);
-        const R rp = sp * (fp - ep);
-        const R rm = sm * (fm - em);
-        const R fo = (R)3 * t * ef;
-        fs[q] = fl[q] - rp - rm + fo;
-        fs[qb] = fl[qb] - rp + rm - fo;
+        const R rp = fused((R)0.5, fl[q] + fl[qb], -ep);
+        const R rm = fused((R)0.5, fl[q] - fl[qb], -em);
+        fs[q] = fused((R)3 * t, ef, fused(-sm, rm, fused(-sp, rp, fl[q])));
+        fs[qb] = fused((R)-3 * t, ef, fused(sm, rm, fused(-sp, rp, fl[qb])));
     }
 
 #pragma unroll
@@ -639,10 +693,11 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
     if (i == 0) *a.fresh = 0;        // the state now holds outgoing moments
 }
 
-template <int PREC, bool ODD, int NB, bool STREAM>
+template <int PREC, bool ODD, int NB, bool STREAM, bool EARLY>
 __global__ void __launch_bounds__(256) collide_kernel(StepArgs a) {
-    const int i = logical_block(a) * blockDim.x + threadIdx.x;
-    if (i < a.N) collide_voxel<PREC, ODD, NB, STREAM>(a, i);
+    load_args<NB>(a);
+    const int i = tile_start(a) + (int)threadIdx.x;
+    if (i < a.N) collide_voxel<PREC, ODD, NB, STREAM, EARLY>(a, i);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -670,10 +725,11 @@ __device__ __forceinline__ T load_const(const T* p) {
     return out;
 }
 
-template <int PREC, bool ODD, int NB>
+template <int PREC, int NB>
 __global__ void __launch_bounds__(256) phase_batched(BatchArgs b) {
     const int nt = *as_const(b.ntiles);
-    const int first = b.xcd ? xcd_run_tile((int)blockIdx.x, kXcdRun) : (int)blockIdx.x;
+    const int first = b.xcd ? xcd_run_tile((int)blockIdx.x, kXcdRun, xcd_mul_of(kXcdRun))
+                            : (int)blockIdx.x;
     for (int t = first; t < nt; t += gridDim.x) {
         const int d = as_const(b.tile_dom)[t];
         const StepArgs a = load_const(b.doms + d);
@@ -685,12 +741,13 @@ __global__ void __launch_bounds__(256) phase_batched(BatchArgs b) {
 template <int PREC, bool ODD, int NB>
 __global__ void __launch_bounds__(256) collide_batched(BatchArgs b) {
     const int nt = *as_const(b.ntiles);
-    const int first = b.xcd ? xcd_run_tile((int)blockIdx.x, kXcdRun) : (int)blockIdx.x;
+    const int first = b.xcd ? xcd_run_tile((int)blockIdx.x, kXcdRun, xcd_mul_of(kXcdRun))
+                            : (int)blockIdx.x;
     for (int t = first; t < nt; t += gridDim.x) {
         const int d = as_const(b.tile_dom)[t];
         const StepArgs a = load_const(b.doms + d);
         const int i = (t - as_const(b.tile_first)[d]) * blockDim.x + threadIdx.x;
-        if (i < a.N) collide_voxel<PREC, ODD, NB>(a, i);
+        if (i < a.N) collide_voxel<PREC, ODD, NB, false, false>(a, i);
     }
 }
 
@@ -979,11 +1036,6 @@ __global__ void __launch_bounds__(kInletBlocks) inlet_finish_kernel(
 
 int grid_for(const StepArgs& a, int block) { return (a.N + block - 1) / block; }
 
-dim3 step_grid(const StepArgs& a) {
-    const int g = 8 * a.xcd_run;  // XCD-aware order: whole runs on every XCD
-    return dim3(a.xcd_run ? ((a.nblocks + g - 1) / g) * g : a.nblocks);
-}
-
 }  // namespace
 
 // ------------------------------------------------------------------------------------------
@@ -1006,24 +1058,6 @@ dim3 step_grid(const StepArgs& a) {
             hipLaunchKernelGGL((KERNEL<P, false, NBV>), GRID, BLOCK, 0, s, __VA_ARGS__);       \
     } while (0)
 
-// `lds`: dynamic LDS per workgroup, which the step kernels do not use; it only bounds how many
-// workgroups a CU holds at once (see step_kernel_lds).
-#define LBM_LAUNCH_ODD_NB_ST(KERNEL, P, NBV, GRID, BLOCK, ...)                                 \
-    do {                                                                                       \
-        if (odd && stream)                                                                     \
-            hipLaunchKernelGGL((KERNEL<P, true, NBV, true>), GRID, BLOCK, lds, s,              \
-                               __VA_ARGS__);                                                   \
-        else if (odd)                                                                          \
-            hipLaunchKernelGGL((KERNEL<P, true, NBV, false>), GRID, BLOCK, lds, s,             \
-                               __VA_ARGS__);                                                   \
-        else if (stream)                                                                       \
-            hipLaunchKernelGGL((KERNEL<P, false, NBV, true>), GRID, BLOCK, lds, s,             \
-                               __VA_ARGS__);                                                   \
-        else                                                                                   \
-            hipLaunchKernelGGL((KERNEL<P, false, NBV, false>), GRID, BLOCK, lds, s,            \
-                               __VA_ARGS__);                                                   \
-    } while (0)
-
 #define LBM_PREC_SWITCH(PREC, LAUNCH, KERNEL, ...)                                             \
     do {                                                                                       \
         if ((PREC) == LBM_FP32_DEV)                                                            \
@@ -1036,9 +1070,6 @@ dim3 step_grid(const StepArgs& a) {
 
 #define LBM_DISPATCH(KERNEL, GRID, BLOCK, ...)                                                 \
     LBM_PREC_SWITCH(a.prec, LBM_LAUNCH_ODD, KERNEL, GRID, BLOCK, __VA_ARGS__)
-
-#define LBM_DISPATCH_NB_ST(KERNEL, GRID, BLOCK, ...)                                           \
-    LBM_PREC_SWITCH(a.prec, LBM_LAUNCH_ODD_NB_ST, KERNEL, NB, GRID, BLOCK, __VA_ARGS__)
 
 hipError_t launch_init(const StepArgs& a, const double* phi0, int block, hipStream_t s) {
     (void)block;
@@ -1054,57 +1085,50 @@ hipError_t launch_init(const StepArgs& a, const double* phi0, int block, hipStre
     return hipGetLastError();
 }
 
-// Step kernels: also on the neighbour lookup, fixed per domain, and on streaming accesses.
-template <int NB>
-hipError_t launch_phase_nb(const StepArgs& a, bool odd, int block, bool stream, unsigned lds,
-                           hipStream_t s) {
-    LBM_DISPATCH_NB_ST(phase_kernel, step_grid(a), dim3(block), a);
-    return hipGetLastError();
+// The step kernel (0: phase, 1: collide) of a domain, by precision, parity, neighbour lookup,
+// streaming accesses and load order. The phase kernel is the same at both parities.
+using StepKernel = void (*)(StepArgs);
+
+template <int P, int NB, bool ST>
+static StepKernel step_kernel_fn(const StepArgs& a, int kernel, bool odd) {
+    if (kernel == 0) return phase_kernel<P, NB, ST>;
+    if (!ST && a.N <= kEarlyVoxels)
+        return odd ? collide_kernel<P, true, NB, false, true>
+                   : collide_kernel<P, false, NB, false, true>;
+    return odd ? collide_kernel<P, true, NB, ST, false> : collide_kernel<P, false, NB, ST, false>;
 }
 
-template <int NB>
-hipError_t launch_collide_nb(const StepArgs& a, bool odd, int block, bool stream, unsigned lds,
-                             hipStream_t s) {
-    LBM_DISPATCH_NB_ST(collide_kernel, step_grid(a), dim3(block), a);
-    return hipGetLastError();
+template <int P, bool ST>
+static StepKernel step_kernel_fn_nb(const StepArgs& a, int kernel, bool odd) {
+    return a.words ? step_kernel_fn<P, NB_RANK, ST>(a, kernel, odd)
+           : a.cax ? step_kernel_fn<P, NB_COMPACT, ST>(a, kernel, odd)
+                     : step_kernel_fn<P, NB_TABLE, ST>(a, kernel, odd);
 }
 
+template <bool ST>
+static StepKernel step_kernel_fn_prec(const StepArgs& a, int kernel, bool odd) {
+    if (a.prec == LBM_FP32_DEV) return step_kernel_fn_nb<LBM_FP32_DEV, ST>(a, kernel, odd);
+    if (a.prec == LBM_FP32_MIXED) return step_kernel_fn_nb<LBM_FP32_MIXED, ST>(a, kernel, odd);
+    return step_kernel_fn_nb<LBM_FP64, ST>(a, kernel, odd);
+}
+
+static StepKernel step_kernel(const StepArgs& a, int kernel, bool odd, bool stream) {
+    return stream ? step_kernel_fn_prec<true>(a, kernel, odd)
+                  : step_kernel_fn_prec<false>(a, kernel, odd);
+}
+
+// `lds`: dynamic LDS per workgroup, which the step kernels do not use; it only bounds how many
+// workgroups a CU holds at once (see step_kernel_lds).
 hipError_t launch_phase(const StepArgs& a, bool odd, int block, bool stream, unsigned lds,
                         hipStream_t s) {
-    return a.words ? launch_phase_nb<NB_RANK>(a, odd, block, stream, lds, s)
-           : a.cax ? launch_phase_nb<NB_COMPACT>(a, odd, block, stream, lds, s)
-                   : launch_phase_nb<NB_TABLE>(a, odd, block, stream, lds, s);
+    hipLaunchKernelGGL(step_kernel(a, 0, odd, stream), dim3(a.grid), dim3(block), lds, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_collide(const StepArgs& a, bool odd, int block, bool stream, unsigned lds,
                           hipStream_t s) {
-    return a.words ? launch_collide_nb<NB_RANK>(a, odd, block, stream, lds, s)
-           : a.cax ? launch_collide_nb<NB_COMPACT>(a, odd, block, stream, lds, s)
-                   : launch_collide_nb<NB_TABLE>(a, odd, block, stream, lds, s);
-}
-
-// The step kernel (0: phase, 1: collide) that launch_phase / launch_collide would run.
-template <int P, int NB, bool ST>
-static const void* step_kernel_fn(int kernel, bool odd) {
-    if (kernel == 0)
-        return odd ? (const void*)phase_kernel<P, true, NB, ST>
-                   : (const void*)phase_kernel<P, false, NB, ST>;
-    return odd ? (const void*)collide_kernel<P, true, NB, ST>
-               : (const void*)collide_kernel<P, false, NB, ST>;
-}
-
-template <int P, bool ST>
-static const void* step_kernel_fn_nb(const StepArgs& a, int kernel, bool odd) {
-    return a.words ? step_kernel_fn<P, NB_RANK, ST>(kernel, odd)
-           : a.cax ? step_kernel_fn<P, NB_COMPACT, ST>(kernel, odd)
-                   : step_kernel_fn<P, NB_TABLE, ST>(kernel, odd);
-}
-
-template <bool ST>
-static const void* step_kernel_fn_prec(const StepArgs& a, int kernel, bool odd) {
-    if (a.prec == LBM_FP32_DEV) return step_kernel_fn_nb<LBM_FP32_DEV, ST>(a, kernel, odd);
-    if (a.prec == LBM_FP32_MIXED) return step_kernel_fn_nb<LBM_FP32_MIXED, ST>(a, kernel, odd);
-    return step_kernel_fn_nb<LBM_FP64, ST>(a, kernel, odd);
+    hipLaunchKernelGGL(step_kernel(a, 1, odd, stream), dim3(a.grid), dim3(block), lds, s, a);
+    return hipGetLastError();
 }
 
 // Occupancy limit. Fewer resident waves can be faster for these kernels: their in-flight
@@ -1126,8 +1150,7 @@ hipError_t step_kernel_lds(const StepArgs& a, int kernel, int block, bool stream
     if (e != hipSuccess) return e;
     unsigned need = 0;
     for (int odd = 0; odd < 2; ++odd) {
-        const void* fn = stream ? step_kernel_fn_prec<true>(a, kernel, odd != 0)
-                                : step_kernel_fn_prec<false>(a, kernel, odd != 0);
+        const void* fn = (const void*)step_kernel(a, kernel, odd != 0, stream);
         auto blocks = [&](unsigned bytes, int* n) {
             return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, fn, block, bytes);
         };
@@ -1164,28 +1187,32 @@ hipError_t launch_reduce(const StepArgs& a, bool odd, double* partials, double* 
 #define LBM_DISPATCH_B(KERNEL, GRID, BLOCK, ...)                                               \
     LBM_PREC_SWITCH(prec, LBM_LAUNCH_ODD, KERNEL, GRID, BLOCK, __VA_ARGS__)
 
-#define LBM_DISPATCH_B_NB(KERNEL, GRID, BLOCK, ...)                                            \
+#define LBM_LAUNCH_NB(KERNEL, P, NBV, GRID, BLOCK, ...)                                        \
+    hipLaunchKernelGGL((KERNEL<P, NBV>), GRID, BLOCK, 0, s, __VA_ARGS__)
+
+#define LBM_DISPATCH_B_NB(LAUNCH, KERNEL, GRID, BLOCK, ...)                                            \
     do {                                                                                       \
         if (lookup == LBM_NBR_TABLE)                                                           \
-            LBM_PREC_SWITCH(prec, LBM_LAUNCH_ODD_NB, KERNEL, NB_TABLE, GRID, BLOCK, __VA_ARGS__); \
+            LBM_PREC_SWITCH(prec, LAUNCH, KERNEL, NB_TABLE, GRID, BLOCK, __VA_ARGS__); \
         else if (lookup == LBM_NBR_COMPACT)                                                    \
-            LBM_PREC_SWITCH(prec, LBM_LAUNCH_ODD_NB, KERNEL, NB_COMPACT, GRID, BLOCK,          \
+            LBM_PREC_SWITCH(prec, LAUNCH, KERNEL, NB_COMPACT, GRID, BLOCK,          \
                             __VA_ARGS__);                                                      \
         else if (lookup == LBM_NBR_RANK)                                                       \
-            LBM_PREC_SWITCH(prec, LBM_LAUNCH_ODD_NB, KERNEL, NB_RANK, GRID, BLOCK, __VA_ARGS__); \
+            LBM_PREC_SWITCH(prec, LAUNCH, KERNEL, NB_RANK, GRID, BLOCK, __VA_ARGS__); \
         else                                                                                   \
-            LBM_PREC_SWITCH(prec, LBM_LAUNCH_ODD_NB, KERNEL, NB_DYN, GRID, BLOCK, __VA_ARGS__); \
+            LBM_PREC_SWITCH(prec, LAUNCH, KERNEL, NB_DYN, GRID, BLOCK, __VA_ARGS__); \
     } while (0)
 
 hipError_t launch_phase_batched(const BatchArgs& b, int prec, bool odd, int lookup, int grid,
                                 int block, hipStream_t s) {
-    LBM_DISPATCH_B_NB(phase_batched, dim3(grid), dim3(block), b);
+    (void)odd;
+    LBM_DISPATCH_B_NB(LBM_LAUNCH_NB, phase_batched, dim3(grid), dim3(block), b);
     return hipGetLastError();
 }
 
 hipError_t launch_collide_batched(const BatchArgs& b, int prec, bool odd, int lookup, int grid,
                                   int block, hipStream_t s) {
-    LBM_DISPATCH_B_NB(collide_batched, dim3(grid), dim3(block), b);
+    LBM_DISPATCH_B_NB(LBM_LAUNCH_ODD_NB, collide_batched, dim3(grid), dim3(block), b);
     return hipGetLastError();
 }
 
