@@ -64,9 +64,9 @@ struct lbm_domain {
     lbm::RowWord* words = nullptr; // row segments (rank mode)
     bool rank = false;
     // Compact lookup (compact mode; layout in lbm_prepass.h)
-    uint4* cax = nullptr;
-    uint4* cdg4 = nullptr;
-    uint2* cdg2 = nullptr;
+    uint2* cn8 = nullptr;
+    uint4* cn16 = nullptr;
+    uint4* cwide = nullptr;
     int32_t* cwave = nullptr;
     int32_t* cex = nullptr;
     bool compact = false;
@@ -138,9 +138,9 @@ struct lbm_domain {
         a.tile_sign = sched == 3 ? -1 : 1;
         a.coord = rank ? coord : nullptr;
         a.words = rank ? words : nullptr;
-        a.cax = compact ? cax : nullptr;
-        a.cdg4 = compact ? cdg4 : nullptr;
-        a.cdg2 = compact ? cdg2 : nullptr;
+        a.cn8 = compact ? cn8 : nullptr;
+        a.cn16 = compact ? cn16 : nullptr;
+        a.cwide = compact ? cwide : nullptr;
         a.cwave = compact ? cwave : nullptr;
         a.cex = compact ? cex : nullptr;
         a.nx = p.nx;

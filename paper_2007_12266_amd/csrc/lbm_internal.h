@@ -47,11 +47,11 @@ struct StepArgs {
     // Rank lookup of neighbours (used instead of nbr when words != null):
     const uint32_t* coord;   // [ld] packed (x, y, z) of each pore voxel
     const RowWord* words;    // [nz][ny][W] 64-voxel row segments
-    // Compact lookup (used instead of nbr when cax != null; layout in lbm_prepass.h):
-    const uint4* cax;        // [ld] mask and codes of q = 1..6
-    const uint4* cdg4;       // [ld] codes of q = 7..14
-    const uint2* cdg2;       // [ld] codes of q = 15..18
-    const int32_t* cwave;    // [ld / 64][kCompactWaveInts] bases and exception row
+    // Compact lookup (used instead of nbr when cwave != null; layout in lbm_prepass.h):
+    const uint2* cn8;        // [ld] byte waves: axis codes; 16-bit waves: codes of q = 15..18
+    const uint4* cn16;       // [ld] codes of q = 7..18 (byte waves) or 7..14
+    const uint4* cwide;      // [ld] 16-bit waves: mask and codes of q = 1..6
+    const int32_t* cwave;    // [ld / 64][kCompactWaveInts] bases, exception row, kind
     const int32_t* cex;      // [exception waves][18][64] int32 targets
     int32_t nx, ny, nz, W;
     int32_t periodic;        // bit a set: axis a is periodic

@@ -102,7 +102,7 @@ template <> struct Prec<LBM_FP32_MIXED> {
 };
 
 // Neighbour lookup, fixed at compile time for the single-domain step kernels and chosen per
-// domain at run time (words != null selects the rank lookup, cax != null the compact one) where
+// domain at run time (words != null selects the rank lookup, cwave != null the compact one) where
 // domains of several kinds meet.
 enum { NB_DYN = 0, NB_TABLE = 1, NB_RANK = 2, NB_COMPACT = 3 };
 
@@ -126,7 +126,7 @@ __device__ __forceinline__ void load_args(const StepArgs& a) {
                  "s"(a.fresh), "s"(a.face), "s"(a.block), "s"(a.xcd_run), "s"(a.xcd_mul),
                  "s"(a.tile_first), "s"(a.tile_sign));
     if (NB == NB_COMPACT)
-        asm volatile("" ::"s"(a.cwave), "s"(a.cax), "s"(a.cdg4), "s"(a.cdg2), "s"(a.cex));
+        asm volatile("" ::"s"(a.cwave), "s"(a.cn8), "s"(a.cn16), "s"(a.cwide), "s"(a.cex));
     if (NB == NB_TABLE) asm volatile("" ::"s"(a.nbr));
 }
 
@@ -187,12 +187,12 @@ __device__ __forceinline__ void store_pair(S* __restrict__ M, size_t ld, int k, 
 
 template <int NB>
 __device__ __forceinline__ bool use_compact(const StepArgs& a) {
-    return NB == NB_COMPACT || (NB == NB_DYN && a.cax);
+    return NB == NB_COMPACT || (NB == NB_DYN && a.cwave);
 }
 
 template <int NB>
 __device__ __forceinline__ bool use_table(const StepArgs& a) {
-    return NB == NB_TABLE || (NB == NB_DYN && !a.words && !a.cax);
+    return NB == NB_TABLE || (NB == NB_DYN && !a.words && !a.cwave);
 }
 
 template <int NB>
@@ -214,38 +214,57 @@ struct Pos {
     int cn[18];
 };
 
-// Compact lookup of all 18 neighbours of pore voxel i: a 16-bit code above the wave's pore or
-// tail base for each direction (bit q of the mask chooses), or the int32 entries of an exception
-// wave. The wave record is read once per voxel; with WAVE, the caller's waves hold 64 consecutive
-// pore voxels (tiles of a multiple of 64 starting at a multiple of 64), so the record's address
-// is wave-uniform: it is read with scalar loads and the exception test is one scalar branch.
-// Directions a kernel never asks for are dead code (the phase kernel reads only the axis record).
+// Compact lookup of all 18 neighbours of pore voxel i: a code above the wave's pore or tail base
+// for each direction (a mask bit chooses), 8 bits wide in byte waves and 16 bits in the others,
+// or the int32 entries of an exception wave (layout in lbm_prepass.h). The wave record is read
+// once per voxel; with WAVE, the caller's waves hold 64 consecutive pore voxels (tiles of a
+// multiple of 64 starting at a multiple of 64), so the record's address is wave-uniform: it is
+// read with scalar loads and the tests of the wave's kind are scalar branches. Directions a
+// kernel never asks for are dead code (the phase kernel reads only n8 of a byte wave, and only
+// wide of a 16-bit one). Byte codes take 13 and 6 bytes per voxel off the two kernels (80% byte
+// waves); with 16-bit codes alone 256^3 FP64 took 2.5% longer, 320^3 FP32-mixed 3.1%, 512^3
+// FP64 2.5%, a pool of 16 FP32-mixed members 4.5%. Giving exception waves byte codes too, above
+// bases for each of up to four stretches of lanes, saved no time.
 template <bool WAVE, bool STREAM>
 __device__ __forceinline__ void compact_all(const StepArgs& a, int i, int (&cn)[18]) {
+    typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t U2 __attribute__((ext_vector_type(2)));
     const int w = WAVE ? __builtin_amdgcn_readfirstlane(i >> 6) : (i >> 6);
     const auto* rec = as_const(a.cwave) + (size_t)w * kCompactWaveInts;
-    const int32_t row = rec[kCompactExRow];
+    const int32_t row = rec[kCompactExRow], kind = rec[kCompactKind];
     if (row >= 0) {
         const int32_t* ex = a.cex + (size_t)row * 18 * 64 + (i & 63);
 #pragma unroll
         for (int q = 1; q < 19; ++q) cn[q - 1] = load_once<STREAM>(ex + (q - 1) * 64);
         return;
     }
-    typedef uint32_t U4 __attribute__((ext_vector_type(4)));
-    typedef uint32_t U2 __attribute__((ext_vector_type(2)));
-    const U4 ax = load_once<STREAM>(reinterpret_cast<const U4*>(a.cax) + i);
-    const U4 d4 = load_once<STREAM>(reinterpret_cast<const U4*>(a.cdg4) + i);
-    const U2 d2 = load_once<STREAM>(reinterpret_cast<const U2*>(a.cdg2) + i);
-    const uint32_t words[9] = {ax.y, ax.z, ax.w, d4.x, d4.y, d4.z, d4.w, d2.x, d2.y};
+    const U2 n8 = load_once<STREAM>(reinterpret_cast<const U2*>(a.cn8) + i);
+    const U4 n16 = load_once<STREAM>(reinterpret_cast<const U4*>(a.cn16) + i);
+    // Byte code and mask bit of direction q.
+    auto byte_code = [&](int q) {
+        const uint32_t words[5] = {n8.x, n8.y, n16.x, n16.y, n16.z};
+        const int k = q < 7 ? q - 1 : q + 1;
+        return (words[k >> 2] >> (8 * (k & 3))) & 0xffu;
+    };
+    auto byte_tail = [&](int q) { return (q < 7 ? n8.y >> (16 + q - 1) : n16.w >> (q - 7)) & 1u; };
+    // Both bases as wave-uniform values, then a per-lane select (a select of the two addresses
+    // would turn the scalar loads into vector ones).
+    auto target = [&](int q, uint32_t tail, uint32_t code) {
+        const int32_t pb = WAVE ? __builtin_amdgcn_readfirstlane(rec[q - 1]) : rec[q - 1];
+        const int32_t tb = WAVE ? __builtin_amdgcn_readfirstlane(rec[18 + q - 1]) : rec[18 + q - 1];
+        return (tail ? tb : pb) + (int)code;
+    };
+    if (kind == 1) {
+#pragma unroll
+        for (int q = 1; q < 19; ++q) cn[q - 1] = target(q, byte_tail(q), byte_code(q));
+        return;
+    }
+    const U4 wide = load_once<STREAM>(reinterpret_cast<const U4*>(a.cwide) + i);
+    const uint32_t words[9] = {wide.y, wide.z, wide.w, n16.x, n16.y, n16.z, n16.w, n8.x, n8.y};
 #pragma unroll
     for (int q = 1; q < 19; ++q) {
         const uint32_t word = words[(q - 1) >> 1];
-        const uint32_t code = (q & 1) ? (word & 0xffffu) : (word >> 16);
-        // Both bases as wave-uniform values, then a per-lane select (a select of the two
-        // addresses would turn the scalar loads into vector ones).
-        const int32_t pb = WAVE ? __builtin_amdgcn_readfirstlane(rec[q - 1]) : rec[q - 1];
-        const int32_t tb = WAVE ? __builtin_amdgcn_readfirstlane(rec[18 + q - 1]) : rec[18 + q - 1];
-        cn[q - 1] = (((ax.x >> q) & 1u) ? tb : pb) + (int)code;
+        cn[q - 1] = target(q, (wide.x >> q) & 1u, (q & 1) ? (word & 0xffffu) : (word >> 16));
     }
 }
 
@@ -1101,7 +1120,7 @@ static StepKernel step_kernel_fn(const StepArgs& a, int kernel, bool odd) {
 template <int P, bool ST>
 static StepKernel step_kernel_fn_nb(const StepArgs& a, int kernel, bool odd) {
     return a.words ? step_kernel_fn<P, NB_RANK, ST>(a, kernel, odd)
-           : a.cax ? step_kernel_fn<P, NB_COMPACT, ST>(a, kernel, odd)
+           : a.cwave ? step_kernel_fn<P, NB_COMPACT, ST>(a, kernel, odd)
                      : step_kernel_fn<P, NB_TABLE, ST>(a, kernel, odd);
 }
 

@@ -363,30 +363,32 @@ std::string prepass(const lbm_params& p, const int32_t* labels, int32_t n_labels
 std::string build_compact_lookup(Prepass& pre) {
     CompactNbr& c = pre.compact;
     const int64_t ld = pre.ld, n = pre.n_pore, nw = ld / 64;
-    c.ax.assign((size_t)ld * 4, 0u);
-    c.dg4.assign((size_t)ld * 4, 0u);
-    c.dg2.assign((size_t)ld * 2, 0u);
+    c.n8.assign((size_t)ld * 2, 0u);
+    c.n16.assign((size_t)ld * 4, 0u);
+    c.wide.assign((size_t)ld * 4, 0u);
     c.wave.assign((size_t)nw * kCompactWaveInts, 0);
     auto target = [&](int q, int64_t i) -> int64_t { return pre.nbr[(size_t)(q - 1) * ld + i]; };
-    // Bases per wave and direction; waves that do not fit 16-bit codes become exceptions.
+    // Bases per wave and direction; waves whose codes all fit 8 bits become byte waves, those
+    // that do not fit 16 bits exceptions.
     std::vector<uint8_t> is_ex((size_t)nw, 0);
     parallel_for(nw, [&](int64_t w0, int64_t w1) {
         for (int64_t w = w0; w < w1; ++w) {
             int32_t* rec = &c.wave[(size_t)w * kCompactWaveInts];
-            bool fits = true;
-            for (int q = 1; q < 19 && fits; ++q) {
+            int64_t spread = 0;
+            for (int q = 1; q < 19 && spread <= 0xffff; ++q) {
                 int64_t plo = INT64_MAX, phi = -1, tlo = INT64_MAX, thi = -1;
                 for (int64_t i = 64 * w; i < 64 * w + 64; ++i) {
                     const int64_t t = target(q, i);
                     if (t < n) { plo = std::min(plo, t); phi = std::max(phi, t); }
                     else { tlo = std::min(tlo, t); thi = std::max(thi, t); }
                 }
-                if ((phi >= 0 && phi - plo > 0xffff) || (thi >= 0 && thi - tlo > 0xffff))
-                    fits = false;
+                if (phi >= 0) spread = std::max(spread, phi - plo);
+                if (thi >= 0) spread = std::max(spread, thi - tlo);
                 rec[q - 1] = phi >= 0 ? (int32_t)plo : 0;
                 rec[18 + q - 1] = thi >= 0 ? (int32_t)tlo : (int32_t)n;
             }
-            is_ex[(size_t)w] = fits ? 0 : 1;
+            is_ex[(size_t)w] = spread > 0xffff ? 1 : 0;
+            rec[kCompactKind] = spread <= 0xff ? 1 : 0;
         }
     }, nw * 64 * 18);
     c.n_ex = 0;
@@ -412,13 +414,24 @@ std::string build_compact_lookup(Prepass& pre) {
                     if (tail) mask |= 1u << q;
                     code[q] = (uint16_t)(t - (tail ? rec[18 + q - 1] : rec[q - 1]));
                 }
-                c.ax[(size_t)i * 4 + 0] = mask;
-                for (int k = 0; k < 3; ++k)
-                    c.ax[(size_t)i * 4 + 1 + k] = code[1 + 2 * k] | (uint32_t)code[2 + 2 * k] << 16;
-                for (int k = 0; k < 4; ++k)
-                    c.dg4[(size_t)i * 4 + k] = code[7 + 2 * k] | (uint32_t)code[8 + 2 * k] << 16;
-                for (int k = 0; k < 2; ++k)
-                    c.dg2[(size_t)i * 2 + k] = code[15 + 2 * k] | (uint32_t)code[16 + 2 * k] << 16;
+                if (row >= 0) continue;
+                uint32_t* n8 = &c.n8[(size_t)i * 2];
+                uint32_t* n16 = &c.n16[(size_t)i * 4];
+                uint32_t* wide = &c.wide[(size_t)i * 4];
+                if (rec[kCompactKind]) {
+                    for (int q = 1; q < 7; ++q)
+                        n8[(q - 1) / 4] |= (uint32_t)code[q] << (8 * ((q - 1) % 4));
+                    n8[1] |= ((mask >> 1) & 0x3fu) << 16;
+                    for (int q = 7; q < 19; ++q)
+                        n16[(q - 7) / 4] |= (uint32_t)code[q] << (8 * ((q - 7) % 4));
+                    n16[3] = mask >> 7;
+                } else {
+                    auto pair = [&](int q) { return code[q] | (uint32_t)code[q + 1] << 16; };
+                    wide[0] = mask;
+                    for (int k = 0; k < 3; ++k) wide[1 + k] = pair(1 + 2 * k);
+                    for (int k = 0; k < 4; ++k) n16[k] = pair(7 + 2 * k);
+                    for (int k = 0; k < 2; ++k) n8[k] = pair(15 + 2 * k);
+                }
             }
         }
     }, ld * 18);
@@ -434,12 +447,22 @@ std::string build_compact_lookup(Prepass& pre) {
                         got = c.ex[((size_t)rec[kCompactExRow] * 18 + (q - 1)) * 64 +
                                    (size_t)(i & 63)];
                     } else {
-                        uint32_t word;
-                        if (q <= 6) word = c.ax[(size_t)i * 4 + 1 + (q - 1) / 2];
-                        else if (q <= 14) word = c.dg4[(size_t)i * 4 + (q - 7) / 2];
-                        else word = c.dg2[(size_t)i * 2 + (q - 15) / 2];
-                        const uint32_t code = (q & 1) ? (word & 0xffffu) : (word >> 16);
-                        const bool tail = (c.ax[(size_t)i * 4] >> q) & 1u;
+                        const uint32_t* n8 = &c.n8[(size_t)i * 2];
+                        const uint32_t* n16 = &c.n16[(size_t)i * 4];
+                        const uint32_t* wide = &c.wide[(size_t)i * 4];
+                        uint32_t code;
+                        bool tail;
+                        if (rec[kCompactKind]) {
+                            const uint32_t word = q < 7 ? n8[(q - 1) / 4] : n16[(q - 7) / 4];
+                            code = (word >> (8 * ((q < 7 ? q - 1 : q - 7) % 4))) & 0xffu;
+                            tail = (q < 7 ? n8[1] >> (16 + q - 1) : n16[3] >> (q - 7)) & 1u;
+                        } else {
+                            const uint32_t word = q < 7    ? wide[1 + (q - 1) / 2]
+                                                  : q < 15 ? n16[(q - 7) / 2]
+                                                           : n8[(q - 15) / 2];
+                            code = (q & 1) ? (word & 0xffffu) : (word >> 16);
+                            tail = (wide[0] >> q) & 1u;
+                        }
                         got = (int64_t)(tail ? rec[18 + q - 1] : rec[q - 1]) + code;
                     }
                     if (got != target(q, i)) {

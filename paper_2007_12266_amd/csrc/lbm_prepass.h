@@ -29,19 +29,31 @@ constexpr int kCoordXBits = 10, kCoordYBits = 11, kCoordZBits = 11;
 
 // Compact neighbour lookup. The pore list is cut into waves of 64 consecutive voxels. For each
 // wave and direction q the targets of its voxels (pore index, or N + tail index) lie close
-// together, so each is stored as a 16-bit code above one of two per-wave bases, the pore base or
-// the tail base; bit q of the voxel's mask says which. Per voxel: an axis record of 16 bytes
-// (mask, codes of q = 1..6, all the densities need) and diagonal records of 16 + 8 bytes (codes
-// of q = 7..14 and 15..18). Per wave: kCompactWaveInts ints: pore bases of q = 1..18, tail bases
-// of q = 1..18, then the wave's exception row or -1. A wave whose targets spread beyond 16 bits
-// (where the pore list jumps between blocks of rows) keeps its 18 x 64 targets as int32 in
-// exception row r: cex[(r * 18 + q - 1) * 64 + lane].
+// together, so each is stored as a code above one of two per-wave bases, the pore base or the
+// tail base; a mask bit of the voxel says which. 40 bytes per voxel are kept, in records of
+// 8 + 16 + 16 bytes; how much of them a kernel reads is the wave's:
+//  * byte waves (kCompactKind of the wave record is 1): every code fits 8 bits. n8 holds the
+//    codes of q = 1..6 and their mask bits, all the densities need (8 bytes read), n16 the codes
+//    and mask bits of q = 7..18 (24 bytes read in all). About 80% of the waves of the rocks in
+//    use (64^3 to 512^3, porosity 0.2 to 0.25).
+//  * 16-bit waves (kind 0): wide holds the mask and the codes of q = 1..6 (16 bytes read by the
+//    densities), n16 the codes of q = 7..14 and n8 those of q = 15..18 (40 in all).
+//  * exception waves, whose targets spread beyond 16 bits (where the pore list jumps between
+//    blocks of rows; 15-20% of the waves of those rocks): their 18 x 64 targets as int32 in
+//    exception row r, ex[(r * 18 + q - 1) * 64 + lane].
+// Per wave: kCompactWaveInts ints: pore bases of q = 1..18, tail bases of q = 1..18, the wave's
+// exception row or -1, and its kind.
 constexpr int kCompactWaveInts = 40;
 constexpr int kCompactExRow = 36;
+constexpr int kCompactKind = 37;
 struct CompactNbr {
-    std::vector<uint32_t> ax;     // [ld][4]: mask (bit q = tail target), codes 1|2, 3|4, 5|6
-    std::vector<uint32_t> dg4;    // [ld][4]: codes 7|8, 9|10, 11|12, 13|14
-    std::vector<uint32_t> dg2;    // [ld][2]: codes 15|16, 17|18
+    // Byte waves: n8 = codes 1..4 | codes 5, 6 and mask bits 1..6 from bit 16;
+    //   n16 = codes 7..10 | 11..14 | 15..18 | mask bits 7..18 from bit 0.
+    // 16-bit waves: wide = mask (bit q) | codes 1, 2 | 3, 4 | 5, 6; n16 = codes 7, 8 | ... |
+    //   13, 14; n8 = codes 15, 16 | 17, 18. A mask bit set is a tail target.
+    std::vector<uint32_t> n8;     // [ld][2]
+    std::vector<uint32_t> n16;    // [ld][4]
+    std::vector<uint32_t> wide;   // [ld][4]
     std::vector<int32_t> wave;    // [ld / 64][kCompactWaveInts]
     std::vector<int32_t> ex;      // [exception waves][18][64]
     int64_t n_ex = 0;             // exception waves

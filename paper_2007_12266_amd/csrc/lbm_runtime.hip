@@ -263,8 +263,8 @@ static bool uses_compact(const lbm_params& p) {
 static int64_t compact_bytes(const Prepass& pre) {
     auto r = [](size_t b) { return (int64_t)std::max<size_t>(b, 256); };
     const CompactNbr& c = pre.compact;
-    return r(sizeof(uint32_t) * c.ax.size()) + r(sizeof(uint32_t) * c.dg4.size()) +
-           r(sizeof(uint32_t) * c.dg2.size()) + r(sizeof(int32_t) * c.wave.size()) +
+    return r(sizeof(uint32_t) * c.n8.size()) + r(sizeof(uint32_t) * c.n16.size()) +
+           r(sizeof(uint32_t) * c.wide.size()) + r(sizeof(int32_t) * c.wave.size()) +
            r(sizeof(int32_t) * c.ex.size());
 }
 
@@ -398,9 +398,9 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
         d->coord = (uint32_t*)d->dalloc(sizeof(uint32_t) * ld);
         d->words = (RowWord*)d->dalloc(sizeof(RowWord) * pre.words.size());
     } else if (d->compact) {
-        d->cax = (uint4*)d->dalloc(sizeof(uint32_t) * cn.ax.size());
-        d->cdg4 = (uint4*)d->dalloc(sizeof(uint32_t) * cn.dg4.size());
-        d->cdg2 = (uint2*)d->dalloc(sizeof(uint32_t) * cn.dg2.size());
+        d->cn8 = (uint2*)d->dalloc(sizeof(uint32_t) * cn.n8.size());
+        d->cn16 = (uint4*)d->dalloc(sizeof(uint32_t) * cn.n16.size());
+        d->cwide = (uint4*)d->dalloc(sizeof(uint32_t) * cn.wide.size());
         d->cwave = (int32_t*)d->dalloc(sizeof(int32_t) * cn.wave.size());
         d->cex = (int32_t*)d->dalloc(sizeof(int32_t) * cn.ex.size());
     } else {
@@ -412,7 +412,7 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
     double* phi0 = d->stage;
     if (!d->f || !d->M || !d->fresh || !d->phi || !d->ntot || !d->stage ||
         (d->rank ? (!d->coord || !d->words)
-                 : d->compact ? (!d->cax || !d->cdg4 || !d->cdg2 || !d->cwave || !d->cex)
+                 : d->compact ? (!d->cn8 || !d->cn16 || !d->cwide || !d->cwave || !d->cex)
                               : !d->nbr) ||
         !d->red_partials || !d->red_out || !d->hist) {
         d->release();
@@ -454,9 +454,9 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
         guard(up(d->coord, pre.coord.data(), sizeof(uint32_t) * pre.coord.size()), "upload coord");
         guard(up(d->words, pre.words.data(), sizeof(RowWord) * pre.words.size()), "upload words");
     } else if (d->compact) {
-        guard(up(d->cax, cn.ax.data(), sizeof(uint32_t) * cn.ax.size()), "upload compact");
-        guard(up(d->cdg4, cn.dg4.data(), sizeof(uint32_t) * cn.dg4.size()), "upload compact");
-        guard(up(d->cdg2, cn.dg2.data(), sizeof(uint32_t) * cn.dg2.size()), "upload compact");
+        guard(up(d->cn8, cn.n8.data(), sizeof(uint32_t) * cn.n8.size()), "upload compact");
+        guard(up(d->cn16, cn.n16.data(), sizeof(uint32_t) * cn.n16.size()), "upload compact");
+        guard(up(d->cwide, cn.wide.data(), sizeof(uint32_t) * cn.wide.size()), "upload compact");
         guard(up(d->cwave, cn.wave.data(), sizeof(int32_t) * cn.wave.size()), "upload compact");
         if (!cn.ex.empty())
             guard(up(d->cex, cn.ex.data(), sizeof(int32_t) * cn.ex.size()), "upload compact");
