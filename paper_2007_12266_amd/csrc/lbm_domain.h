@@ -25,8 +25,10 @@ void finish_reduction(const lbm_domain* d, const double* acc, int64_t step, lbm_
 // A member's launch arguments changed: the pool re-uploads them before its next step.
 lbm_status pool_member_changed(lbm_pool* p, const lbm_domain* d);
 // The launches of one time step of d alone at parity `odd` on d->stream, with d's own launch
-// configuration (lbm_runtime.hip).
-lbm_status launch_domain_step(lbm_domain* d, bool odd);
+// configuration; `settle` as for launch_faces (lbm_runtime.hip).
+lbm_status launch_domain_step(lbm_domain* d, bool odd, bool settle);
+// The face launches after a step's collide kernel, on stream s (lbm_runtime.hip).
+lbm_status launch_faces(lbm_domain* d, const StepArgs& a, bool odd, bool settle, hipStream_t s);
 }  // namespace lbm
 
 #define HIP_TRY(expr)                                                                        \
@@ -53,7 +55,7 @@ struct lbm_domain {
 
     void* f = nullptr;
     void* M = nullptr;        // [4][ld][2] D3Q7 moment slot pairs
-    int32_t* fresh = nullptr; // device flag: the state is the initial one
+    int32_t* fresh = nullptr; // device flags: the state is the initial one (StepArgs)
     int8_t* face = nullptr;   // [N] pressure-face flags (bc_z == 1 only)
     int32_t one = 1;          // host source of fresh-flag uploads (outlives the async copy)
     void* phi = nullptr;      // [N + n_tail] storage type
@@ -79,8 +81,6 @@ struct lbm_domain {
     std::vector<int64_t> hist_step;
     int32_t* faces = nullptr;       // inlet then outlet pore indices (bc_z == 1)
     double* inlet_rho = nullptr;    // device scalar: this step's inlet density (flux inlet)
-    int32_t* ghost_tail = nullptr;  // z-face mirror entries of the phi tail
-    int32_t* ghost_src = nullptr;
 
     // Work buffers of the morphological growth step, allocated on its first use.
     uint8_t* morph_label = nullptr;  // [nx*ny*nz] 1 where a pore voxel has phi > 0
@@ -110,6 +110,10 @@ struct lbm_domain {
         step_graph = nullptr;
     }
 
+    // The pressure condition is a kernel of its own after every step: a flux inlet, whose density
+    // is known only then, and a single plane, which is both faces.
+    bool faces_each_step() const { return inlet_rho || p.nz == 1; }
+
     // Kernel arguments for a launch with `blk` threads per workgroup and schedule `sched`
     // (XCD runs of `run` tiles for schedules 2 and 3).
     lbm::StepArgs args(int blk = 256, int sched = 1, int run = lbm::kXcdRun) const {
@@ -129,6 +133,9 @@ struct lbm_domain {
         a.alpha = p.alpha;
         a.beta = p.beta;
         for (int c = 0; c < 3; ++c) a.F[c] = p.force[c];
+        a.rho_face[0] = p.rho_in;
+        a.rho_face[1] = p.rho_out;
+        a.face_bc = p.bc_z == 1 && !faces_each_step() ? 1 : 0;
         const int64_t tiles = (pre.n_pore + blk - 1) / blk;
         const int64_t whole = 8 * (int64_t)run;   // whole runs on every XCD
         a.grid = (int32_t)(sched >= 2 ? (tiles + whole - 1) / whole * whole : tiles);

@@ -33,11 +33,14 @@ struct StepArgs {
     void* f;            // [19][ld] populations (storage type per precision)
     void* M;            // [4][ld][2] D3Q7 moment slot pairs: (N_a, N_b), (u_x, G_x), (u_y, G_y),
                         // (u_z, G_z)
-    int32_t* fresh;     // device flag: 1 while the state is the initial one
+    int32_t* fresh;     // device flags: [0] 1 while the state is the initial one; [1] its value at
+                        // the step's phase kernel, for the collide kernel that clears [0]
     const int8_t* face; // per pore voxel: 0, 1 (inlet face), 2 (outlet face); null without faces
     double nu_a, nu_b;  // kinematic viscosities
     double alpha, beta;
     double F[3];
+    double rho_face[2]; // imposed densities of the inlet and the outlet face
+    int32_t face_bc;    // 1: the collide kernel applies the pressure condition (fixed densities)
     int32_t grid;       // workgroups of a step kernel's launch
     int32_t xcd_run;    // tiles per run of the XCD-aware order (1: launch order)
     uint32_t xcd_mul;   // xcd_mul_of(xcd_run)
@@ -105,8 +108,6 @@ hipError_t launch_collide(const StepArgs& a, bool odd, int block, bool stream, u
 // Dynamic LDS that bounds a step kernel (0: phase, 1: collide) to `wg` workgroups per CU.
 hipError_t step_kernel_lds(const StepArgs& a, int kernel, int block, bool stream, int wg,
                            unsigned* lds);
-hipError_t launch_ghosts(const StepArgs& a, const int32_t* ghost_tail, const int32_t* ghost_src,
-                         int32_t n, hipStream_t s);
 // faces: inlet pore indices (n_in) followed by outlet ones (n_out); next_odd: parity of the
 // step that will read the state the condition is applied to.
 // rho_in_dev (nullable): device scalar that replaces rho_in (flux inlet).
@@ -123,10 +124,11 @@ hipError_t launch_reduce(const StepArgs& a, bool odd, double* partials, double* 
                          hipStream_t s);
 // lookup: LBM_NBR_TABLE or LBM_NBR_RANK when every member uses that neighbour lookup, else
 // LBM_NBR_AUTO (each tile tests its domain's lookup at run time).
-hipError_t launch_phase_batched(const BatchArgs& b, int prec, bool odd, int lookup, int grid,
+// face: whether any member has pressure faces.
+hipError_t launch_phase_batched(const BatchArgs& b, int prec, int lookup, bool face, int grid,
                                 int block, hipStream_t s);
-hipError_t launch_collide_batched(const BatchArgs& b, int prec, bool odd, int lookup, int grid,
-                                  int block, hipStream_t s);
+hipError_t launch_collide_batched(const BatchArgs& b, int prec, bool odd, int lookup, bool face,
+                                  int grid, int block, hipStream_t s);
 // Reductions of slots 0..nslots-1 into out[nslots][kNRed]; partials holds nslots*kRedBlocks rows.
 hipError_t launch_reduce_batched(const BatchArgs& b, int prec, bool odd, int nslots,
                                  double* partials, double* out, hipStream_t s);

@@ -268,6 +268,18 @@ __device__ __forceinline__ void compact_all(const StepArgs& a, int i, int (&cn)[
     }
 }
 
+// Pressure face of pore voxel i: 0, 1 (inlet) or 2 (outlet). With the compact lookup a mark in the
+// wave's record says whether the wave holds any, so the others read no flags.
+template <int NB>
+__device__ __forceinline__ int face_of(const StepArgs& a, int i) {
+    if (!a.face) return 0;
+    if (NB == NB_COMPACT) {
+        const int w = __builtin_amdgcn_readfirstlane(i >> 6);
+        if (!(as_const(a.cwave) + (size_t)w * kCompactWaveInts)[kCompactFace]) return 0;
+    }
+    return a.face[i];
+}
+
 // Per-voxel lookup state of pore voxel i (see Pos).
 template <int NB = NB_DYN, bool WAVE = false, bool STREAM = false>
 __device__ __forceinline__ Pos pos_of(const StepArgs& a, int i) {
@@ -430,9 +442,12 @@ __device__ __forceinline__ void out_ab(const S* __restrict__ M, int64_t ld, int 
 // upstream neighbour selects the voxel's own slots and flips the sign), so the loads of one
 // voxel are in flight together.
 // Callers keep each wave on 64 consecutive pore voxels (see compact_all).
-template <int PREC, int NB = NB_DYN, bool STREAM = false>
+// `ghost`: for a voxel of a pressure face the tail entry that mirrors its phi across the face (the
+// target beyond the face), else -1; the rank lookup has no such entries.
+// FACE: the domain may have pressure faces.
+template <int PREC, int NB = NB_DYN, bool STREAM = false, bool FACE = true>
 __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, double& na,
-                                          double& nbv) {
+                                          double& nbv, int& ghost) {
     using P = Prec<PREC>;
     using S = typename P::S;
     using R = typename P::R;
@@ -443,7 +458,8 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, 
     int up[7];
 #pragma unroll
     for (int q = 1; q < 7; ++q) up[q] = nb_stream<NB, STREAM>(a, OPP[q], i, pos);  // i - xi_q
-    const int fc = a.face ? a.face[i] : 0;
+    const int fc = FACE ? face_of<NB>(a, i) : 0;
+    ghost = fc && !use_rank<NB>(a) ? (fc == 1 ? up[5] : up[6]) : -1;   // along -z, along +z
     R sna[7], snb[7], suc[7], sgc[7];
 #pragma unroll
     for (int q = 1; q < 7; ++q) {
@@ -520,27 +536,72 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, 
 // Densities and phase indicator: N_a = sum_q A_q, N_b = sum_q B_q (q = 0..6) of the streamed-in
 // D3Q7 populations; phi = (N_a - N_b)/(N_a + N_b); N = N_a + N_b.
 // ------------------------------------------------------------------------------------------
-template <int PREC, int NB = NB_DYN, bool STREAM = false>
+template <int PREC, int NB, bool STREAM, bool FACE>
 __device__ __forceinline__ void phase_voxel(const StepArgs& a, int i, bool fresh) {
     using S = typename Prec<PREC>::S;
     double na, nbv;
-    densities<PREC, NB, STREAM>(a, i, fresh, na, nbv);
+    int ghost;
+    densities<PREC, NB, STREAM, FACE>(a, i, fresh, na, nbv, ghost);
     const double nt = na + nbv;
-    store_once<STREAM>((S)((na - nbv) / nt), (S*)a.phi + i);
+    const S phi = (S)((na - nbv) / nt);
+    store_once<STREAM>(phi, (S*)a.phi + i);
     store_once<STREAM>((S)nt, (S*)a.ntot + i);
+    if (FACE) {
+        if (ghost >= 0) ((S*)a.phi)[ghost] = phi;
+        if (i == 0) a.fresh[1] = fresh ? 1 : 0;
+    }
 }
 
-template <int PREC, int NB, bool STREAM>
+template <int PREC, int NB, bool STREAM, bool FACE>
 __global__ void __launch_bounds__(256) phase_kernel(StepArgs a) {
     load_args<NB>(a);
     const int i = tile_start(a) + (int)threadIdx.x;
-    if (i < a.N) phase_voxel<PREC, NB, STREAM>(a, i, *a.fresh != 0);
+    if (i < a.N) phase_voxel<PREC, NB, STREAM, FACE>(a, i, *a.fresh != 0);
 }
 
 // ------------------------------------------------------------------------------------------
 // Fused colour gradient + MRT collision with interfacial terms and body force + recolouring +
 // AA streaming.
 // ------------------------------------------------------------------------------------------
+// Zou-He pressure condition of density rho on the streamed populations of a voxel of the inlet
+// (fc = 1, z = 0) or the outlet (2, z = nz - 1): the unknowns, whose xi_z points into the domain,
+// follow from the others, so applying the condition again gives the same values. The composition
+// of the face planes (pure a, N = 1, at the inlet; pure b at the outlet) is imposed where
+// densities are formed (the face flag), which equals resetting their D3Q7 populations to
+// equilibrium.
+template <int PREC>
+__device__ __forceinline__ void pressure_face(typename Prec<PREC>::F (&f)[19], int fc, double rho) {
+#pragma clang fp contract(off)
+    using P = Prec<PREC>;
+    using F = typename P::F;
+    const int dir = fc == 1 ? 1 : -1;
+    double fl[19];
+#pragma unroll
+    for (int q = 0; q < 19; ++q) fl[q] = (double)f[q] + (P::kDev ? tw(q) : 0.0);
+    double s0 = 0.0, up = 0.0, down = 0.0, tx = 0.0, ty = 0.0;
+#pragma unroll
+    for (int q = 0; q < 19; ++q) {
+        if (CZ[q] == 0) {
+            s0 += fl[q];
+            if (CX[q]) tx += CX[q] * fl[q];
+            if (CY[q]) ty += CY[q] * fl[q];
+        } else if (CZ[q] > 0) {
+            up += fl[q];
+        } else {
+            down += fl[q];
+        }
+    }
+    const double jz = dir * (rho - s0 - 2.0 * (dir > 0 ? down : up));
+#pragma unroll
+    for (int q = 1; q < 19; ++q) {
+        if (CZ[q] == 0) continue;
+        double val = fused(6.0 * tw(q) * CZ[q], jz, fl[OPP[q]]);
+        if (CX[q]) val -= 0.5 * (CX[q] * tx);
+        if (CY[q]) val -= 0.5 * (CY[q] * ty);
+        if (CZ[q] == dir) f[q] = (F)(val - (P::kDev ? tw(q) : 0.0));
+    }
+}
+
 // EARLY: every load of a voxel is issued before the first value is used: the even step's own
 // populations first, as they need no index, then (indices known) the neighbours' phi and the odd
 // step's populations. The scheduler otherwise issues the populations after the gradient has
@@ -548,7 +609,7 @@ __global__ void __launch_bounds__(256) phase_kernel(StepArgs a) {
 // CU to hide it (32^3 bead pack in FP64, with load_args: 8.7 -> 8.1 us a step; 64^3 in
 // FP32-mixed 9.2 -> 8.5), nothing in a pool, and a loss where the waves in flight compete for the
 // L2 (256^3 FP64 -0.7%, 320^3 FP32-mixed -0.9%): on for domains up to kEarlyVoxels.
-template <int PREC, bool ODD, int NB, bool STREAM, bool EARLY>
+template <int PREC, bool ODD, int NB, bool STREAM, bool EARLY, bool FACE>
 __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
 #pragma clang fp contract(off)
     using P = Prec<PREC>;
@@ -597,6 +658,7 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
             fraw[q] = load_in<ODD, F, STREAM>(f, a, q, i, RS(OPP[q]));
     }
     if (EARLY) __builtin_amdgcn_sched_barrier(0);
+    const int fc = FACE && a.face_bc ? face_of<NB>(a, i) : 0;
     R p[19];
 #pragma unroll
     for (int q = 1; q < 19; ++q) p[q] = (R)praw[q];
@@ -624,6 +686,7 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
         phi_own = ph[i];
         n_own = ((const S*)a.ntot)[i];
     }
+    if (FACE && fc && !a.fresh[1]) pressure_face<PREC>(fraw, fc, a.rho_face[fc - 1]);
     R fl[19];
 #pragma unroll
     for (int q = 0; q < 19; ++q) fl[q] = (R)fraw[q];
@@ -712,11 +775,11 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
     if (i == 0) *a.fresh = 0;        // the state now holds outgoing moments
 }
 
-template <int PREC, bool ODD, int NB, bool STREAM, bool EARLY>
+template <int PREC, bool ODD, int NB, bool STREAM, bool EARLY, bool FACE>
 __global__ void __launch_bounds__(256) collide_kernel(StepArgs a) {
     load_args<NB>(a);
     const int i = tile_start(a) + (int)threadIdx.x;
-    if (i < a.N) collide_voxel<PREC, ODD, NB, STREAM, EARLY>(a, i);
+    if (i < a.N) collide_voxel<PREC, ODD, NB, STREAM, EARLY, FACE>(a, i);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -744,7 +807,7 @@ __device__ __forceinline__ T load_const(const T* p) {
     return out;
 }
 
-template <int PREC, int NB>
+template <int PREC, int NB, bool FACE>
 __global__ void __launch_bounds__(256) phase_batched(BatchArgs b) {
     const int nt = *as_const(b.ntiles);
     const int first = b.xcd ? xcd_run_tile((int)blockIdx.x, kXcdRun, xcd_mul_of(kXcdRun))
@@ -753,11 +816,11 @@ __global__ void __launch_bounds__(256) phase_batched(BatchArgs b) {
         const int d = as_const(b.tile_dom)[t];
         const StepArgs a = load_const(b.doms + d);
         const int i = (t - as_const(b.tile_first)[d]) * blockDim.x + threadIdx.x;
-        if (i < a.N) phase_voxel<PREC, NB>(a, i, *a.fresh != 0);
+        if (i < a.N) phase_voxel<PREC, NB, false, FACE>(a, i, *a.fresh != 0);
     }
 }
 
-template <int PREC, bool ODD, int NB>
+template <int PREC, bool ODD, int NB, bool FACE>
 __global__ void __launch_bounds__(256) collide_batched(BatchArgs b) {
     const int nt = *as_const(b.ntiles);
     const int first = b.xcd ? xcd_run_tile((int)blockIdx.x, kXcdRun, xcd_mul_of(kXcdRun))
@@ -766,7 +829,7 @@ __global__ void __launch_bounds__(256) collide_batched(BatchArgs b) {
         const int d = as_const(b.tile_dom)[t];
         const StepArgs a = load_const(b.doms + d);
         const int i = (t - as_const(b.tile_first)[d]) * blockDim.x + threadIdx.x;
-        if (i < a.N) collide_voxel<PREC, ODD, NB, false, false>(a, i);
+        if (i < a.N) collide_voxel<PREC, ODD, NB, false, false, FACE>(a, i);
     }
 }
 
@@ -784,7 +847,8 @@ __device__ __forceinline__ void voxel_state(const StepArgs& a, int i, double& na
     const Pos pos = pos_of(a, i);
 #pragma unroll
     for (int q = 1; q < 19; ++q) r[q] = ODD ? nb_stream(a, q, i, pos) : 0;
-    densities<PREC>(a, i, *a.fresh != 0, na, nbv);   // field and reduction kernels: waves aligned
+    int ghost;
+    densities<PREC>(a, i, *a.fresh != 0, na, nbv, ghost);   // callers' waves are aligned
     rho = 0.0;
     jx = jy = jz = 0.0;
 #pragma unroll
@@ -935,25 +999,15 @@ __global__ void __launch_bounds__(256) field_kernel(StepArgs a, int field,
 }
 
 // ------------------------------------------------------------------------------------------
-// Pressure faces. Across the z faces the colour gradient mirrors the plane: tail entries that
-// stand for an out-of-domain z neighbour carry the phi of the in-plane voxel, refreshed after
-// every phase kernel.
+// Pressure faces. Across the z faces the colour gradient mirrors the plane: the tail entry that
+// stands for an out-of-domain z neighbour carries the phi of the in-plane voxel, written by the
+// phase kernel beside that voxel's own. The collide kernel applies the pressure condition to the
+// populations of a face voxel as it reads them; pressure_bc_kernel applies it to the stored state
+// where a stretch of steps ends, and after every step of a flux inlet, whose density is known
+// only then. (With a kernel of their own each, ghosts and faces took 10 of 128^3's 55 us a step.)
+// The kernel reads and writes in the layout of the next step (parity ODD); the unknowns always
+// sit in the voxel's own slot q, because their upstream neighbour is outside.
 // ------------------------------------------------------------------------------------------
-template <typename S>
-__global__ void __launch_bounds__(256) ghost_kernel(StepArgs a, const int32_t* __restrict__ tail,
-                                                    const int32_t* __restrict__ src, int n) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    S* ph = (S*)a.phi;
-    ph[a.N + tail[k]] = ph[src[k]];
-}
-
-// Zou-He pressure condition on the streamed populations of the z = 0 (inlet, first n_in
-// entries of `faces`) and z = nz-1 (outlet) pore voxels, read and written in the layout of the
-// next step (parity ODD). Unknowns (xi_z pointing into the domain) always sit in the voxel's
-// own slot q, because their upstream neighbour is outside. The composition of the face planes
-// (pure a, N = 1, at the inlet; pure b at the outlet) is imposed where densities are formed
-// (the per-voxel face flag), which equals resetting their D3Q7 populations to equilibrium.
 template <int PREC, bool ODD>
 __global__ void __launch_bounds__(256) pressure_bc_kernel(StepArgs a,
                                                           const int32_t* __restrict__ faces,
@@ -965,36 +1019,20 @@ __global__ void __launch_bounds__(256) pressure_bc_kernel(StepArgs a,
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n_in + n_out) return;
     const int i = faces[k];
-    const int dir = k < n_in ? 1 : -1;
-    const double rho_b = k < n_in ? (rho_in_dev ? *rho_in_dev : rho_in) : rho_out;
+    const int fc = k < n_in ? 1 : 2;
     F* f = (F*)a.f;
     int r[19];
     r[0] = i;
     const Pos pos = pos_of(a, i);
 #pragma unroll
     for (int q = 1; q < 19; ++q) r[q] = nb_stream(a, q, i, pos);
-    double fl[19];
+    F fl[19];
 #pragma unroll
-    for (int q = 0; q < 19; ++q)
-        fl[q] = (double)load_in<ODD>(f, a, q, i, r[OPP[q]]) + (P::kDev ? tw(q) : 0.0);
-    double s0 = 0.0, sout = 0.0, tx = 0.0, ty = 0.0;
+    for (int q = 0; q < 19; ++q) fl[q] = load_in<ODD>(f, a, q, i, r[OPP[q]]);
+    pressure_face<PREC>(fl, fc, fc == 1 ? (rho_in_dev ? *rho_in_dev : rho_in) : rho_out);
 #pragma unroll
-    for (int q = 0; q < 19; ++q) {
-        if (CZ[q] == 0) {
-            s0 += fl[q];
-            tx += CX[q] * fl[q];
-            ty += CY[q] * fl[q];
-        } else if (CZ[q] == -dir) {
-            sout += fl[q];
-        }
-    }
-    const double jz = dir * (rho_b - s0 - 2.0 * sout);
-#pragma unroll
-    for (int q = 0; q < 19; ++q) {
-        if (CZ[q] != dir) continue;
-        const double val = fl[OPP[q]] + 6.0 * tw(q) * CZ[q] * jz - 0.5 * (CX[q] * tx + CY[q] * ty);
-        f[(size_t)q * a.ld + i] = (F)(val - (P::kDev ? tw(q) : 0.0));
-    }
+    for (int q = 1; q < 19; ++q)
+        if (CZ[q] == (fc == 1 ? 1 : -1)) f[(size_t)q * a.ld + i] = fl[q];
 }
 
 // Flux inlet: sum over the inlet voxels of s0 + 2 sout (the known part of each voxel's
@@ -1071,10 +1109,14 @@ int grid_for(const StepArgs& a, int block) { return (a.N + block - 1) / block; }
 
 #define LBM_LAUNCH_ODD_NB(KERNEL, P, NBV, GRID, BLOCK, ...)                                    \
     do {                                                                                       \
-        if (odd)                                                                               \
-            hipLaunchKernelGGL((KERNEL<P, true, NBV>), GRID, BLOCK, 0, s, __VA_ARGS__);        \
+        if (odd && face)                                                                       \
+            hipLaunchKernelGGL((KERNEL<P, true, NBV, true>), GRID, BLOCK, 0, s, __VA_ARGS__);  \
+        else if (odd)                                                                          \
+            hipLaunchKernelGGL((KERNEL<P, true, NBV, false>), GRID, BLOCK, 0, s, __VA_ARGS__); \
+        else if (face)                                                                         \
+            hipLaunchKernelGGL((KERNEL<P, false, NBV, true>), GRID, BLOCK, 0, s, __VA_ARGS__); \
         else                                                                                   \
-            hipLaunchKernelGGL((KERNEL<P, false, NBV>), GRID, BLOCK, 0, s, __VA_ARGS__);       \
+            hipLaunchKernelGGL((KERNEL<P, false, NBV, false>), GRID, BLOCK, 0, s, __VA_ARGS__); \
     } while (0)
 
 #define LBM_PREC_SWITCH(PREC, LAUNCH, KERNEL, ...)                                             \
@@ -1105,16 +1147,24 @@ hipError_t launch_init(const StepArgs& a, const double* phi0, int block, hipStre
 }
 
 // The step kernel (0: phase, 1: collide) of a domain, by precision, parity, neighbour lookup,
-// streaming accesses and load order. The phase kernel is the same at both parities.
+// streaming accesses, load order and pressure faces (whose code costs the collide kernel 20 to 40
+// registers). The phase kernel is the same at both parities.
 using StepKernel = void (*)(StepArgs);
+
+template <int P, int NB, bool ST, bool FACE>
+static StepKernel step_kernel_fn(const StepArgs& a, int kernel, bool odd) {
+    if (kernel == 0) return phase_kernel<P, NB, ST, FACE>;
+    if (!ST && a.N <= kEarlyVoxels)
+        return odd ? collide_kernel<P, true, NB, false, true, FACE>
+                   : collide_kernel<P, false, NB, false, true, FACE>;
+    return odd ? collide_kernel<P, true, NB, ST, false, FACE>
+               : collide_kernel<P, false, NB, ST, false, FACE>;
+}
 
 template <int P, int NB, bool ST>
 static StepKernel step_kernel_fn(const StepArgs& a, int kernel, bool odd) {
-    if (kernel == 0) return phase_kernel<P, NB, ST>;
-    if (!ST && a.N <= kEarlyVoxels)
-        return odd ? collide_kernel<P, true, NB, false, true>
-                   : collide_kernel<P, false, NB, false, true>;
-    return odd ? collide_kernel<P, true, NB, ST, false> : collide_kernel<P, false, NB, ST, false>;
+    return a.face ? step_kernel_fn<P, NB, ST, true>(a, kernel, odd)
+                  : step_kernel_fn<P, NB, ST, false>(a, kernel, odd);
 }
 
 template <int P, bool ST>
@@ -1207,7 +1257,12 @@ hipError_t launch_reduce(const StepArgs& a, bool odd, double* partials, double* 
     LBM_PREC_SWITCH(prec, LBM_LAUNCH_ODD, KERNEL, GRID, BLOCK, __VA_ARGS__)
 
 #define LBM_LAUNCH_NB(KERNEL, P, NBV, GRID, BLOCK, ...)                                        \
-    hipLaunchKernelGGL((KERNEL<P, NBV>), GRID, BLOCK, 0, s, __VA_ARGS__)
+    do {                                                                                       \
+        if (face)                                                                              \
+            hipLaunchKernelGGL((KERNEL<P, NBV, true>), GRID, BLOCK, 0, s, __VA_ARGS__);        \
+        else                                                                                   \
+            hipLaunchKernelGGL((KERNEL<P, NBV, false>), GRID, BLOCK, 0, s, __VA_ARGS__);       \
+    } while (0)
 
 #define LBM_DISPATCH_B_NB(LAUNCH, KERNEL, GRID, BLOCK, ...)                                            \
     do {                                                                                       \
@@ -1222,15 +1277,14 @@ hipError_t launch_reduce(const StepArgs& a, bool odd, double* partials, double* 
             LBM_PREC_SWITCH(prec, LAUNCH, KERNEL, NB_DYN, GRID, BLOCK, __VA_ARGS__); \
     } while (0)
 
-hipError_t launch_phase_batched(const BatchArgs& b, int prec, bool odd, int lookup, int grid,
+hipError_t launch_phase_batched(const BatchArgs& b, int prec, int lookup, bool face, int grid,
                                 int block, hipStream_t s) {
-    (void)odd;
     LBM_DISPATCH_B_NB(LBM_LAUNCH_NB, phase_batched, dim3(grid), dim3(block), b);
     return hipGetLastError();
 }
 
-hipError_t launch_collide_batched(const BatchArgs& b, int prec, bool odd, int lookup, int grid,
-                                  int block, hipStream_t s) {
+hipError_t launch_collide_batched(const BatchArgs& b, int prec, bool odd, int lookup, bool face,
+                                  int grid, int block, hipStream_t s) {
     LBM_DISPATCH_B_NB(LBM_LAUNCH_ODD_NB, collide_batched, dim3(grid), dim3(block), b);
     return hipGetLastError();
 }
@@ -1250,19 +1304,6 @@ hipError_t launch_field(const StepArgs& a, bool odd, int field, double* out, int
                         hipStream_t s) {
     (void)block;
     LBM_DISPATCH(field_kernel, dim3(grid_for(a, 256)), dim3(256), a, field, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_ghosts(const StepArgs& a, const int32_t* ghost_tail, const int32_t* ghost_src,
-                         int32_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const dim3 grid((n + 255) / 256);
-    if (a.prec == LBM_FP32_DEV)
-        hipLaunchKernelGGL(ghost_kernel<float>, grid, dim3(256), 0, s, a, ghost_tail, ghost_src,
-                           n);
-    else
-        hipLaunchKernelGGL(ghost_kernel<double>, grid, dim3(256), 0, s, a, ghost_tail, ghost_src,
-                           n);
     return hipGetLastError();
 }
 

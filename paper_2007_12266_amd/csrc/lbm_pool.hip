@@ -239,29 +239,14 @@ lbm_status upload_tables(lbm_pool* p) {
     return LBM_OK;
 }
 
-// A member with pressure faces gets the boundary work of its single-domain step between and
-// after the batched launches, in the same order: the ghost phi entries after the phase kernel,
-// then (flux inlet) the inlet density and the pressure faces after the collide kernel.
+// A member with pressure faces gets the face launches of its single-domain step after the
+// batched collide launch.
 lbm_status launch_face_work(lbm_pool* p, const std::vector<int32_t>& members, bool odd,
-                            bool after_collide) {
+                            bool settle) {
     for (int32_t s : members) {
         lbm_domain* d = p->slots[s];
-        if (!d || d->p.bc_z != 1) continue;
-        const StepArgs a = d->args();
-        if (!after_collide) {
-            if (!d->rank && !d->pre.ghost_tail.empty())
-                HIP_TRY(launch_ghosts(a, d->ghost_tail, d->ghost_src,
-                                      (int32_t)d->pre.ghost_tail.size(), p->stream));
-            continue;
-        }
-        // The member's reduction partials are free between reductions: scratch for the inlet.
-        if (d->inlet_rho)
-            HIP_TRY(launch_inlet_density(a, !odd, d->faces, (int32_t)d->pre.inlet.size(),
-                                         d->p.flux_in, d->inlet_rho, d->red_partials,
-                                         p->stream));
-        HIP_TRY(launch_pressure_bc(a, !odd, d->faces, (int32_t)d->pre.inlet.size(),
-                                   (int32_t)d->pre.outlet.size(), d->p.rho_in, d->p.rho_out,
-                                   d->inlet_rho, p->stream));
+        if (d && d->p.bc_z == 1)
+            if (lbm_status st = launch_faces(d, d->args(), odd, settle, p->stream)) return st;
     }
     return LBM_OK;
 }
@@ -269,14 +254,15 @@ lbm_status launch_face_work(lbm_pool* p, const std::vector<int32_t>& members, bo
 // n steps of the members in `members` over the tiles that b covers.
 lbm_status launch_steps_of(lbm_pool* p, const BatchArgs& b, const std::vector<int32_t>& members,
                            int64_t first_step, int64_t n) {
+    bool face = false;
+    for (int32_t s : members) face = face || (p->slots[s] && p->slots[s]->p.bc_z == 1);
     for (int64_t k = 0; k < n; ++k) {
         const bool odd = ((first_step + k) & 1) != 0;
-        HIP_TRY(launch_phase_batched(b, p->precision, odd, p->lookup, p->launch_grid(),
+        HIP_TRY(launch_phase_batched(b, p->precision, p->lookup, face, p->launch_grid(),
                                      kPoolBlock, p->stream));
-        if (lbm_status st = launch_face_work(p, members, odd, false)) return st;
-        HIP_TRY(launch_collide_batched(b, p->precision, odd, p->lookup, p->launch_grid(),
+        HIP_TRY(launch_collide_batched(b, p->precision, odd, p->lookup, face, p->launch_grid(),
                                        kPoolBlock, p->stream));
-        if (lbm_status st = launch_face_work(p, members, odd, true)) return st;
+        if (lbm_status st = launch_face_work(p, members, odd, k + 1 == n)) return st;
     }
     return LBM_OK;
 }
@@ -311,7 +297,7 @@ lbm_status capture(lbm_pool* p) {
                 // voxel, so the result is the same bitwise.
                 lbm_domain* d = p->slots[members[0]];
                 for (int64_t k = 0; k < p->chunk && st == LBM_OK; ++k)
-                    st = launch_domain_step(d, (k & 1) != 0);
+                    st = launch_domain_step(d, (k & 1) != 0, k + 1 == p->chunk);
             } else {
                 st = launch_steps_of(p, p->group_batch(g), members, 0, p->chunk);
             }

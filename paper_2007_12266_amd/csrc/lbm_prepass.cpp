@@ -391,6 +391,8 @@ std::string build_compact_lookup(Prepass& pre) {
             rec[kCompactKind] = spread <= 0xff ? 1 : 0;
         }
     }, nw * 64 * 18);
+    for (const std::vector<int32_t>* face : {&pre.inlet, &pre.outlet})
+        for (int32_t i : *face) c.wave[(size_t)(i / 64) * kCompactWaveInts + kCompactFace] = 1;
     c.n_ex = 0;
     for (int64_t w = 0; w < nw; ++w) {
         int32_t* rec = &c.wave[(size_t)w * kCompactWaveInts];

@@ -42,10 +42,11 @@ constexpr int kCoordXBits = 10, kCoordYBits = 11, kCoordZBits = 11;
 //    blocks of rows; 15-20% of the waves of those rocks): their 18 x 64 targets as int32 in
 //    exception row r, ex[(r * 18 + q - 1) * 64 + lane].
 // Per wave: kCompactWaveInts ints: pore bases of q = 1..18, tail bases of q = 1..18, the wave's
-// exception row or -1, and its kind.
+// exception row or -1, its kind, and the face mark.
 constexpr int kCompactWaveInts = 40;
 constexpr int kCompactExRow = 36;
 constexpr int kCompactKind = 37;
+constexpr int kCompactFace = 38;   // 1: the wave holds a voxel of a pressure face
 struct CompactNbr {
     // Byte waves: n8 = codes 1..4 | codes 5, 6 and mask bits 1..6 from bit 16;
     //   n16 = codes 7..10 | 11..14 | 15..18 | mask bits 7..18 from bit 0.

@@ -86,36 +86,26 @@ lbm_status check_domain(lbm_domain* d) {
     return LBM_OK;
 }
 
-// The launches of one time step at parity `odd`: densities and phase, the z-face mirror of
-// the phase, the fused gradient + collision + recolouring + streaming, then (pressure faces) the
-// inlet density of a flux inlet and the face conditions. `mark(kind, begin)` brackets each
-// kernel group with events when timing (kind 0: phase, 1: collide, 2: faces); null otherwise.
+// The launches of one time step at parity `odd`: densities and phase (with the z-face mirror of
+// the phase), the fused gradient + collision + recolouring + streaming, then the face launches
+// (launch_faces). `mark(kind, begin)` brackets each kernel group with events when timing (kind 0:
+// phase, 1: collide, 2: faces); null otherwise.
 template <typename Mark>
-lbm_status launch_step(lbm_domain* d, bool odd, Mark mark) {
+lbm_status launch_step(lbm_domain* d, bool odd, bool settle, Mark mark) {
     const lbm_tuning& tu = d->tune;
     const int par = odd ? 1 : 0;
     const StepArgs ap = d->args(tu.phase_block, tu.phase_schedule, tu.phase_run[par]);
     const StepArgs ac = d->args(tu.collide_block, tu.collide_schedule, tu.collide_run[par]);
     if (lbm_status s = mark(0, true)) return s;
     HIP_TRY(launch_phase(ap, odd, tu.phase_block, tu.phase_stream != 0, d->lds[0], d->stream));
-    if (!d->rank && !d->pre.ghost_tail.empty())
-        HIP_TRY(launch_ghosts(ap, d->ghost_tail, d->ghost_src, (int32_t)d->pre.ghost_tail.size(),
-                              d->stream));
     if (lbm_status s = mark(0, false)) return s;
     if (lbm_status s = mark(1, true)) return s;
     HIP_TRY(launch_collide(ac, odd, tu.collide_block, tu.collide_stream != 0, d->lds[1],
                            d->stream));
     if (lbm_status s = mark(1, false)) return s;
-    if (d->p.bc_z == 1) {
+    if (d->p.bc_z == 1 && (settle || d->faces_each_step())) {
         if (lbm_status s = mark(2, true)) return s;
-        // The reduction partials are free between reductions: scratch for the inlet sum.
-        if (d->inlet_rho)
-            HIP_TRY(launch_inlet_density(ac, !odd, d->faces, (int32_t)d->pre.inlet.size(),
-                                         d->p.flux_in, d->inlet_rho, d->red_partials,
-                                         d->stream));
-        HIP_TRY(launch_pressure_bc(ac, !odd, d->faces, (int32_t)d->pre.inlet.size(),
-                                   (int32_t)d->pre.outlet.size(), d->p.rho_in, d->p.rho_out,
-                                   d->inlet_rho, d->stream));
+        if (lbm_status s = launch_faces(d, ac, odd, settle, d->stream)) return s;
         if (lbm_status s = mark(2, false)) return s;
     }
     return LBM_OK;
@@ -130,7 +120,7 @@ lbm_status capture_step_chunk(lbm_domain* d) {
     HIP_TRY(hipStreamBeginCapture(d->stream, hipStreamCaptureModeThreadLocal));
     lbm_status st = LBM_OK;
     for (int64_t k = 0; k < kStepGraphChunk && st == LBM_OK; ++k)
-        st = launch_step(d, (k & 1) != 0, no_mark);
+        st = launch_step(d, (k & 1) != 0, k + 1 == kStepGraphChunk, no_mark);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(d->stream, &g);
     if (st != LBM_OK || e != hipSuccess) {
@@ -203,8 +193,9 @@ lbm_status step_impl(lbm_domain* d, int64_t nsteps, lbm_timing* timing) {
             d->step += kStepGraphChunk;
             s += kStepGraphChunk;
         } else {
-            st = timing ? launch_step(d, (d->step & 1) != 0, mark)
-                        : launch_step(d, (d->step & 1) != 0, no_mark);
+            const bool settle = s + 1 == nsteps || (every > 0 && (d->step + 1) % every == 0);
+            st = timing ? launch_step(d, (d->step & 1) != 0, settle, mark)
+                        : launch_step(d, (d->step & 1) != 0, settle, no_mark);
             if (st != LBM_OK) break;
             d->step += 1;
             s += 1;
@@ -245,7 +236,26 @@ lbm_status step_impl(lbm_domain* d, int64_t nsteps, lbm_timing* timing) {
 }  // namespace
 
 namespace lbm {
-lbm_status launch_domain_step(lbm_domain* d, bool odd) { return launch_step(d, odd, no_mark); }
+lbm_status launch_domain_step(lbm_domain* d, bool odd, bool settle) {
+    return launch_step(d, odd, settle, no_mark);
+}
+
+// A flux inlet's density needs a sum over the inlet plane: its kernels and the face kernel run
+// after every step. With fixed densities the next step's collide kernel applies the condition as
+// it reads the face voxels, and the face kernel only runs where a stretch of steps ends
+// (`settle`), so that the stored state is whole for whoever reads it next; both compute the same
+// values, and applying them twice changes nothing.
+lbm_status launch_faces(lbm_domain* d, const StepArgs& a, bool odd, bool settle, hipStream_t s) {
+    if (d->p.bc_z != 1 || !(settle || d->faces_each_step())) return LBM_OK;
+    // The reduction partials are free between reductions: scratch for the inlet sum.
+    if (d->inlet_rho)
+        HIP_TRY(launch_inlet_density(a, !odd, d->faces, (int32_t)d->pre.inlet.size(),
+                                     d->p.flux_in, d->inlet_rho, d->red_partials, s));
+    HIP_TRY(launch_pressure_bc(a, !odd, d->faces, (int32_t)d->pre.inlet.size(),
+                               (int32_t)d->pre.outlet.size(), d->p.rho_in, d->p.rho_out,
+                               d->inlet_rho, s));
+    return LBM_OK;
+}
 }  // namespace lbm
 
 // Device bytes lbm_domain_create allocates for a pre-passed input (every buffer is rounded up to
@@ -277,7 +287,7 @@ static int64_t domain_bytes(const lbm_params& p, const Prepass& pre) {
                             ? r(sizeof(uint32_t) * ld) + r(sizeof(RowWord) * pre.words.size())
                             : uses_compact(p) ? compact_bytes(pre)
                                               : r(sizeof(int32_t) * 18 * ld);
-    int64_t total = r(fb * 19 * ld) + r(eb * 8 * ld) + r(sizeof(int32_t)) +
+    int64_t total = r(fb * 19 * ld) + r(eb * 8 * ld) + r(2 * sizeof(int32_t)) +
                     r(eb * (size_t)(pre.n_pore + pre.n_tail)) + r(eb * ld) +
                     r(sizeof(double) * ld) + nbr +
                     r(sizeof(double) * kRedBlocks * kNRed) + r(sizeof(double) * kNRed) +
@@ -285,7 +295,6 @@ static int64_t domain_bytes(const lbm_params& p, const Prepass& pre) {
     const size_t faces = pre.inlet.size() + pre.outlet.size();
     if (faces) total += r(sizeof(int32_t) * faces) + r(sizeof(int8_t) * ld);
     if (faces && p.inlet_mode == 1) total += r(sizeof(double));
-    if (!pre.ghost_tail.empty()) total += 2 * r(sizeof(int32_t) * pre.ghost_tail.size());
     return total;
 }
 
@@ -389,7 +398,7 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
     const size_t ld = (size_t)pre.ld;
     d->f = d->dalloc(fb * 19 * ld);
     d->M = d->dalloc(eb * 8 * ld);
-    d->fresh = (int32_t*)d->dalloc(sizeof(int32_t));
+    d->fresh = (int32_t*)d->dalloc(2 * sizeof(int32_t));
     d->phi = d->dalloc(eb * (size_t)(pre.n_pore + pre.n_tail));
     d->ntot = d->dalloc(eb * ld);
     d->stage = (double*)d->dalloc(sizeof(double) * ld);
@@ -430,12 +439,7 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
         for (int32_t v : pre.inlet) face_flags[v] = 1;
         for (int32_t v : pre.outlet) face_flags[v] = 2;
     }
-    if (!pre.ghost_tail.empty()) {
-        d->ghost_tail = (int32_t*)d->dalloc(sizeof(int32_t) * pre.ghost_tail.size());
-        d->ghost_src = (int32_t*)d->dalloc(sizeof(int32_t) * pre.ghost_src.size());
-    }
-    if ((!faces.empty() && (!d->faces || !d->face || (p.inlet_mode == 1 && !d->inlet_rho))) ||
-        (!pre.ghost_tail.empty() && (!d->ghost_tail || !d->ghost_src))) {
+    if (!faces.empty() && (!d->faces || !d->face || (p.inlet_mode == 1 && !d->inlet_rho))) {
         d->release();
         return fail(LBM_ERR_OOM, "device allocation failed");
     }
@@ -482,12 +486,6 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
         guard(up(d->face, face_flags.data(), sizeof(int8_t) * ld), "upload face flags");
     }
     guard(up(d->fresh, &d->one, sizeof(int32_t)), "set fresh");
-    if (d->ghost_tail) {
-        guard(up(d->ghost_tail, pre.ghost_tail.data(), sizeof(int32_t) * pre.ghost_tail.size()),
-              "upload ghosts");
-        guard(up(d->ghost_src, pre.ghost_src.data(), sizeof(int32_t) * pre.ghost_src.size()),
-              "upload ghosts");
-    }
     guard(hipMemsetAsync(d->f, 0, fb * 19 * ld, d->stream), "clear f");
     guard(hipMemsetAsync(d->M, 0, eb * 8 * ld, d->stream), "clear M");
     if (st == LBM_OK) guard(launch_init(d->args(), phi0, d->block, d->stream), "init kernel");
