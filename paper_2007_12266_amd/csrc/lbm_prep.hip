@@ -19,13 +19,13 @@
 // chunk of x, so no thread divides a 64-bit index. Bit rows are packed with wide loads and
 // shuffles when rows are a multiple of 8 long, else with a ballot per word.
 //
-// Connectivity of the sphere centres to the inlet plane: union-find labelling. Every centre
-// starts under the first voxel of its run of centres along x; runs that touch across a -y or
+// Connectivity of the sphere centres to the inlet plane: union-find labelling of the runs of
+// centres along x, a run's label at its first voxel; runs that touch across a -y or
 // -z face (or the periodic x face) are united by linking the larger root under the smaller
 // with atomicMin, retrying from the new parent when another thread linked first. A parent
 // index is never larger than its child, so every find walks a strictly decreasing chain and
-// ends. After the merges each label is replaced by its root, the roots of the z = 0 plane are
-// flagged, and a centre is reached when its root is flagged. Counts use fixed-shape workgroup
+// ends. After the merges the roots of the runs in the z = 0 plane are flagged, and a centre is
+// reached when its run's root is flagged. Counts use fixed-shape workgroup
 // sums and a fixed-order final sum, so every result is deterministic.
 #include <algorithm>
 #include <cmath>
@@ -92,15 +92,6 @@ struct FeatureCentre {   // pore voxel where a sphere of squared radius k fits
     int32_t k;
     __device__ bool operator()(int64_t v) const { return pore[v] != 0 && d2[v] >= k; }
 };
-struct FeatureReached {  // centre whose component touches the z = 0 plane
-    const int32_t* label;
-    const uint8_t* flag;
-    __device__ bool operator()(int64_t v) const {
-        const int32_t l = label[v];
-        return l >= 0 && flag[l] != 0;
-    }
-};
-
 // Four consecutive 64-voxel words per wave (their loads in flight together): lane i holds bit i
 // of each (x = 64 w + i of the word's row).
 constexpr int kWordsPerWave = 4;
@@ -288,13 +279,16 @@ __device__ __forceinline__ int row_dist(const uint64_t* __restrict__ r, int W, i
     return d;
 }
 
+// A workgroup takes 256 >> qshift rows, with 1 << qshift threads (at least the row's quads, at
+// most 256) for each: one row to a workgroup left most of its threads idle and was bound by the
+// rate at which workgroups start (128^3: 16384 of one wave, 10.3 us; now 2048, 5.9 us).
 template <typename T>
 __global__ void __launch_bounds__(256) edt_row_kernel(Box b, const uint64_t* __restrict__ bits,
-                                                      int lim, int32_t cap,
+                                                      int qshift, int lim, int32_t cap,
                                                       T* __restrict__ out) {
-    const int row = (int)blockIdx.x;
-    const int x0 = 4 * ((int)blockIdx.y * (int)blockDim.x + (int)threadIdx.x);
-    if (x0 >= b.nx) return;
+    const int row = (int)blockIdx.x * (256 >> qshift) + ((int)threadIdx.x >> qshift);
+    const int x0 = 4 * (((int)blockIdx.y << qshift) + ((int)threadIdx.x & ((1 << qshift) - 1)));
+    if (x0 >= b.nx || row >= b.ny * b.nz) return;
     const uint64_t* r = bits + (int64_t)row * b.W;
     const bool per = (b.per & 1) != 0;
     const int w = x0 >> 6;   // the four voxels share this word
@@ -355,15 +349,22 @@ __device__ __forceinline__ int wall_min(const Box& b, int walls, int x, int y, i
 }
 
 // Line pass along axis `ax` (1: y, 2: z) over kSeg consecutive positions c0 .. c0+kSeg-1 of one
-// line per thread: the window in[c0-4 .. c0+kSeg+3] is read at once, so offsets up to 4 cost no
-// further load, and larger ones (only where the best value so far exceeds 25) continue from
-// memory. A window value of a wrapped position further than half a period is an upper bound of
-// that position's term, never below the minimum, so it may stay in.
+// line per thread: the window in[c0-kWin .. c0+kSeg+kWin-1] is read at once (an unconditional
+// load for each place, the ones outside a non-periodic line replaced afterwards), so offsets up
+// to kWin cost no further load, and larger ones (only where the best value so far exceeds
+// (kWin + 1)^2) continue from memory, one dependent round trip per offset. kWin was 4 with a
+// branch around each load: the continuation then ran in most waves of a rock image, whose pore
+// bodies are 5 to 8 voxels wide (128^3: 10.3 us a pass; now 7.4; the z pass with the wall terms 10.6). A window value of a wrapped
+// position further than half a period is an upper bound of that position's term, never below the
+// minimum, so it may stay in.
 //   MODE 0: out[v] = min(cap, best), with the wall-plane terms of `walls`;
+//   MODE 2: the same without a cap, -1 where there is no feature (the last pass of a transform
+//           that is the result);
 //   MODE 1 (z pass of the drainage dilation): a pore voxel is non-wetting when best < cap (the
 //           squared radius); writes nw when it is not null and the count of each workgroup
 //           (kPrepThreads threads).
 constexpr int kSeg = 8;
+constexpr int kWin = 8;
 
 template <int MODE, typename T>
 __global__ void __launch_bounds__(256) edt_seg_kernel(Box b, int ax, int32_t cap, int walls,
@@ -384,12 +385,17 @@ __global__ void __launch_bounds__(256) edt_seg_kernel(Box b, int ax, int32_t cap
     const int c0 = seg * kSeg;
     int cnt = 0;
     if (active) {
-        int win[kSeg + 8];
+        int win[kSeg + 2 * kWin];
 #pragma unroll
-        for (int j = 0; j < kSeg + 8; ++j) {
-            int c = c0 - 4 + j;
-            if (c < 0 || c >= n) c = per ? ((c % n) + n) % n : -1;
-            win[j] = c >= 0 ? (int)in[base + (int64_t)c * stride] : kInf;
+        for (int j = 0; j < kSeg + 2 * kWin; ++j) {
+            int c = c0 - kWin + j;
+            if (c < 0 || c >= n) c = per ? ((c % n) + n) % n : c0;   // c0: any place of the line
+            win[j] = (int)in[base + (int64_t)c * stride];
+        }
+        if (!per) {
+#pragma unroll
+            for (int j = 0; j < kSeg + 2 * kWin; ++j)
+                if (c0 - kWin + j < 0 || c0 - kWin + j >= n) win[j] = kInf;
         }
 #pragma unroll
         for (int i = 0; i < kSeg; ++i) {
@@ -400,14 +406,17 @@ __global__ void __launch_bounds__(256) edt_seg_kernel(Box b, int ax, int32_t cap
                 if (nw) nw[v] = 0;
                 continue;
             }
-            int best = win[i + 4];
+            int best = win[i + kWin];
             if (walls) best = wall_min(b, walls, x, ax == 1 ? c : o, ax == 1 ? o : c, best);
 #pragma unroll
-            for (int d = 1; d <= 4; ++d)
-                best = min(best, min(win[i + 4 + d], win[i + 4 - d]) + d * d);
-            if (best > 25) best = line_min_from(in, base, stride, c, n, per, best, 5);
+            for (int d = 1; d <= kWin; ++d)
+                best = min(best, min(win[i + kWin + d], win[i + kWin - d]) + d * d);
+            if (best > (kWin + 1) * (kWin + 1))
+                best = line_min_from(in, base, stride, c, n, per, best, kWin + 1);
             if (MODE == 0) {
                 out[v] = (T)min(best, cap);
+            } else if (MODE == 2) {
+                out[v] = best >= kInf ? (T)-1 : (T)best;
             } else {
                 const bool f = best < cap;
                 cnt += f ? 1 : 0;
@@ -449,12 +458,18 @@ __device__ __forceinline__ int32_t label_load(const int32_t* L, int32_t i) {
     return __hip_atomic_load(L + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Root of i: parents are never larger than their children, so the walk strictly decreases.
-__device__ __forceinline__ int32_t find_root(const int32_t* L, int32_t i) {
+// Root of i: parents are never larger than their children, so the walk strictly decreases. On
+// the way every entry passed is pointed at its grandparent (path halving), so that chains stay
+// short; the store races only with stores of other ancestors and with a link that another
+// thread is making of the entry, and that thread goes on to unite what the entry pointed at
+// (see unite), so no connection is lost.
+__device__ __forceinline__ int32_t find_root(int32_t* L, int32_t i) {
     int32_t p = label_load(L, i);
     while (p != i) {
+        const int32_t g = label_load(L, p);
+        if (g != p) __hip_atomic_store(L + i, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         i = p;
-        p = label_load(L, i);
+        p = g;
     }
     return i;
 }
@@ -488,59 +503,103 @@ __device__ __forceinline__ int run_start(const uint64_t* __restrict__ r, int x) 
     return (w << 6) + 64 - __clzll((long long)m);
 }
 
-// Every centre starts under the first voxel of its run along x (a parent no larger than the
-// child), so a run is one component before any union.
-__global__ void __launch_bounds__(256) ccl_init_kernel(Box b, const uint64_t* __restrict__ centre,
-                                                       int32_t* __restrict__ L) {
-    const VoxelIdx t = voxel_of(b);
-    if (!t.active) return;
-    const uint64_t* r = centre + (int64_t)t.row * b.W;
-    const bool c = (r[t.x >> 6] >> (t.x & 63)) & 1ull;
-    L[t.v] = c ? (int32_t)((int64_t)t.row * b.nx + run_start(r, t.x)) : -1;
+// The labelling works on runs: a run's label lies at its first voxel, and no other entry is
+// touched. One thread takes one 64-voxel word of a row and loops over the few runs in it. (With
+// a thread per voxel, most of them idle, and a label per voxel the merge was bound by rounds of
+// waves that each waited for a chain of labels: 256^3, mean over the radii of a drainage,
+// merge 221 us, init 29, compress 49, pack 28; now 171, 8, none and 18: what is left is the
+// merge of the widest radii, up to 750 us, in chains of labels that other XCDs change.)
+struct WordIdx {
+    int64_t k;       // word
+    int row, w;
+    bool active;
+};
+__device__ __forceinline__ WordIdx word_of(const Box& b) {
+    WordIdx t;
+    t.k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    t.active = t.k < b.nwords;
+    t.row = (int)(t.k / b.W);
+    t.w = (int)(t.k - (int64_t)t.row * b.W);
+    return t;
 }
 
-// Unions across the -y and -z faces (and the periodic x face). Two runs that overlap are
-// united once, at the first overlapping x: where both left neighbours are centres too, the
-// pair to the left has already linked the same two runs.
+// Bits of word w of row r that start a run.
+__device__ __forceinline__ uint64_t run_starts(const uint64_t* __restrict__ r, int w) {
+    const uint64_t m = r[w], before = w > 0 ? r[w - 1] >> 63 : 0ull;
+    return m & ~((m << 1) | before);
+}
+
+// Every run is its own component, not reached.
+__global__ void __launch_bounds__(256) ccl_init_kernel(Box b, const uint64_t* __restrict__ centre,
+                                                       int32_t* __restrict__ L,
+                                                       uint8_t* __restrict__ flag) {
+    const WordIdx t = word_of(b);
+    if (!t.active) return;
+    const int32_t v0 = (int32_t)((int64_t)t.row * b.nx + 64 * t.w);
+    for (uint64_t m = run_starts(centre + (int64_t)t.row * b.W, t.w); m; m &= m - 1) {
+        const int32_t v = v0 + __ffsll((long long)m) - 1;
+        L[v] = v;
+        flag[v] = 0;
+    }
+}
+
+// Unions across the -y (blockIdx.y 0) and -z (1) faces, and the periodic x face (with 0). Two
+// runs that overlap are united once, at the first overlapping x: where both left neighbours are
+// centres too, the pair to the left has already linked the same two runs.
 __global__ void __launch_bounds__(256) ccl_merge_kernel(Box b, const uint64_t* __restrict__ centre,
                                                         int32_t* L) {
-    const VoxelIdx t = voxel_of(b);
-    if (!t.active || !bit_at(centre, b, t.row, t.x)) return;
-    const int y = t.row % b.ny, z = t.row / b.ny;
-    const int32_t v = (int32_t)t.v;
-    const bool left = t.x > 0 && bit_at(centre, b, t.row, t.x - 1);
-    if (t.x == 0 && (b.per & 1) && b.nx > 1 && bit_at(centre, b, t.row, b.nx - 1))
-        unite(L, v, (int32_t)((int64_t)t.row * b.nx + b.nx - 1));
-    int yn = y - 1;
-    if (yn < 0 && (b.per & 2)) yn = b.ny - 1;
-    if (yn >= 0 && yn != y) {
-        const int rn = z * b.ny + yn;
-        if (bit_at(centre, b, rn, t.x) && !(left && bit_at(centre, b, rn, t.x - 1)))
-            unite(L, v, (int32_t)((int64_t)rn * b.nx + t.x));
-    }
-    int zn = z - 1;
-    if (zn < 0 && (b.per & 4)) zn = b.nz - 1;
-    if (zn >= 0 && zn != z) {
-        const int rn = zn * b.ny + y;
-        if (bit_at(centre, b, rn, t.x) && !(left && bit_at(centre, b, rn, t.x - 1)))
-            unite(L, v, (int32_t)((int64_t)rn * b.nx + t.x));
-    }
-}
-
-__global__ void __launch_bounds__(256) ccl_compress_kernel(Box b, int32_t* L) {
-    const VoxelIdx t = voxel_of(b);
+    const WordIdx t = word_of(b);
     if (!t.active) return;
-    const int32_t l = L[t.v];
-    if (l >= 0) L[t.v] = find_root(L, l);
+    const uint64_t* r = centre + (int64_t)t.row * b.W;
+    const uint64_t m = r[t.w];
+    if (!m) return;
+    const int y = t.row % b.ny, z = t.row / b.ny;
+    const int64_t base = (int64_t)t.row * b.nx;
+    const bool along_z = blockIdx.y != 0;
+    if (!along_z && t.w == 0 && (b.per & 1) && b.nx > 1 && (m & 1ull) &&
+        bit_at(centre, b, t.row, b.nx - 1))
+        unite(L, (int32_t)base, (int32_t)(base + run_start(r, b.nx - 1)));
+    int c = (along_z ? z : y) - 1;
+    if (c < 0 && (b.per & (along_z ? 4 : 2))) c = (along_z ? b.nz : b.ny) - 1;
+    if (c < 0 || c == (along_z ? z : y)) return;
+    const int rn = along_z ? c * b.ny + y : z * b.ny + c;
+    const uint64_t* q = centre + (int64_t)rn * b.W;
+    const uint64_t o = m & q[t.w];
+    const uint64_t before = t.w > 0 ? (r[t.w - 1] & q[t.w - 1]) >> 63 : 0ull;
+    for (uint64_t f = o & ~((o << 1) | before); f; f &= f - 1) {
+        const int x = 64 * t.w + __ffsll((long long)f) - 1;
+        unite(L, (int32_t)(base + run_start(r, x)),
+              (int32_t)((int64_t)rn * b.nx + run_start(q, x)));
+    }
 }
 
-// Flag the roots of the centres in the z = 0 plane (rows 0 .. ny-1). Every writer stores 1.
-__global__ void __launch_bounds__(256) ccl_mark_kernel(Box b, const int32_t* __restrict__ L,
-                                                       uint8_t* __restrict__ flag) {
-    const VoxelIdx t = voxel_of(b);
+// Flag the roots of the runs in the z = 0 plane (rows 0 .. ny-1). Every writer stores 1.
+__global__ void __launch_bounds__(256) ccl_mark_kernel(Box b, const uint64_t* __restrict__ centre,
+                                                       int32_t* L, uint8_t* __restrict__ flag) {
+    const WordIdx t = word_of(b);
     if (!t.active || t.row >= b.ny) return;
-    const int32_t l = L[t.v];
-    if (l >= 0) flag[l] = 1;
+    const int32_t v0 = (int32_t)((int64_t)t.row * b.nx + 64 * t.w);
+    for (uint64_t m = run_starts(centre + (int64_t)t.row * b.W, t.w); m; m &= m - 1)
+        flag[find_root(L, v0 + __ffsll((long long)m) - 1)] = 1;
+}
+
+// Reach bits: the runs whose root is flagged.
+__global__ void __launch_bounds__(256) ccl_reach_kernel(Box b, const uint64_t* __restrict__ centre,
+                                                        int32_t* L,
+                                                        const uint8_t* __restrict__ flag,
+                                                        uint64_t* __restrict__ reach) {
+    const WordIdx t = word_of(b);
+    if (!t.active) return;
+    const uint64_t* r = centre + (int64_t)t.row * b.W;
+    const int32_t base = (int32_t)((int64_t)t.row * b.nx);
+    uint64_t out = 0;
+    for (uint64_t m = r[t.w]; m;) {
+        const uint64_t low = m & (0ull - m), run = m & ~(m + low);   // the lowest run in the word
+        const int x = 64 * t.w + __ffsll((long long)low) - 1;
+        if (flag[find_root(L, base + run_start(r, x))]) out |= run;
+        m &= ~run;
+    }
+    reach[t.k] = out;
 }
 
 // Largest d2 over pore voxels and the pore count: eight consecutive voxels per thread (wide
@@ -701,14 +760,15 @@ lbm_status check_box(int32_t nx, int32_t ny, int32_t nz, const int32_t* periodic
 
 // Grid of the per-voxel kernels (one workgroup per row and chunk of x) and of the bit packing.
 dim3 vox_grid(const Box& b) { return dim3((unsigned)(b.ny * b.nz), (unsigned)b.chunks); }
-// Row pass: four voxels per thread.
-int row_threads(const Box& b) {
-    const int quads = (b.nx + 3) / 4;
-    return std::min(kPrepThreads, 64 * ((quads + 63) / 64));
+// Row pass: four voxels per thread, 1 << row_shift threads per row.
+int row_shift(const Box& b) {
+    int s = 0;
+    while (s < 8 && (4 << s) < b.nx) ++s;
+    return s;
 }
 dim3 row_grid(const Box& b) {
-    const int t = 4 * row_threads(b);
-    return dim3((unsigned)(b.ny * b.nz), (unsigned)((b.nx + t - 1) / t));
+    const int s = row_shift(b), rows = 256 >> s, span = 4 << s;
+    return dim3((unsigned)((b.ny * b.nz + rows - 1) / rows), (unsigned)((b.nx + span - 1) / span));
 }
 dim3 pack8_grid(const Box& b) { return dim3((unsigned)((b.nwords + 31) / 32)); }
 dim3 pack_grid(const Box& b) {
@@ -762,8 +822,8 @@ int64_t seg_blocks(const Box& b, int ax) {
 template <typename T>
 lbm_status edt_xy(const Box& b, const uint64_t* bits, int32_t cap, T* tmp, T* mid,
                   hipStream_t s) {
-    hipLaunchKernelGGL(edt_row_kernel<T>, row_grid(b), dim3(row_threads(b)), 0, s, b, bits,
-                       row_limit(b, cap), cap, tmp);
+    hipLaunchKernelGGL(edt_row_kernel<T>, row_grid(b), dim3(256), 0, s, b, bits,
+                       row_shift(b), row_limit(b, cap), cap, tmp);
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL((edt_seg_kernel<0, T>), seg_grid(b, 1), dim3(b.tpb), 0, s, b, 1, cap, 0,
                        (const T*)tmp, mid, nullptr, nullptr, nullptr);
@@ -772,12 +832,13 @@ lbm_status edt_xy(const Box& b, const uint64_t* bits, int32_t cap, T* tmp, T* mi
 }
 
 // Full squared distance transform of the feature bits into out (tmp: a second buffer of nvox);
-// values at or above cap are clipped to cap.
-template <typename T>
+// values at or above cap are clipped to cap (MODE 0), or -1 stands for no feature (MODE 2, no
+// cap).
+template <typename T, int MODE = 0>
 lbm_status edt(const Box& b, const uint64_t* bits, int32_t cap, int walls, T* tmp, T* out,
                hipStream_t s) {
     if (lbm_status st = edt_xy<T>(b, bits, cap, out, tmp, s)) return st;
-    hipLaunchKernelGGL((edt_seg_kernel<0, T>), seg_grid(b, 2), dim3(b.tpb), 0, s, b, 2, cap,
+    hipLaunchKernelGGL((edt_seg_kernel<MODE, T>), seg_grid(b, 2), dim3(b.tpb), 0, s, b, 2, cap,
                        walls, (const T*)tmp, out, nullptr, nullptr, nullptr);
     HIP_TRY(hipGetLastError());
     return LBM_OK;
@@ -799,21 +860,33 @@ struct DrainBuffers {
 
 // Reach bits: the centres whose face-connected component touches the z = 0 plane.
 lbm_status connect_to_inlet(const Box& b, const DrainBuffers& db, hipStream_t s) {
-    hipLaunchKernelGGL(ccl_init_kernel, vox_grid(b), dim3(b.tpb), 0, s, b,
-                       (const uint64_t*)db.centre, db.label);
+    const unsigned blocks = (unsigned)((b.nwords + 255) / 256);
+    const uint64_t* centre = db.centre;
+    hipLaunchKernelGGL(ccl_init_kernel, dim3(blocks), dim3(256), 0, s, b, centre, db.label,
+                       db.flag);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(ccl_merge_kernel, vox_grid(b), dim3(b.tpb), 0, s, b,
-                       (const uint64_t*)db.centre, db.label);
+    hipLaunchKernelGGL(ccl_merge_kernel, dim3(blocks, 2), dim3(256), 0, s, b, centre, db.label);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(ccl_compress_kernel, vox_grid(b), dim3(b.tpb), 0, s, b, db.label);
+    const int64_t plane = (int64_t)b.ny * b.W;
+    hipLaunchKernelGGL(ccl_mark_kernel, dim3((unsigned)((plane + 255) / 256)), dim3(256), 0, s, b,
+                       centre, db.label, db.flag);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemsetAsync(db.flag, 0, (size_t)b.nvox, s));
-    hipLaunchKernelGGL(ccl_mark_kernel, vox_grid(b), dim3(b.tpb), 0, s, b,
-                       (const int32_t*)db.label, db.flag);
+    hipLaunchKernelGGL(ccl_reach_kernel, dim3(blocks), dim3(256), 0, s, b, centre, db.label,
+                       (const uint8_t*)db.flag, db.reach);
     HIP_TRY(hipGetLastError());
-    FeatureReached fr{db.label, db.flag};
-    hipLaunchKernelGGL(pack_kernel<FeatureReached>, pack_grid(b), dim3(256), 0, s, b, fr,
-                       db.reach);
+    return LBM_OK;
+}
+
+// The passes of a drainage dilation: per-workgroup counts of the pore voxels closer than
+// sqrt(k) to a feature bit, and their mask when nw_dev is not null.
+template <typename T>
+lbm_status dilate_count(const Box& b, const uint64_t* feat, int32_t k, T* tmp, T* mid,
+                        const DrainBuffers& db, uint8_t* nw_dev, hipStream_t s) {
+    if (lbm_status st = edt_xy<T>(b, feat, k, tmp, mid, s)) return st;
+    // kPrepThreads per workgroup (its block sum needs them all): whenever b.tpb is smaller,
+    // there is one chunk per row, which 256 threads cover as well.
+    hipLaunchKernelGGL((edt_seg_kernel<1, T>), seg_grid(b, 2), dim3(kPrepThreads), 0, s, b, 2, k,
+                       0, (const T*)mid, (T*)nullptr, (const uint8_t*)db.pore, nw_dev, db.part);
     HIP_TRY(hipGetLastError());
     return LBM_OK;
 }
@@ -828,12 +901,14 @@ lbm_status drain_eval(const Box& b, const DrainBuffers& db, int32_t k, bool inle
         if (lbm_status st = connect_to_inlet(b, db, s)) return st;
         feat = db.reach;
     }
-    if (lbm_status st = edt_xy(b, feat, k, db.tmp, db.mid, s)) return st;
-    // kPrepThreads per workgroup (its block sum needs them all): whenever b.tpb is smaller,
-    // there is one chunk per row, which 256 threads cover as well.
-    hipLaunchKernelGGL((edt_seg_kernel<1, int32_t>), seg_grid(b, 2), dim3(kPrepThreads), 0, s, b, 2, k, 0,
-                       (const int32_t*)db.mid, nullptr, (const uint8_t*)db.pore, nw_dev, db.part);
-    HIP_TRY(hipGetLastError());
+    // The passes hold values up to k: bytes while they suffice (k <= 255, spheres of a radius up
+    // to 15 voxels, all that a rock's pores admit), a quarter of the int32 traffic.
+    if (k <= 255) {
+        if (lbm_status st = dilate_count(b, feat, k, (uint8_t*)db.tmp, (uint8_t*)db.mid, db, nw_dev, s))
+            return st;
+    } else if (lbm_status st = dilate_count(b, feat, k, db.tmp, db.mid, db, nw_dev, s)) {
+        return st;
+    }
     hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(kSumThreads), 0, s, (const int*)db.part,
                        seg_blocks(b, 2), db.part2);
     HIP_TRY(hipGetLastError());
@@ -873,13 +948,6 @@ lbm_status noalloc_scratch_of_current_device(void** out) {
     return LBM_OK;
 }
 
-// No feature within reach: kInf -> -1, as the host side of lbm_prep_distance does.
-__global__ void __launch_bounds__(256) none_to_minus_one_kernel(int32_t* __restrict__ d,
-                                                                int64_t n) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n && d[v] >= kInf) d[v] = -1;
-}
-
 }  // namespace
 
 namespace lbm {
@@ -917,10 +985,8 @@ lbm_status lbm_prep_distance(int32_t nx, int32_t ny, int32_t nz, const int32_t p
     if (!f || !bits || !tmp || !out) return sc.failed("the transform");
     HIP_TRY(copy_to_device(f, feature, (size_t)b.nvox, s));
     if (lbm_status st = pack(b, FeatureNonzero{f}, Wide8Nonzero{f}, bits, s)) return st;
-    if (lbm_status st = edt(b, bits, kInf, wall_axes, tmp, out, s)) return st;
+    if (lbm_status st = edt<int32_t, 2>(b, bits, kInf, wall_axes, tmp, out, s)) return st;
     HIP_TRY(copy_to_host(dist_sq, out, sizeof(int32_t) * (size_t)b.nvox, s));
-    for (int64_t v = 0; v < b.nvox; ++v)
-        if (dist_sq[v] >= kInf) dist_sq[v] = -1;
     return LBM_OK;
 }
 
@@ -954,10 +1020,8 @@ lbm_status lbm_prep_distance_noalloc(int32_t nx, int32_t ny, int32_t nz, const i
         hipLaunchKernelGGL(pack_kernel<FeatureNonzero>, pack_grid(b), dim3(256), 0, s, b,
                            FeatureNonzero{feature_dev}, bits);
     HIP_TRY(hipGetLastError());
-    if (lbm_status st = edt(b, bits, kInf, wall_axes, tmp, dist_sq_dev, s)) return st;
-    hipLaunchKernelGGL(none_to_minus_one_kernel, dim3((unsigned)((b.nvox + 255) / 256)),
-                       dim3(256), 0, s, dist_sq_dev, b.nvox);
-    HIP_TRY(hipGetLastError());
+    if (lbm_status st = edt<int32_t, 2>(b, bits, kInf, wall_axes, tmp, dist_sq_dev, s))
+        return st;
     return LBM_OK;
 }
 
