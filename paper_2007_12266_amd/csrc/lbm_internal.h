@@ -141,6 +141,25 @@ hipError_t launch_field(const StepArgs& a, bool odd, int field, double* out, int
 hipError_t copy_to_device(void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t copy_to_host(void* dst, const void* src, size_t bytes, hipStream_t s);
 
+// Pinned host memory of up to kPinnedBytes that a kernel of this call writes its result into (the
+// host address is valid on every device). ptr() is null when `bytes` is larger or no memory is to
+// be had: the caller then goes through a device buffer.
+constexpr size_t kPinnedBytes = size_t(8) << 20;
+class PinnedOut {
+public:
+    explicit PinnedOut(size_t bytes);
+    ~PinnedOut();
+    PinnedOut(const PinnedOut&) = delete;
+    PinnedOut& operator=(const PinnedOut&) = delete;
+    void* ptr() const { return ptr_; }
+    // Waits for stream s, on which the kernel was launched, and copies the result to dst. Must
+    // also run (or the stream be waited for) before the object goes if a launch used ptr().
+    hipError_t take(void* dst, size_t bytes, hipStream_t s);
+
+private:
+    void* ptr_ = nullptr;
+};
+
 // Squared distances between voxel centres for the morphological step (lbm_prep.hip), clipped
 // at cap (<= 255): to_a[v] to the nearest voxel whose bit is set in label_bits (rows packed as
 // 64-voxel words), to_other[v] to the nearest voxel whose bit is clear or beyond a non-periodic

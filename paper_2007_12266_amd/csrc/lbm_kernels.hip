@@ -834,11 +834,11 @@ __global__ void __launch_bounds__(256) collide_batched(BatchArgs b) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Per-voxel read-out in FP64 from either storage: N_a, N_b, rho, j.
+// Per-voxel read-out in FP64 from either storage: rho and j, and with the densities N_a, N_b.
 // ------------------------------------------------------------------------------------------
 template <int PREC, bool ODD>
-__device__ __forceinline__ void voxel_state(const StepArgs& a, int i, double& na, double& nbv,
-                                            double& rho, double& jx, double& jy, double& jz) {
+__device__ __forceinline__ void voxel_flow(const StepArgs& a, int i, double& rho, double& jx,
+                                           double& jy, double& jz) {
     using P = Prec<PREC>;
     using F = typename P::F;
     const F* f = (const F*)a.f;
@@ -847,8 +847,6 @@ __device__ __forceinline__ void voxel_state(const StepArgs& a, int i, double& na
     const Pos pos = pos_of(a, i);
 #pragma unroll
     for (int q = 1; q < 19; ++q) r[q] = ODD ? nb_stream(a, q, i, pos) : 0;
-    int ghost;
-    densities<PREC>(a, i, *a.fresh != 0, na, nbv, ghost);   // callers' waves are aligned
     rho = 0.0;
     jx = jy = jz = 0.0;
 #pragma unroll
@@ -860,6 +858,14 @@ __device__ __forceinline__ void voxel_state(const StepArgs& a, int i, double& na
         jz += CZ[q] * v;
     }
     if (P::kDev) rho += 1.0;
+}
+
+template <int PREC, bool ODD>
+__device__ __forceinline__ void voxel_state(const StepArgs& a, int i, double& na, double& nbv,
+                                            double& rho, double& jx, double& jy, double& jz) {
+    int ghost;
+    densities<PREC>(a, i, *a.fresh != 0, na, nbv, ghost);   // callers' waves are aligned
+    voxel_flow<PREC, ODD>(a, i, rho, jx, jy, jz);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -875,6 +881,10 @@ __device__ __forceinline__ double wave_sum(double v) {
 template <int PREC, bool ODD>
 __device__ __forceinline__ void reduce_block(const StepArgs& a, int blk,
                                              double* __restrict__ partials) {
+    if ((int64_t)blk * kRedThreads >= a.N) {   // no voxel: a small domain has few blocks that do
+        if (threadIdx.x < kNRed) partials[(size_t)blk * kNRed + threadIdx.x] = 0.0;
+        return;
+    }
     double acc[kNRed];
 #pragma unroll
     for (int k = 0; k < kNRed; ++k) acc[k] = 0.0;
@@ -982,13 +992,19 @@ __global__ void __launch_bounds__(256) field_kernel(StepArgs a, int field,
                                                     double* __restrict__ out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= a.N) return;
-    double na, nbv, rho, jx, jy, jz;
-    voxel_state<PREC, ODD>(a, i, na, nbv, rho, jx, jy, jz);
     double v;
+    if (field <= LBM_FIELD_PHI) {   // N_a, N_b, phi: the components alone (a third of the bytes)
+        double na, nbv;
+        int ghost;
+        densities<PREC>(a, i, *a.fresh != 0, na, nbv, ghost);
+        out[i] = field == LBM_FIELD_NA   ? na
+                 : field == LBM_FIELD_NB ? nbv
+                                         : (na - nbv) / (na + nbv);
+        return;
+    }
+    double rho, jx, jy, jz;
+    voxel_flow<PREC, ODD>(a, i, rho, jx, jy, jz);
     switch (field) {
-    case LBM_FIELD_NA: v = na; break;
-    case LBM_FIELD_NB: v = nbv; break;
-    case LBM_FIELD_PHI: v = (na - nbv) / (na + nbv); break;
     case LBM_FIELD_RHO: v = rho; break;
     case LBM_FIELD_P: v = rho / 3.0; break;
     case LBM_FIELD_UX: v = jx + 0.5 * a.F[0]; break;

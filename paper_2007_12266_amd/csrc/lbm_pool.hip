@@ -476,10 +476,18 @@ lbm_status lbm_pool_reduce_all(lbm_pool* p, lbm_reduction* out, int32_t max_coun
     const int32_t n = std::min(highest_slot(p), std::max(max_count, 0));
     std::vector<double> acc((size_t)std::max(n, 1) * kNRed);
     if (n > 0) {
-        HIP_TRY(launch_reduce_batched(p->batch(), p->precision, (p->step & 1) != 0, n,
-                                      p->d_partials, p->d_red, p->stream));
-        HIP_TRY(hipMemcpyAsync(acc.data(), p->d_red, sizeof(double) * kNRed * n,
-                               hipMemcpyDeviceToHost, p->stream));
+        const size_t bytes = sizeof(double) * kNRed * n;
+        PinnedOut sums(bytes);
+        const hipError_t e =
+            launch_reduce_batched(p->batch(), p->precision, (p->step & 1) != 0, n, p->d_partials,
+                                  sums.ptr() ? (double*)sums.ptr() : p->d_red, p->stream);
+        if (e != hipSuccess) (void)hipStreamSynchronize(p->stream);
+        HIP_TRY(e);
+        if (sums.ptr()) {
+            HIP_TRY(sums.take(acc.data(), bytes, p->stream));
+        } else {
+            HIP_TRY(hipMemcpyAsync(acc.data(), p->d_red, bytes, hipMemcpyDeviceToHost, p->stream));
+        }
     }
     HIP_TRY(hipStreamSynchronize(p->stream));
     for (int32_t s = 0; s < n; ++s) {

@@ -538,8 +538,16 @@ lbm_status lbm_read_pore_field(lbm_domain* d, int32_t field, double* host_pore) 
     if (field < LBM_FIELD_NA || field > LBM_FIELD_UZ) return fail(LBM_ERR_ARG, "bad field id");
     if (!host_pore) return fail(LBM_ERR_ARG, "host_pore must be non-null");
     const StepArgs a = d->args();
-    HIP_TRY(launch_field(a, (d->step & 1) != 0, field, d->stage, d->block, d->stream));
-    HIP_TRY(copy_to_host(host_pore, d->stage, sizeof(double) * d->pre.n_pore, d->stream));
+    const bool odd = (d->step & 1) != 0;
+    const size_t bytes = sizeof(double) * (size_t)d->pre.n_pore;
+    PinnedOut out(bytes);
+    if (out.ptr()) {
+        HIP_TRY(launch_field(a, odd, field, (double*)out.ptr(), d->block, d->stream));
+        HIP_TRY(out.take(host_pore, bytes, d->stream));
+        return LBM_OK;
+    }
+    HIP_TRY(launch_field(a, odd, field, d->stage, d->block, d->stream));
+    HIP_TRY(copy_to_host(host_pore, d->stage, bytes, d->stream));
     return LBM_OK;
 }
 
@@ -564,10 +572,18 @@ lbm_status lbm_pore_index(lbm_domain* d, int64_t* host_index) {
 lbm_status lbm_reduce(lbm_domain* d, lbm_reduction* out) {
     if (lbm_status s = check_domain(d)) return s;
     if (!out) return fail(LBM_ERR_ARG, "out must be non-null");
-    if (lbm_status s = record_reduction(d, d->red_out)) return s;
     double acc[kNRed];
-    HIP_TRY(hipMemcpyAsync(acc, d->red_out, sizeof acc, hipMemcpyDeviceToHost, d->stream));
-    HIP_TRY(hipStreamSynchronize(d->stream));
+    PinnedOut sums(sizeof acc);
+    if (lbm_status s = record_reduction(d, sums.ptr() ? (double*)sums.ptr() : d->red_out)) {
+        (void)hipStreamSynchronize(d->stream);
+        return s;
+    }
+    if (sums.ptr()) {
+        HIP_TRY(sums.take(acc, sizeof acc, d->stream));
+    } else {
+        HIP_TRY(hipMemcpyAsync(acc, d->red_out, sizeof acc, hipMemcpyDeviceToHost, d->stream));
+        HIP_TRY(hipStreamSynchronize(d->stream));
+    }
     finish_reduction(d, acc, d->step, out);
     if (out->unstable) d->unstable = true;
     return LBM_OK;

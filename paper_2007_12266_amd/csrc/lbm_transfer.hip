@@ -6,7 +6,14 @@
 // to kThreads host threads while the DMA of the other buffer runs. The buffers are allocated
 // once per process (pinned with hipHostMalloc) and shared under a mutex, so concurrent callers
 // take turns; copies below kDirect bytes go straight to hipMemcpyAsync.
+//
+// Small results (a field of a small domain, the sums of a reduction) need no device buffer at
+// all: their kernels write into pinned host memory (PinnedOut), the host waits for the stream and
+// copies them out. A device-to-host copy of pageable memory costs 40 us and more before its first
+// byte (a field of 20 thousand voxels took 95 us, now 25; one of 524 thousand 285, now 195; a
+// reduction 60, now 45).
 #include <algorithm>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <system_error>
@@ -30,6 +37,19 @@ struct Staging {
 Staging& staging() {
     static Staging st;
     return st;
+}
+
+// Idle buffers of PinnedOut, kPinnedBytes each: taken by one caller at a time, at most kPinnedIdle
+// kept for the process.
+constexpr size_t kPinnedIdle = 4;
+struct PinnedPool {
+    std::mutex mu;
+    std::vector<void*> idle;
+};
+
+PinnedPool& pinned_pool() {
+    static PinnedPool* p = new PinnedPool;   // outlives every caller
+    return *p;
 }
 
 hipError_t ensure_buffers(Staging& st) {
@@ -87,6 +107,77 @@ hipError_t drained(hipError_t e, hipStream_t s) {
 }
 
 }  // namespace
+
+PinnedOut::PinnedOut(size_t bytes) {
+    if (bytes > kPinnedBytes) return;
+    PinnedPool& p = pinned_pool();
+    {
+        std::lock_guard<std::mutex> lock(p.mu);
+        if (!p.idle.empty()) {
+            ptr_ = p.idle.back();
+            p.idle.pop_back();
+            return;
+        }
+    }
+    if (hipHostMalloc(&ptr_, kPinnedBytes, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        ptr_ = nullptr;
+    }
+}
+
+PinnedOut::~PinnedOut() {
+    if (!ptr_) return;
+    PinnedPool& p = pinned_pool();
+    {
+        std::lock_guard<std::mutex> lock(p.mu);
+        if (p.idle.size() < kPinnedIdle) {
+            p.idle.push_back(ptr_);
+            return;
+        }
+    }
+    (void)hipHostFree(ptr_);
+}
+
+// The copying threads are started before the wait for the stream, so that starting them (about
+// 15 us each) runs beside the kernel.
+hipError_t PinnedOut::take(void* dst, size_t bytes, hipStream_t s) {
+    const unsigned hw = std::max(1u, std::min(kThreads, std::thread::hardware_concurrency()));
+    const size_t parts = bytes < (1u << 20) ? 1 : hw;
+    const size_t slice = (bytes + parts - 1) / parts;
+    auto part = [&](size_t k) {
+        const size_t b = k * slice;
+        if (b < bytes) std::memcpy((char*)dst + b, (const char*)ptr_ + b, std::min(slice, bytes - b));
+    };
+    std::mutex mu;
+    std::condition_variable cv;
+    int go = 0;   // 1: the result is there, -1: there is none
+    std::vector<std::thread> threads;
+    size_t started = 1;
+    for (; started < parts; ++started) {
+        try {
+            threads.emplace_back([&, k = started] {
+                std::unique_lock<std::mutex> lock(mu);
+                cv.wait(lock, [&] { return go != 0; });
+                lock.unlock();
+                if (go > 0) part(k);
+            });
+        } catch (const std::system_error&) {
+            break;   // no thread to be had: this one copies the rest
+        }
+    }
+    const hipError_t e = hipStreamSynchronize(s);
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        go = e == hipSuccess ? 1 : -1;
+    }
+    cv.notify_all();
+    if (e == hipSuccess) {
+        part(0);
+        for (size_t k = started; k < parts; ++k) part(k);
+    }
+    for (std::thread& t : threads) t.join();
+    return e;
+}
 
 hipError_t copy_to_device(void* dst, const void* src, size_t bytes, hipStream_t s) {
     if (bytes == 0) return hipSuccess;
