@@ -221,9 +221,9 @@ __device__ __forceinline__ int last_set(const uint64_t* __restrict__ r, int s, i
 
 // Row pass: out[v] = min(g^2, cap), g = distance along x to the nearest feature bit in the
 // row (wrapping when x is periodic), searched to at most `lim` voxels. Four consecutive voxels
-// per thread (one 16-byte store when nx is a multiple of 4). The words w-1, w, w+1 around them
-// are read together and settle almost every voxel; the full word-by-word search runs only for a
-// side they leave open and whose remainder lies within the limit.
+// per thread (one 16-byte store when nx is a multiple of 4). row_dist: the distance from the
+// words w-1, w, w+1 around a voxel where they settle it; the full word-by-word search runs only
+// for a side they leave open and whose remainder lies within the limit.
 __device__ __forceinline__ int row_dist(const uint64_t* __restrict__ r, int W, int nx, bool per,
                                         int lim, int x, uint64_t cur, uint64_t lo, uint64_t hi) {
     const int w = x >> 6, sh = x & 63;
@@ -291,15 +291,40 @@ __global__ void __launch_bounds__(256) edt_row_kernel(Box b, const uint64_t* __r
     if (x0 >= b.nx || row >= b.ny * b.nz) return;
     const uint64_t* r = bits + (int64_t)row * b.W;
     const bool per = (b.per & 1) != 0;
-    const int w = x0 >> 6;   // the four voxels share this word
-    const uint64_t cur = r[w];
-    const uint64_t lo = w > 0 ? r[w - 1] : 0ull;
-    const uint64_t hi = w + 1 < b.W ? r[w + 1] : 0ull;
+    // The half words at and beside the four voxels (which share one) settle every distance below
+    // 32, in about fifteen instructions without a branch; row_dist with its three words and
+    // searches takes over five times as many, and was what bound this pass (256^3, bytes: 56 us;
+    // now 22). On a periodic row the windows near the ends go on with the first and the last
+    // 32 voxels of the row; a row shorter than 64 leaves its wraps to row_dist.
+    const uint32_t* h = reinterpret_cast<const uint32_t*>(r);
+    const int k = x0 >> 5;
+    const uint64_t cur = h[k], lo = k > 0 ? h[k - 1] : 0u, hi = k + 1 < 2 * b.W ? h[k + 1] : 0u;
+    const uint64_t right = hi << 32 | cur, left = cur << 32 | lo;
+    const bool wrap = per && b.nx >= 64;
+    uint32_t head = 0, last = 0;
+    if (wrap) {
+        const int e = (b.nx - 1) >> 5;
+        head = h[0];
+        last = (uint32_t)(((uint64_t)h[e] << 32 | h[e - 1]) >> (((b.nx - 1) & 31) + 1));
+    }
     int res[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int x = x0 + j;
-        const int d = x < b.nx ? row_dist(r, b.W, b.nx, per, lim, x, cur, lo, hi) : kInf;
+        const int x = x0 + j, sh = x & 31;
+        uint32_t R = (uint32_t)(right >> sh), L = (uint32_t)(left >> (sh + 1));
+        if (wrap) {
+            if (b.nx - x < 32) R |= head << max(0, b.nx - x);
+            if (x < 31) L |= last >> (x + 1);
+        }
+        int d = min(R ? __ffs((int)R) - 1 : 32, L ? __clz((int)L) : 32);
+        const int edge = per && !wrap ? min(x + 1, b.nx - x) : kInf;
+        const bool more = (d == 32 && lim >= 32) || (d > edge && edge <= lim);
+        if (d == 32) d = kInf;
+        if (more && x < b.nx) {
+            const int w = x0 >> 6;
+            d = row_dist(r, b.W, b.nx, per, lim, x, r[w], w > 0 ? r[w - 1] : 0ull,
+                         w + 1 < b.W ? r[w + 1] : 0ull);
+        }
         res[j] = d >= kInf ? cap : min(d * d, cap);
     }
     const int64_t v = (int64_t)row * b.nx + x0;
@@ -317,21 +342,32 @@ __global__ void __launch_bounds__(256) edt_row_kernel(Box b, const uint64_t* __r
     }
 }
 
-// Continues min over d >= d0 of in[base + ((c + d) mod n) stride] + d^2 (offsets outside a
-// non-periodic line are skipped) from `best`, stopping once d^2 reaches best.
+// Continues min over d >= d0 of in[base + ((c + d) mod n) stride] + d^2 from `best`, stopping once
+// d^2 reaches best. Four offsets to a round trip: an offset more than needed, and the place c
+// itself in the stead of one outside the line, give terms that are never below the minimum.
 template <typename T>
 __device__ __forceinline__ int line_min_from(const T* __restrict__ in, int64_t base,
                                              int64_t stride, int c, int n, bool per, int best,
                                              int d0) {
     const int lim = per ? n / 2 : max(c, n - 1 - c);
-    for (int d = d0; d <= lim; ++d) {
-        const int d2 = d * d;
-        if (d2 >= best) break;
-        int a = c + d, e = c - d;
-        if (a >= n) a = per ? a - n : -1;
-        if (e < 0) e = per ? e + n : -1;
-        if (a >= 0) best = min(best, (int)in[base + (int64_t)a * stride] + d2);
-        if (e >= 0) best = min(best, (int)in[base + (int64_t)e * stride] + d2);
+    for (int d = d0; d <= lim; d += 4) {
+        if (d * d >= best) break;
+        int v[8];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            int a = c + d + k, e = c - d - k;
+            if (per) {
+                a = a >= n ? a - n : a;
+                e = e < 0 ? e + n : e;
+            }
+            if (a >= n) a = c;
+            if (e < 0) e = c;
+            v[2 * k] = (int)in[base + (int64_t)a * stride];
+            v[2 * k + 1] = (int)in[base + (int64_t)e * stride];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            best = min(best, min(v[2 * k], v[2 * k + 1]) + (d + k) * (d + k));
     }
     return best;
 }
@@ -422,6 +458,100 @@ __global__ void __launch_bounds__(256) edt_seg_kernel(Box b, int ax, int32_t cap
                 cnt += f ? 1 : 0;
                 if (nw) nw[v] = f ? 1 : 0;
             }
+        }
+    }
+    if (MODE == 1) {
+        for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
+        __shared__ int ws[kPrepThreads / 64];
+        if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = cnt;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int t = 0;
+            for (int i = 0; i < kPrepThreads / 64; ++i) t += ws[i];
+            part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = t;
+        }
+    }
+}
+
+// The line pass for distances held in bytes (cap <= 255) and rows of a multiple of 4: a thread
+// takes four neighbouring lines, a window entry is one 4-byte load, and the minima run on pairs
+// of 16-bit values. With a byte per load and a minimum per value the passes took as long as with
+// int32 (256^3: 43 us each, bound by their loads and instructions); now 23. The lines'
+// threads are 1 << qshift to a row as in the row pass, so a workgroup holds 256 >> qshift
+// segments. MODE 0 and 1 as above. Offsets beyond the window matter only to a cap above
+// (kWin + 1)^2.
+typedef unsigned short Pair16 __attribute__((ext_vector_type(2)));
+
+template <int MODE>
+__global__ void __launch_bounds__(256) edt_seg8_kernel(Box b, int ax, int qshift, int32_t cap,
+                                                       int walls, const uint8_t* __restrict__ in,
+                                                       uint8_t* __restrict__ out,
+                                                       const uint8_t* __restrict__ pore,
+                                                       uint8_t* __restrict__ nw,
+                                                       int* __restrict__ part) {
+    constexpr unsigned short kFar = 0x7fff;   // no value: above every cap, also with d^2 added
+    const int x0 = 4 * (((int)blockIdx.y << qshift) + ((int)threadIdx.x & ((1 << qshift) - 1)));
+    const int n = ax == 1 ? b.ny : b.nz, other = ax == 1 ? b.nz : b.ny;
+    const int nseg = (n + kSeg - 1) / kSeg;
+    const int at = (int)blockIdx.x * (256 >> qshift) + ((int)threadIdx.x >> qshift);
+    const int o = at / nseg, c0 = (at - o * nseg) * kSeg;
+    const int64_t stride = ax == 1 ? (int64_t)b.nx : (int64_t)b.nx * b.ny;
+    const int64_t base = ax == 1 ? (int64_t)o * b.ny * b.nx + x0 : (int64_t)o * b.nx + x0;
+    const bool per = ((b.per >> ax) & 1) != 0;
+    int cnt = 0;
+    if (x0 < b.nx && at < other * nseg) {
+        uint32_t raw[kSeg + 2 * kWin];
+#pragma unroll
+        for (int j = 0; j < kSeg + 2 * kWin; ++j) {
+            int c = c0 - kWin + j;
+            if (c < 0 || c >= n) c = per ? ((c % n) + n) % n : c0;
+            raw[j] = *reinterpret_cast<const uint32_t*>(in + base + (int64_t)c * stride);
+        }
+        Pair16 even[kSeg + 2 * kWin], odd[kSeg + 2 * kWin];   // lines x0, x0 + 2 and x0 + 1, x0 + 3
+#pragma unroll
+        for (int j = 0; j < kSeg + 2 * kWin; ++j) {
+            const int c = c0 - kWin + j;
+            const bool none = !per && (c < 0 || c >= n);
+            even[j] = none ? (Pair16)kFar : __builtin_bit_cast(Pair16, raw[j] & 0x00ff00ffu);
+            odd[j] = none ? (Pair16)kFar : __builtin_bit_cast(Pair16, (raw[j] >> 8) & 0x00ff00ffu);
+        }
+#pragma unroll
+        for (int i = 0; i < kSeg; ++i) {
+            const int c = c0 + i;
+            if (c >= n) break;
+            Pair16 e = even[i + kWin], f = odd[i + kWin];
+#pragma unroll
+            for (int d = 1; d <= kWin; ++d) {
+                e = __builtin_elementwise_min(
+                    e, __builtin_elementwise_min(even[i + kWin + d], even[i + kWin - d]) +
+                           (Pair16)(unsigned short)(d * d));
+                f = __builtin_elementwise_min(
+                    f, __builtin_elementwise_min(odd[i + kWin + d], odd[i + kWin - d]) +
+                           (Pair16)(unsigned short)(d * d));
+            }
+            int best[4] = {e.x, f.x, e.y, f.y};
+            const int64_t v = base + (int64_t)c * stride;
+            uint32_t p = 0x01010101u;
+            if (MODE == 1) p = *reinterpret_cast<const uint32_t*>(pore + v);
+            uint32_t word = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (walls)
+                    best[j] = wall_min(b, walls, x0 + j, ax == 1 ? c : o, ax == 1 ? o : c, best[j]);
+                if (cap > (kWin + 1) * (kWin + 1) && best[j] > (kWin + 1) * (kWin + 1))
+                    best[j] = line_min_from(in, base + j, stride, c, n, per, best[j], kWin + 1);
+                if (MODE == 0) {
+                    word |= (uint32_t)min(best[j], cap) << (8 * j);
+                } else {
+                    const uint32_t near = ((p >> (8 * j)) & 0xffu) && best[j] < cap ? 1u : 0u;
+                    cnt += (int)near;
+                    word |= near << (8 * j);
+                }
+            }
+            if (MODE == 0)
+                *reinterpret_cast<uint32_t*>(out + v) = word;
+            else if (nw)
+                *reinterpret_cast<uint32_t*>(nw + v) = word;
         }
     }
     if (MODE == 1) {
@@ -709,26 +839,34 @@ __global__ void __launch_bounds__(256) mixing_kernel(Box b, const int32_t* __res
 // ---------------------------------------------------------------------------------------------
 // Host side
 
-// Device buffers of one call; the destructor waits for the stream, then frees them.
+// Device buffers of one call, carved from one allocation (each separate one of an image's size
+// costs its own mapping); the destructor waits for the stream, then frees it.
 struct Scratch {
     hipStream_t s;
-    std::vector<void*> ptrs;
-    hipError_t err = hipSuccess;   // first failed allocation
+    char* base = nullptr;
+    struct Want { void** ptr; size_t offset; };
+    std::vector<Want> wants;
+    size_t total = 0;
+    hipError_t err = hipSuccess;
     explicit Scratch(hipStream_t st) : s(st) {}
     ~Scratch() {
-        if (!ptrs.empty()) (void)hipStreamSynchronize(s);
-        for (void* p : ptrs) (void)hipFree(p);
+        if (!base) return;
+        (void)hipStreamSynchronize(s);
+        (void)hipFree(base);
     }
+    // *ptr will hold `count` elements, 256-byte aligned, once get() has succeeded.
     template <typename T>
-    T* get(int64_t count) {
+    void want(T** ptr, int64_t count) {
+        wants.push_back(Want{(void**)ptr, total});
+        total += (std::max<size_t>(1, sizeof(T) * (size_t)count) + 255) / 256 * 256;
+    }
+    bool get() {
         void* p = nullptr;
-        const hipError_t e = hipMalloc(&p, std::max<size_t>(256, sizeof(T) * (size_t)count));
-        if (e != hipSuccess) {
-            if (err == hipSuccess) err = e;
-            return nullptr;
-        }
-        ptrs.push_back(p);
-        return (T*)p;
+        err = hipMalloc(&p, total);
+        if (err != hipSuccess) return false;
+        base = (char*)p;
+        for (const Want& w : wants) *w.ptr = base + w.offset;
+        return true;
     }
     // Status for a failed allocation: out of memory, or no usable device.
     lbm_status failed(const char* what) const {
@@ -817,6 +955,40 @@ int64_t seg_blocks(const Box& b, int ax) {
     return (int64_t)g.x * g.y;
 }
 
+// Grid of the line passes on bytes.
+dim3 seg8_grid(const Box& b, int ax) {
+    const int n = ax == 1 ? b.ny : b.nz, other = ax == 1 ? b.nz : b.ny;
+    const int64_t segs = (int64_t)other * ((n + kSeg - 1) / kSeg);
+    const int s = row_shift(b), per = 256 >> s, span = 4 << s;
+    return dim3((unsigned)((segs + per - 1) / per), (unsigned)((b.nx + span - 1) / span));
+}
+
+// One line pass in MODE 0 or 1 (see edt_seg_kernel); *blocks receives the workgroups of the
+// launch, one partial count each in MODE 1.
+template <int MODE, typename T>
+lbm_status line_pass(const Box& b, int ax, int32_t cap, int walls, const T* in, T* out,
+                     const uint8_t* pore, uint8_t* nw, int* part, int64_t* blocks,
+                     hipStream_t s) {
+    if constexpr (sizeof(T) == 1) {
+        if ((b.nx & 3) == 0) {
+            const dim3 g = seg8_grid(b, ax);
+            hipLaunchKernelGGL((edt_seg8_kernel<MODE>), g, dim3(256), 0, s, b, ax, row_shift(b),
+                               cap, walls, in, out, pore, nw, part);
+            HIP_TRY(hipGetLastError());
+            if (blocks) *blocks = (int64_t)g.x * g.y;
+            return LBM_OK;
+        }
+    }
+    // MODE 1: kPrepThreads per workgroup (its block sum needs them all): whenever b.tpb is
+    // smaller, there is one chunk per row, which 256 threads cover as well.
+    const dim3 g = seg_grid(b, ax);
+    hipLaunchKernelGGL((edt_seg_kernel<MODE, T>), g, dim3(MODE == 1 ? kPrepThreads : b.tpb), 0, s,
+                       b, ax, cap, walls, in, out, pore, nw, part);
+    HIP_TRY(hipGetLastError());
+    if (blocks) *blocks = (int64_t)g.x * g.y;
+    return LBM_OK;
+}
+
 // Row and y passes of the transform of the feature bits: leaves the y-pass result in mid
 // (row-pass scratch in tmp). T holds values up to cap (int32_t, or uint8_t for caps <= 255).
 template <typename T>
@@ -825,10 +997,7 @@ lbm_status edt_xy(const Box& b, const uint64_t* bits, int32_t cap, T* tmp, T* mi
     hipLaunchKernelGGL(edt_row_kernel<T>, row_grid(b), dim3(256), 0, s, b, bits,
                        row_shift(b), row_limit(b, cap), cap, tmp);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL((edt_seg_kernel<0, T>), seg_grid(b, 1), dim3(b.tpb), 0, s, b, 1, cap, 0,
-                       (const T*)tmp, mid, nullptr, nullptr, nullptr);
-    HIP_TRY(hipGetLastError());
-    return LBM_OK;
+    return line_pass<0, T>(b, 1, cap, 0, tmp, mid, nullptr, nullptr, nullptr, nullptr, s);
 }
 
 // Full squared distance transform of the feature bits into out (tmp: a second buffer of nvox);
@@ -838,6 +1007,8 @@ template <typename T, int MODE = 0>
 lbm_status edt(const Box& b, const uint64_t* bits, int32_t cap, int walls, T* tmp, T* out,
                hipStream_t s) {
     if (lbm_status st = edt_xy<T>(b, bits, cap, out, tmp, s)) return st;
+    if constexpr (MODE == 0)
+        return line_pass<0, T>(b, 2, cap, walls, tmp, out, nullptr, nullptr, nullptr, nullptr, s);
     hipLaunchKernelGGL((edt_seg_kernel<MODE, T>), seg_grid(b, 2), dim3(b.tpb), 0, s, b, 2, cap,
                        walls, (const T*)tmp, out, nullptr, nullptr, nullptr);
     HIP_TRY(hipGetLastError());
@@ -877,16 +1048,18 @@ lbm_status connect_to_inlet(const Box& b, const DrainBuffers& db, hipStream_t s)
     return LBM_OK;
 }
 
-// The passes of a drainage dilation: per-workgroup counts of the pore voxels closer than
-// sqrt(k) to a feature bit, and their mask when nw_dev is not null.
+// The passes of a drainage dilation: the number of pore voxels closer than sqrt(k) to a feature
+// bit, into db.part2, and their mask when nw_dev is not null.
 template <typename T>
 lbm_status dilate_count(const Box& b, const uint64_t* feat, int32_t k, T* tmp, T* mid,
                         const DrainBuffers& db, uint8_t* nw_dev, hipStream_t s) {
     if (lbm_status st = edt_xy<T>(b, feat, k, tmp, mid, s)) return st;
-    // kPrepThreads per workgroup (its block sum needs them all): whenever b.tpb is smaller,
-    // there is one chunk per row, which 256 threads cover as well.
-    hipLaunchKernelGGL((edt_seg_kernel<1, T>), seg_grid(b, 2), dim3(kPrepThreads), 0, s, b, 2, k,
-                       0, (const T*)mid, (T*)nullptr, (const uint8_t*)db.pore, nw_dev, db.part);
+    int64_t blocks = 0;
+    if (lbm_status st = line_pass<1, T>(b, 2, k, 0, mid, nullptr, db.pore, nw_dev, db.part,
+                                        &blocks, s))
+        return st;
+    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(kSumThreads), 0, s, (const int*)db.part, blocks,
+                       db.part2);
     HIP_TRY(hipGetLastError());
     return LBM_OK;
 }
@@ -909,9 +1082,6 @@ lbm_status drain_eval(const Box& b, const DrainBuffers& db, int32_t k, bool inle
     } else if (lbm_status st = dilate_count(b, feat, k, db.tmp, db.mid, db, nw_dev, s)) {
         return st;
     }
-    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(kSumThreads), 0, s, (const int*)db.part,
-                       seg_blocks(b, 2), db.part2);
-    HIP_TRY(hipGetLastError());
     long long h = 0;
     HIP_TRY(hipMemcpyAsync(&h, db.part2, sizeof h, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -978,11 +1148,14 @@ lbm_status lbm_prep_distance(int32_t nx, int32_t ny, int32_t nz, const int32_t p
     if (wall_axes < 0 || wall_axes > 7) return fail(LBM_ERR_ARG, "wall_axes must lie in [0, 7]");
     hipStream_t s = (hipStream_t)hip_stream;
     Scratch sc(s);
-    uint8_t* f = sc.get<uint8_t>(b.nvox);
-    uint64_t* bits = sc.get<uint64_t>(b.nwords);
-    int32_t* tmp = sc.get<int32_t>(b.nvox);
-    int32_t* out = sc.get<int32_t>(b.nvox);
-    if (!f || !bits || !tmp || !out) return sc.failed("the transform");
+    uint8_t* f;
+    uint64_t* bits;
+    int32_t *tmp, *out;
+    sc.want(&f, b.nvox);
+    sc.want(&bits, b.nwords);
+    sc.want(&tmp, b.nvox);
+    sc.want(&out, b.nvox);
+    if (!sc.get()) return sc.failed("the transform");
     HIP_TRY(copy_to_device(f, feature, (size_t)b.nvox, s));
     if (lbm_status st = pack(b, FeatureNonzero{f}, Wide8Nonzero{f}, bits, s)) return st;
     if (lbm_status st = edt<int32_t, 2>(b, bits, kInf, wall_axes, tmp, out, s)) return st;
@@ -1040,23 +1213,21 @@ lbm_status lbm_prep_drain(int32_t nx, int32_t ny, int32_t nz, const int32_t peri
     hipStream_t s = (hipStream_t)hip_stream;
     Scratch sc(s);
     DrainBuffers db{};
-    db.pore = sc.get<uint8_t>(b.nvox);
-    db.d2 = sc.get<int32_t>(b.nvox);
-    db.tmp = sc.get<int32_t>(b.nvox);
-    db.mid = sc.get<int32_t>(b.nvox);
-    db.centre = sc.get<uint64_t>(b.nwords);
-    db.part = sc.get<int>(seg_blocks(b, 2));
-    db.part2 = sc.get<long long>(2);
-    db.pairs = sc.get<long long>(2 * ((b.nvox + 8 * kPrepThreads - 1) / (8 * kPrepThreads)));
-    uint8_t* nw_dev = sc.get<uint8_t>(b.nvox);
-    if (inlet) {
-        db.label = sc.get<int32_t>(b.nvox);
-        db.flag = sc.get<uint8_t>(b.nvox);
-        db.reach = sc.get<uint64_t>(b.nwords);
-    }
-    if (!db.pore || !db.d2 || !db.tmp || !db.mid || !db.centre || !db.part || !db.part2 ||
-        !db.pairs || !nw_dev || (inlet && (!db.label || !db.flag || !db.reach)))
-        return sc.failed("the drainage");
+    uint8_t* nw_dev;
+    sc.want(&db.pore, b.nvox);
+    sc.want(&db.d2, b.nvox);
+    sc.want(&db.tmp, b.nvox);
+    sc.want(&db.mid, b.nvox);
+    sc.want(&db.centre, b.nwords);
+    sc.want(&db.part, seg_blocks(b, 2));   // no line pass on bytes has more workgroups
+    sc.want(&db.part2, 2);
+    sc.want(&db.pairs, 2 * ((b.nvox + 8 * kPrepThreads - 1) / (8 * kPrepThreads)));
+    sc.want(&nw_dev, b.nvox);
+    if (inlet) sc.want(&db.reach, b.nwords);
+    if (!sc.get()) return sc.failed("the drainage");
+    // The labelling is done before the passes of a radius begin: it uses their buffers.
+    db.label = db.mid;
+    db.flag = (uint8_t*)db.tmp;
     HIP_TRY(copy_to_device(db.pore, pore, (size_t)b.nvox, s));
 
     // D^2: distance to the solid and to the wall planes of the non-periodic faces.
@@ -1119,15 +1290,18 @@ lbm_status lbm_prep_relabel(int32_t nx, int32_t ny, int32_t nz, const int32_t pe
     const int32_t cap = within + 1;
     hipStream_t s = (hipStream_t)hip_stream;
     Scratch sc(s);
-    int32_t* lab = sc.get<int32_t>(b.nvox);
-    int32_t* res = sc.get<int32_t>(b.nvox);
-    int8_t* kind = sc.get<int8_t>(n_labels);
-    uint8_t* m = sc.get<uint8_t>(b.nvox);
-    uint64_t* bits = sc.get<uint64_t>(b.nwords);
-    int32_t* e2 = sc.get<int32_t>(b.nvox);
-    int32_t* tmp = sc.get<int32_t>(b.nvox);
-    if (!lab || !res || !kind || !m || !bits || !e2 || !tmp)
-        return sc.failed("the relabelling");
+    int32_t *lab, *res, *e2, *tmp;
+    int8_t* kind;
+    uint8_t* m;
+    uint64_t* bits;
+    sc.want(&lab, b.nvox);
+    sc.want(&res, b.nvox);
+    sc.want(&kind, n_labels);
+    sc.want(&m, b.nvox);
+    sc.want(&bits, b.nwords);
+    sc.want(&e2, b.nvox);
+    sc.want(&tmp, b.nvox);
+    if (!sc.get()) return sc.failed("the relabelling");
     HIP_TRY(copy_to_device(lab, labels, sizeof(int32_t) * (size_t)b.nvox, s));
     HIP_TRY(hipMemcpyAsync(kind, label_kind, (size_t)n_labels, hipMemcpyHostToDevice, s));
     HIP_TRY(copy_to_device(m, nw, (size_t)b.nvox, s));
@@ -1153,10 +1327,12 @@ lbm_status lbm_prep_mixing_layer(int32_t nx, int32_t ny, int32_t nz, const int32
         return fail(LBM_ERR_ARG, "pore_label must be a pore label of the table");
     hipStream_t s = (hipStream_t)hip_stream;
     Scratch sc(s);
-    int32_t* lab = sc.get<int32_t>(b.nvox);
-    int32_t* res = sc.get<int32_t>(b.nvox);
-    int8_t* kind = sc.get<int8_t>(n_labels);
-    if (!lab || !res || !kind) return sc.failed("the mixing layer");
+    int32_t *lab, *res;
+    int8_t* kind;
+    sc.want(&lab, b.nvox);
+    sc.want(&res, b.nvox);
+    sc.want(&kind, n_labels);
+    if (!sc.get()) return sc.failed("the mixing layer");
     HIP_TRY(copy_to_device(lab, labels, sizeof(int32_t) * (size_t)b.nvox, s));
     HIP_TRY(hipMemcpyAsync(kind, label_kind, (size_t)n_labels, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(mixing_kernel, vox_grid(b), dim3(b.tpb), 0, s, b, (const int32_t*)lab,

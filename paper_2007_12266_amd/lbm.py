@@ -655,7 +655,7 @@ def prep_drain(pore: np.ndarray, periodic=(False, False, False), target_sw: floa
     _check(load_library().lbm_prep_drain(nx, ny, nz, _periodic3(periodic), _ptr(m),
                                          ctypes.byref(dp), _ptr(nw), ctypes.byref(r),
                                          _stream_handle(stream)))
-    return nw.astype(bool), {"k": r.radius_sq, "kmax": r.max_radius_sq,
+    return nw.view(np.bool_), {"k": r.radius_sq, "kmax": r.max_radius_sq,
                              "evaluations": r.evaluations, "n_pore": r.n_pore,
                              "n_nw": r.n_nw, "sw": r.sw}
 
