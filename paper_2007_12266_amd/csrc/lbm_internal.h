@@ -78,9 +78,27 @@ constexpr int kMaxXcdRun = 64;
 constexpr int64_t kStepGraphChunk = 64;
 
 // Device memory above which a new domain launches its step kernels with streaming
-// (non-temporal) accesses: twice the MI355X Infinity Cache (256 MB), so that a domain the cache
-// holds from one step to the next keeps that reuse.
-constexpr int64_t kStreamBytes = int64_t(512) << 20;
+// (non-temporal) accesses and the collide runs that go with them: one and a half times the
+// MI355X Infinity Cache (256 MB) in FP64 and FP32-mixed, twice in FP32-dev, so that a domain the
+// cache holds from one step to the next keeps that reuse. us a step without / with, porosity 0.2:
+// FP64 302 MB 105.1 / 105.2, 370 MB 134.3 / 134.5, 447 MB 166.3 / 153.2, 541 MB 206 / 186;
+// FP32-mixed 336 MB 118.6 / 118.2, 406 MB 148.1 / 142.5, 500 MB 186 / 169; FP32-dev 329 MB
+// 111.7 / 115.1, 405 MB 136.0 / 137.6.
+constexpr int64_t stream_bytes(int32_t precision) {
+    return int64_t(precision == LBM_FP32_DEV ? 512 : 384) << 20;
+}
+
+// Fewest pore voxels of a domain whose kernels get the per-CU workgroup limits of a large one
+// without its streaming. us a step without / with limits: FP64 0.79 M voxels 68.5 / 68.5, 0.98 M
+// 105.1 / 101.9, 1.2 M 134.3 / 131.3; FP32-mixed 0.79 M 51.1 / 50.3, 1.2 M 89.1 / 87.0; FP32-dev
+// 0.98 M 51.8 / 51.4. Below, they gain nothing in FP64 (0.6 M: 54.1 / 54.1) and cost a 524
+// thousand voxel domain in FP32-dev a percent.
+constexpr int64_t kLimitVoxels = int64_t(3) << 18;
+
+// Most pore voxels of a domain that steps in workgroups of 64 by default: with 256, fewer than
+// half of the CUs have one. us a step with 256 / 64: FP64 19,660 voxels 8.06 / 7.06, 27,648 8.29 /
+// 7.48; FP32-dev 19,660 7.29 / 6.47; but 65,536 voxels in FP32-mixed 8.29 / 8.73.
+constexpr int64_t kSmallVoxels = int64_t(1) << 15;
 
 // Most pore voxels of a domain whose collide kernel issues all its loads first (EARLY in
 // lbm_kernels.hip): up to about four waves per SIMD. Above, other waves hide the round trip that

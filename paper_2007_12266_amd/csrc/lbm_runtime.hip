@@ -499,16 +499,19 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
         d->release();
         return fail(LBM_ERR_DEVICE, "internal: device footprint estimate out of date");
     }
-    // Domains well beyond the Infinity Cache: streaming accesses, workgroup limits and collide
-    // run lengths, the autotuner's choice at 512^3 for each precision (phase / collide wg: FP64
-    // 5 / 2, FP32-mixed 5 / 3, FP32-dev none / 3; collide runs of 4 tiles on even steps, 32 on
-    // odd ones in all three). Smaller domains keep the plain defaults.
-    const bool large = d->device_bytes > kStreamBytes;
+    // Defaults by size (measured where the constants are defined). Domains well beyond the
+    // Infinity Cache: streaming accesses and collide runs of 4 tiles on even steps, 32 on odd
+    // ones. Workgroup limits: the autotuner's choice at 512^3 for each precision (phase / collide:
+    // FP64 5 / 2, FP32-mixed 5 / 3, FP32-dev none / 3).
     lbm_tuning t0 = d->tune;
+    if (p.block_size == 0 && pre.n_pore <= kSmallVoxels) t0.phase_block = t0.collide_block = 64;
+    const bool large = d->device_bytes > stream_bytes(p.precision);
     t0.phase_stream = t0.collide_stream = large ? 1 : 0;
-    if (large) {
+    if (large || pre.n_pore > kLimitVoxels) {
         t0.phase_wg = p.precision == LBM_FP32_DEV ? 0 : 5;
         t0.collide_wg = p.precision == LBM_FP64 ? 2 : 3;
+    }
+    if (large) {
         t0.collide_run[0] = 4;
         t0.collide_run[1] = 32;
     }
