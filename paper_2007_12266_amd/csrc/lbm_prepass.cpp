@@ -367,25 +367,30 @@ std::string build_compact_lookup(Prepass& pre) {
     c.n16.assign((size_t)ld * 4, 0u);
     c.wide.assign((size_t)ld * 4, 0u);
     c.wave.assign((size_t)nw * kCompactWaveInts, 0);
-    auto target = [&](int q, int64_t i) -> int64_t { return pre.nbr[(size_t)(q - 1) * ld + i]; };
+    // Row of direction q = k + 1 in wave w.
+    auto row_of = [&](int k, int64_t w) { return &pre.nbr[(size_t)k * ld + 64 * (size_t)w]; };
     // Bases per wave and direction; waves whose codes all fit 8 bits become byte waves, those
     // that do not fit 16 bits exceptions.
+    const int32_t n32 = (int32_t)n;
     std::vector<uint8_t> is_ex((size_t)nw, 0);
     parallel_for(nw, [&](int64_t w0, int64_t w1) {
         for (int64_t w = w0; w < w1; ++w) {
             int32_t* rec = &c.wave[(size_t)w * kCompactWaveInts];
-            int64_t spread = 0;
-            for (int q = 1; q < 19 && spread <= 0xffff; ++q) {
-                int64_t plo = INT64_MAX, phi = -1, tlo = INT64_MAX, thi = -1;
-                for (int64_t i = 64 * w; i < 64 * w + 64; ++i) {
-                    const int64_t t = target(q, i);
-                    if (t < n) { plo = std::min(plo, t); phi = std::max(phi, t); }
-                    else { tlo = std::min(tlo, t); thi = std::max(thi, t); }
+            int32_t spread = 0;
+            for (int k = 0; k < 18; ++k) {
+                const int32_t* t = row_of(k, w);
+                int32_t plo = INT32_MAX, phi = -1, tlo = INT32_MAX, thi = -1;
+                for (int l = 0; l < 64; ++l) {
+                    const bool tail = t[l] >= n32;
+                    plo = std::min(plo, tail ? INT32_MAX : t[l]);
+                    phi = std::max(phi, tail ? -1 : t[l]);
+                    tlo = std::min(tlo, tail ? t[l] : INT32_MAX);
+                    thi = std::max(thi, tail ? t[l] : -1);
                 }
                 if (phi >= 0) spread = std::max(spread, phi - plo);
                 if (thi >= 0) spread = std::max(spread, thi - tlo);
-                rec[q - 1] = phi >= 0 ? (int32_t)plo : 0;
-                rec[18 + q - 1] = thi >= 0 ? (int32_t)tlo : (int32_t)n;
+                rec[k] = phi >= 0 ? plo : 0;
+                rec[18 + k] = thi >= 0 ? tlo : n32;
             }
             is_ex[(size_t)w] = spread > 0xffff ? 1 : 0;
             rec[kCompactKind] = spread <= 0xff ? 1 : 0;
@@ -399,79 +404,87 @@ std::string build_compact_lookup(Prepass& pre) {
         rec[kCompactExRow] = is_ex[(size_t)w] ? (int32_t)c.n_ex++ : -1;
     }
     c.ex.assign((size_t)c.n_ex * 18 * 64, 0);
-    parallel_for(nw, [&](int64_t w0, int64_t w1) {
-        for (int64_t w = w0; w < w1; ++w) {
-            const int32_t* rec = &c.wave[(size_t)w * kCompactWaveInts];
-            const int32_t row = rec[kCompactExRow];
-            for (int64_t i = 64 * w; i < 64 * w + 64; ++i) {
-                uint32_t mask = 0;
-                uint16_t code[19] = {0};
-                for (int q = 1; q < 19; ++q) {
-                    const int64_t t = target(q, i);
-                    if (row >= 0) {
-                        c.ex[((size_t)row * 18 + (q - 1)) * 64 + (size_t)(i & 63)] = (int32_t)t;
-                        continue;
-                    }
-                    const bool tail = t >= n;
-                    if (tail) mask |= 1u << q;
-                    code[q] = (uint16_t)(t - (tail ? rec[18 + q - 1] : rec[q - 1]));
-                }
-                if (row >= 0) continue;
-                uint32_t* n8 = &c.n8[(size_t)i * 2];
-                uint32_t* n16 = &c.n16[(size_t)i * 4];
-                uint32_t* wide = &c.wide[(size_t)i * 4];
-                if (rec[kCompactKind]) {
-                    for (int q = 1; q < 7; ++q)
-                        n8[(q - 1) / 4] |= (uint32_t)code[q] << (8 * ((q - 1) % 4));
-                    n8[1] |= ((mask >> 1) & 0x3fu) << 16;
-                    for (int q = 7; q < 19; ++q)
-                        n16[(q - 7) / 4] |= (uint32_t)code[q] << (8 * ((q - 7) % 4));
-                    n16[3] = mask >> 7;
-                } else {
-                    auto pair = [&](int q) { return code[q] | (uint32_t)code[q + 1] << 16; };
-                    wide[0] = mask;
-                    for (int k = 0; k < 3; ++k) wide[1 + k] = pair(1 + 2 * k);
-                    for (int k = 0; k < 4; ++k) n16[k] = pair(7 + 2 * k);
-                    for (int k = 0; k < 2; ++k) n8[k] = pair(15 + 2 * k);
-                }
-            }
-        }
-    }, ld * 18);
-    // Decode every entry as the kernels do and compare it with the table.
+    // Encode a wave, then decode every entry as the kernels do and compare it with the table.
     std::vector<int64_t> bad((size_t)nw, -1);
     parallel_for(nw, [&](int64_t w0, int64_t w1) {
         for (int64_t w = w0; w < w1; ++w) {
             const int32_t* rec = &c.wave[(size_t)w * kCompactWaveInts];
-            for (int64_t i = 64 * w; i < 64 * w + 64 && bad[(size_t)w] < 0; ++i)
-                for (int q = 1; q < 19; ++q) {
-                    int64_t got;
-                    if (rec[kCompactExRow] >= 0) {
-                        got = c.ex[((size_t)rec[kCompactExRow] * 18 + (q - 1)) * 64 +
-                                   (size_t)(i & 63)];
-                    } else {
-                        const uint32_t* n8 = &c.n8[(size_t)i * 2];
-                        const uint32_t* n16 = &c.n16[(size_t)i * 4];
-                        const uint32_t* wide = &c.wide[(size_t)i * 4];
-                        uint32_t code;
-                        bool tail;
-                        if (rec[kCompactKind]) {
-                            const uint32_t word = q < 7 ? n8[(q - 1) / 4] : n16[(q - 7) / 4];
-                            code = (word >> (8 * ((q < 7 ? q - 1 : q - 7) % 4))) & 0xffu;
-                            tail = (q < 7 ? n8[1] >> (16 + q - 1) : n16[3] >> (q - 7)) & 1u;
-                        } else {
-                            const uint32_t word = q < 7    ? wide[1 + (q - 1) / 2]
-                                                  : q < 15 ? n16[(q - 7) / 2]
-                                                           : n8[(q - 15) / 2];
-                            code = (q & 1) ? (word & 0xffffu) : (word >> 16);
-                            tail = (wide[0] >> q) & 1u;
-                        }
-                        got = (int64_t)(tail ? rec[18 + q - 1] : rec[q - 1]) + code;
-                    }
-                    if (got != target(q, i)) {
-                        bad[(size_t)w] = i;
-                        break;
+            const int32_t row = rec[kCompactExRow];
+            if (row >= 0) {
+                for (int k = 0; k < 18; ++k)
+                    std::copy_n(row_of(k, w), 64, &c.ex[((size_t)row * 18 + k) * 64]);
+                for (int k = 0; k < 18; ++k)
+                    if (!std::equal(row_of(k, w), row_of(k, w) + 64,
+                                    &c.ex[((size_t)row * 18 + k) * 64]))
+                        bad[(size_t)w] = 64 * w;
+                continue;
+            }
+            uint32_t code[18][64], mask[64] = {0};   // mask: bit q
+            for (int k = 0; k < 18; ++k) {
+                const int32_t* t = row_of(k, w);
+                const int32_t pb = rec[k], tb = rec[18 + k];
+                for (int l = 0; l < 64; ++l) {
+                    const bool tail = t[l] >= n32;
+                    code[k][l] = (uint32_t)(t[l] - (tail ? tb : pb));
+                    mask[l] |= (tail ? 1u : 0u) << (k + 1);
+                }
+            }
+            uint32_t* n8 = &c.n8[(size_t)w * 128];
+            uint32_t* n16 = &c.n16[(size_t)w * 256];
+            uint32_t* wide = &c.wide[(size_t)w * 256];
+            uint32_t differ = 0;
+            if (rec[kCompactKind]) {
+                auto four = [&](int k, int l) {
+                    return code[k][l] | code[k + 1][l] << 8 | code[k + 2][l] << 16 |
+                           code[k + 3][l] << 24;
+                };
+                for (int l = 0; l < 64; ++l) {
+                    n8[2 * l] = four(0, l);
+                    n8[2 * l + 1] =
+                        code[4][l] | code[5][l] << 8 | ((mask[l] >> 1) & 0x3fu) << 16;
+                    n16[4 * l] = four(6, l);
+                    n16[4 * l + 1] = four(10, l);
+                    n16[4 * l + 2] = four(14, l);
+                    n16[4 * l + 3] = mask[l] >> 7;
+                }
+                for (int k = 0; k < 18; ++k) {
+                    const int32_t* t = row_of(k, w);
+                    const int32_t pb = rec[k], tb = rec[18 + k];
+                    const int j = k < 6 ? k : k - 6;          // place among its record's codes
+                    const uint32_t* word = k < 6 ? n8 + j / 4 : n16 + j / 4;
+                    const int step = k < 6 ? 2 : 4, sh = 8 * (j % 4);
+                    for (int l = 0; l < 64; ++l) {
+                        const uint32_t tail = (k < 6 ? n8[2 * l + 1] >> (16 + k)
+                                                     : n16[4 * l + 3] >> (k - 6)) & 1u;
+                        const int32_t got =
+                            (tail ? tb : pb) + (int32_t)((word[step * l] >> sh) & 0xffu);
+                        differ |= (uint32_t)(got ^ t[l]);
                     }
                 }
+            } else {
+                auto pair = [&](int k, int l) { return code[k][l] | code[k + 1][l] << 16; };
+                for (int l = 0; l < 64; ++l) {
+                    wide[4 * l] = mask[l];
+                    for (int k = 0; k < 3; ++k) wide[4 * l + 1 + k] = pair(2 * k, l);
+                    for (int k = 0; k < 4; ++k) n16[4 * l + k] = pair(6 + 2 * k, l);
+                    for (int k = 0; k < 2; ++k) n8[2 * l + k] = pair(14 + 2 * k, l);
+                }
+                for (int k = 0; k < 18; ++k) {
+                    const int32_t* t = row_of(k, w);
+                    const int32_t pb = rec[k], tb = rec[18 + k];
+                    const uint32_t* word = k < 6    ? wide + 1 + k / 2
+                                           : k < 14 ? n16 + (k - 6) / 2
+                                                    : n8 + (k - 14) / 2;
+                    const int step = k < 14 ? 4 : 2, sh = k & 1 ? 16 : 0;
+                    for (int l = 0; l < 64; ++l) {
+                        const uint32_t tail = (wide[4 * l] >> (k + 1)) & 1u;
+                        const int32_t got =
+                            (tail ? tb : pb) + (int32_t)((word[step * l] >> sh) & 0xffffu);
+                        differ |= (uint32_t)(got ^ t[l]);
+                    }
+                }
+            }
+            if (differ) bad[(size_t)w] = 64 * w;
         }
     }, ld * 18);
     for (int64_t w = 0; w < nw; ++w)
