@@ -54,12 +54,12 @@ struct lbm_domain {
     int64_t device_bytes = 0;
 
     void* f = nullptr;
-    void* M = nullptr;        // [4][ld][2] D3Q7 moment slot pairs
+    void* M = nullptr;        // [3][ld][2] D3Q7 moment slot pairs
     int32_t* fresh = nullptr; // device flags: the state is the initial one (StepArgs)
     int8_t* face = nullptr;   // [N] pressure-face flags (bc_z == 1 only)
     int32_t one = 1;          // host source of fresh-flag uploads (outlives the async copy)
-    void* phi = nullptr;      // [N + n_tail] storage type
-    void* ntot = nullptr;     // [N] storage type
+    void* phi[2] = {nullptr, nullptr};   // [N + n_tail] storage type, of the last step of each
+    void* ntot[2] = {nullptr, nullptr};  // [N] storage type             parity (StepArgs)
     double* stage = nullptr;  // [ld] doubles: initial phase upload and field read-back
     int32_t* nbr = nullptr;        // [9][ld][2] (table mode)
     uint32_t* coord = nullptr;     // [ld] packed coordinates (rank mode)
@@ -116,14 +116,17 @@ struct lbm_domain {
 
     // Kernel arguments for a launch with `blk` threads per workgroup and schedule `sched`
     // (XCD runs of `run` tiles for schedules 2 and 3).
-    lbm::StepArgs args(int blk = 256, int sched = 1, int run = lbm::kXcdRun) const {
+    // For a step of parity `odd` (or a reader of the state that such a step comes next to).
+    lbm::StepArgs args(bool odd, int blk = 256, int sched = 1, int run = lbm::kXcdRun) const {
         lbm::StepArgs a{};
         a.N = (int32_t)pre.n_pore;
         a.block = blk;
         a.ld = pre.ld;
         a.nbr = nbr;
-        a.phi = phi;
-        a.ntot = ntot;
+        a.phi = phi[odd ? 1 : 0];
+        a.ntot = ntot[odd ? 1 : 0];
+        a.phi_prev = phi[odd ? 0 : 1];
+        a.ntot_prev = ntot[odd ? 0 : 1];
         a.f = f;
         a.M = M;
         a.fresh = fresh;
@@ -188,6 +191,23 @@ struct lbm_domain {
         device_bytes = 0;
         if (own_stream && stream) (void)hipStreamDestroy(stream);
         stream = nullptr;
+    }
+
+    // The device arrays that make up the state at its present step, and their sizes.
+    struct StateArray { void* ptr; size_t bytes; };
+    std::vector<StateArray> state_arrays() const {
+        const int prev = (step & 1) ? 0 : 1;
+        const size_t ld = (size_t)pre.ld;
+        return {{f, f_bytes() * 19 * ld},
+                {M, m_bytes() * 6 * ld},
+                {fresh, sizeof(int32_t)},
+                {phi[prev], m_bytes() * (size_t)(pre.n_pore + pre.n_tail)},
+                {ntot[prev], m_bytes() * ld}};
+    }
+    size_t state_bytes() const {
+        size_t n = 0;
+        for (const StateArray& a : state_arrays()) n += a.bytes;
+        return n;
     }
 
     // Bytes per stored D3Q19 population, and per stored moment-slot, phi or N value.

@@ -28,13 +28,17 @@ struct StepArgs {
     int32_t block;      // threads per workgroup of the step kernels (voxels per tile)
     int64_t ld;         // leading dimension of population arrays
     const int32_t* nbr; // [9][ld][2]: neighbours along (q, q + 1) for q = 1, 3, ..., 17
-    void* phi;          // [N + n_tail] in the storage type; the tail holds phi_s
-    void* ntot;         // [N] in the storage type
+    void* phi;          // [N + n_tail] in the storage type: this step's phase indicator, written by
+    void* ntot;         //   the phase kernel; the tail holds phi_s. [N]: this step's N = N_a + N_b
+    void* phi_prev;     // the same of the step before, from which the phase kernel has the
+    void* ntot_prev;    //   densities that the components left with (see `fresh` for a state that
+                        //   no step has made). The pairs of buffers alternate by step parity.
     void* f;            // [19][ld] populations (storage type per precision)
-    void* M;            // [4][ld][2] D3Q7 moment slot pairs: (N_a, N_b), (u_x, G_x), (u_y, G_y),
-                        // (u_z, G_z)
-    int32_t* fresh;     // device flags: [0] 1 while the state is the initial one; [1] its value at
-                        // the step's phase kernel, for the collide kernel that clears [0]
+    void* M;            // [3][ld][2] D3Q7 moment slot pairs: (u_x, G_x), (u_y, G_y), (u_z, G_z)
+    int32_t* fresh;     // device flags: [0] 0 while phi_prev and ntot_prev are a step's; else they
+                        // hold N_a and N_b themselves: 1 in a state at rest (initial, or after a
+                        // morphological step), 2 in a state that was loaded; [1] whether [0] was 1
+                        // at the step's phase kernel, for the collide kernel that clears [0]
     const int8_t* face; // per pore voxel: 0, 1 (inlet face), 2 (outlet face); null without faces
     double nu_a, nu_b;  // kinematic viscosities
     double alpha, beta;
@@ -115,6 +119,7 @@ struct BatchArgs {
     const int32_t* tile_first;  // first tile of each slot
     const int32_t* ntiles;      // number of tiles in use (device scalar)
     int32_t xcd;                // 1: XCD-aware tile order (grid a multiple of 8 * 16)
+    int32_t odd;                // parity of the step (doms holds the arguments of even steps)
 };
 
 // Kernel launchers (lbm_kernels.hip). `odd` is the parity of the step being taken.
@@ -152,6 +157,11 @@ hipError_t launch_reduce_batched(const BatchArgs& b, int prec, bool odd, int nsl
                                  double* partials, double* out, hipStream_t s);
 hipError_t launch_field(const StepArgs& a, bool odd, int field, double* out, int block,
                         hipStream_t s);
+// The densities (N_a, N_b) that the components of voxels i0 .. i0 + n - 1 left with, as pairs in
+// the storage type (saved states hold them), and back (flag 2 of `fresh`).
+hipError_t launch_densities_out(const StepArgs& a, int32_t i0, int32_t n, void* pairs, hipStream_t s);
+hipError_t launch_densities_in(const StepArgs& a, int32_t i0, int32_t n, const void* pairs,
+                               hipStream_t s);
 
 // Host <-> device copies of large caller buffers (lbm_transfer.hip): staged through pinned
 // memory by several host threads while the previous chunk's DMA runs. Ordered on stream s after

@@ -20,16 +20,19 @@
 //    buffer.
 //  * The D3Q7 component populations are streamed in moment form. The mass LBEs relax fully: the
 //    seven outgoing A*_q of a voxel are fixed by N_a, u and G = beta (N_a N_b / N) n (and B*_q by
-//    N_b, u, -G). The collide kernel therefore stores those 8 numbers per voxel, coalesced, in
-//    the voxel's own slots, and the phase kernel rebuilds each incoming A_q(x) = A*_q(x - xi_q)
-//    from the upstream neighbour's 8 numbers with the same arithmetic the populations would have
-//    been formed with (at a wall, from the voxel's own opposite outgoing population). This moves
-//    16 values per voxel and step instead of 28, and turns the odd step's 14 scattered A/B writes
-//    into 8 coalesced ones. On the first step of a fresh state the slots hold the initial
-//    densities themselves (a per-domain device flag, cleared by the first collide). The 8 slots
-//    are stored as 4 rows of value pairs, (N_a, N_b), (u_x, G_x), (u_y, G_y), (u_z, G_z), so
-//    that what a neighbour contributes along one axis is two wide loads; storing each voxel's
-//    8 values contiguously was measured slower on both kernels.
+//    N_b, u, -G). The collide kernel therefore stores u and G per voxel, coalesced, in the voxel's
+//    own slots; N_a and N_b follow from the phi and N that the phase kernel stored for it, which
+//    are kept for one more step in buffers that alternate by step parity. The phase kernel
+//    rebuilds each incoming A_q(x) = A*_q(x - xi_q) from the upstream neighbour's 8 numbers with
+//    the same arithmetic the populations would have been formed with (at a wall, from the voxel's
+//    own opposite outgoing population). This moves 14 values per voxel and step instead of 28, and
+//    turns the odd step's 14 scattered A/B writes into 6 coalesced ones. (With N_a and N_b stored
+//    again by the collide kernel, 512^3 FP64 took 1.9% longer, 320^3 FP32-mixed 2.4%; the phase
+//    kernel's loads, two where a pair was one, cost 8% of its own time.) A state that no step has
+//    made, initial or loaded, holds the densities themselves (a per-domain device flag, cleared by
+//    the first collide). The slots are 3 rows of value pairs, (u_x, G_x), (u_y, G_y), (u_z, G_z),
+//    so that what a neighbour contributes along one axis is one wide load; storing each voxel's
+//    values contiguously was measured slower on both kernels.
 //  * Neighbours come from an int32 table with opposite directions interleaved (one 8-byte load
 //    per pair), or from the voxel's packed coordinate and per-64-voxel row records (the rank
 //    lookup: less memory, a dependent load more, measured slower). The step kernels are
@@ -123,6 +126,7 @@ __device__ __forceinline__ int xcd_run_tile(int b, int C, uint32_t m) {
 template <int NB>
 __device__ __forceinline__ void load_args(const StepArgs& a) {
     asm volatile("" ::"s"(a.N), "s"(a.ld), "s"(a.f), "s"(a.M), "s"(a.phi), "s"(a.ntot),
+                 "s"(a.phi_prev), "s"(a.ntot_prev),
                  "s"(a.fresh), "s"(a.face), "s"(a.block), "s"(a.xcd_run), "s"(a.xcd_mul),
                  "s"(a.tile_first), "s"(a.tile_sign));
     if (NB == NB_COMPACT)
@@ -140,9 +144,8 @@ __device__ __forceinline__ int tile_start(const StepArgs& a) {
     return (a.tile_first + a.tile_sign * t) * a.block;
 }
 
-// The D3Q7 moment slots of a voxel are stored as four pairs, one row of 2*ld values per pair:
-// (N_a, N_b), (u_x, G_x), (u_y, G_y), (u_z, G_z). What a neighbour contributes along one axis is
-// two pairs, each a single 16-byte (FP64) or 8-byte (FP32) access.
+// The D3Q7 moment slots of a voxel are stored as three pairs, one row of 2*ld values per pair:
+// (u_x, G_x), (u_y, G_y), (u_z, G_z), each a single 16-byte (FP64) or 8-byte (FP32) access.
 template <typename S> struct PairOf;
 template <> struct PairOf<double> { using T = double2; };
 template <> struct PairOf<float> { using T = float2; };
@@ -394,10 +397,11 @@ __global__ void __launch_bounds__(256) init_kernel(StepArgs a, const double* __r
     const double na = 0.5 * (1.0 + phi0[i]), nbv = 0.5 * (1.0 - phi0[i]);
 #pragma unroll
     for (int q = 0; q < 19; ++q) f[(size_t)q * a.ld + i] = (F)(P::kDev ? 0.0 : tw(q));
-    // A fresh state: the component slots hold the densities (the fresh flag is set by the host).
-    store_pair<S>(M, a.ld, 0, i, (S)na, (S)nbv);
+    // A fresh state: the densities themselves (the fresh flag is set by the host).
+    ((S*)a.phi_prev)[i] = (S)na;
+    ((S*)a.ntot_prev)[i] = (S)nbv;
 #pragma unroll
-    for (int k = 1; k < 4; ++k) store_pair<S>(M, a.ld, k, i, (S)0, (S)0);
+    for (int k = 0; k < 3; ++k) store_pair<S>(M, a.ld, k, i, (S)0, (S)0);
 }
 
 // a b + c rounded once. The step's arithmetic states each fused operation: left to the compiler,
@@ -424,14 +428,12 @@ __device__ __forceinline__ void ab_out(R na, R nb, R uc, R gc, R sgn, R& ao, R& 
     bo = (R)(1.0 / 9.0) * fused(nb, eu, -en);
 }
 
-// The same for direction q (1..6) of voxel y, read from its moment slots.
-template <typename R, typename S>
-__device__ __forceinline__ void out_ab(const S* __restrict__ M, int64_t ld, int y, int q, R& ao,
-                                       R& bo) {
-    const int c = (q - 1) >> 1;                 // axis of q
-    const auto n = load_pair<S>(M, ld, 0, y);
-    const auto g = load_pair<S>(M, ld, 1 + c, y);
-    ab_out<R>((R)n.x, (R)n.y, (R)g.x, (R)g.y, (q & 1) ? (R)1 : (R)-1, ao, bo);  // +x, +y, +z odd
+// Densities that a voxel's components left with, from the phi and N of the step that sent them
+// (the arithmetic with which the collide kernel formed them), or as they are (raw).
+template <typename R>
+__device__ __forceinline__ void sent(R p, R n, bool raw, R& na, R& nb) {
+    na = raw ? p : (R)0.5 * n * ((R)1 + p);
+    nb = raw ? n : (R)0.5 * n * ((R)1 - p);
 }
 
 // Component densities N_a, N_b of pore voxel i in the current state: the sum of the incoming
@@ -446,14 +448,16 @@ __device__ __forceinline__ void out_ab(const S* __restrict__ M, int64_t ld, int 
 // target beyond the face), else -1; the rank lookup has no such entries.
 // FACE: the domain may have pressure faces.
 template <int PREC, int NB = NB_DYN, bool STREAM = false, bool FACE = true>
-__device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, double& na,
+__device__ __forceinline__ void densities(const StepArgs& a, int i, int fresh, double& na,
                                           double& nbv, int& ghost) {
     using P = Prec<PREC>;
     using S = typename P::S;
     using R = typename P::R;
     const S* M = (const S*)a.M;
+    const S* __restrict__ pp = (const S*)a.phi_prev;
+    const S* __restrict__ np = (const S*)a.ntot_prev;
     R ain[7], bin[7];
-    const auto own = load_pair<S>(M, a.ld, 0, i);
+    const S own_p = pp[i], own_n = np[i];
     const Pos pos = pos_of<NB, true, STREAM>(a, i);
     int up[7];
 #pragma unroll
@@ -465,18 +469,20 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, 
     for (int q = 1; q < 7; ++q) {
         const int c = (q - 1) >> 1;
         const int y = up[q] < a.N ? up[q] : i;
-        const auto n = load_pair<S>(M, a.ld, 0, y);
-        const auto g = load_pair<S>(M, a.ld, 1 + c, y);
-        sna[q] = (R)n.x;
-        snb[q] = (R)n.y;
+        sna[q] = (R)pp[y];
+        snb[q] = (R)np[y];
+        const auto g = load_pair<S>(M, a.ld, c, y);
         suc[q] = (R)g.x;
         sgc[q] = (R)g.y;
     }
 #pragma unroll
     for (int q = 1; q < 7; ++q) {
         const R sq = (q & 1) ? (R)1 : (R)-1;
+        sent<R>(sna[q], snb[q], fresh != 0, sna[q], snb[q]);
         ab_out<R>(sna[q], snb[q], suc[q], sgc[q], up[q] < a.N ? sq : -sq, ain[q], bin[q]);
     }
+    R own_a, own_b;
+    sent<R>((R)own_p, (R)own_n, fresh != 0, own_a, own_b);
     if (sizeof(S) == sizeof(float)) {
         // The rest population is what the six moving ones leave of N (the rounded float weights
         // would otherwise add 1.5e-8 of mass per step); sums in double, see below.
@@ -484,17 +490,18 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, 
 #pragma unroll
         for (int q = 1; q < 7; ++q) {
             R ao, bo;
-            out_ab<R>(M, a.ld, i, q, ao, bo);
+            const auto g = load_pair<S>(M, a.ld, (q - 1) >> 1, i);
+            ab_out<R>(own_a, own_b, (R)g.x, (R)g.y, (q & 1) ? (R)1 : (R)-1, ao, bo);
             sa += (double)ao;
             sb += (double)bo;
         }
         ain[0] = (R)0;
         bin[0] = (R)0;
-        na = (double)own.x - sa;
-        nbv = (double)own.y - sb;
+        na = (double)own_a - sa;
+        nbv = (double)own_b - sb;
     } else {
-        ain[0] = (R)(1.0 / 3.0) * (R)own.x;
-        bin[0] = (R)(1.0 / 3.0) * (R)own.y;
+        ain[0] = (R)(1.0 / 3.0) * own_a;
+        bin[0] = (R)(1.0 / 3.0) * own_b;
         na = 0.0;
         nbv = 0.0;
     }
@@ -512,10 +519,10 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, 
         na = fc == 1 ? 1.0 : 0.0;
         nbv = 1.0 - na;
     }
-    if (fresh) {
+    if (fresh == 1) {
         // The initial populations are w_q N at rest; summing them (rather than taking N) keeps
         // the initial phase bitwise equal to a population-based evaluation.
-        const R n0 = (R)own.x, n1 = (R)own.y;
+        const R n0 = own_a, n1 = own_b;
 #pragma unroll
         for (int q = 0; q < 7; ++q) {
             const R w = q == 0 ? (R)(1.0 / 3.0) : (R)(1.0 / 9.0);
@@ -537,7 +544,7 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, bool fresh, 
 // D3Q7 populations; phi = (N_a - N_b)/(N_a + N_b); N = N_a + N_b.
 // ------------------------------------------------------------------------------------------
 template <int PREC, int NB, bool STREAM, bool FACE>
-__device__ __forceinline__ void phase_voxel(const StepArgs& a, int i, bool fresh) {
+__device__ __forceinline__ void phase_voxel(const StepArgs& a, int i, int fresh) {
     using S = typename Prec<PREC>::S;
     double na, nbv;
     int ghost;
@@ -548,7 +555,7 @@ __device__ __forceinline__ void phase_voxel(const StepArgs& a, int i, bool fresh
     store_once<STREAM>((S)nt, (S*)a.ntot + i);
     if (FACE) {
         if (ghost >= 0) ((S*)a.phi)[ghost] = phi;
-        if (i == 0) a.fresh[1] = fresh ? 1 : 0;
+        if (i == 0) a.fresh[1] = fresh == 1 ? 1 : 0;
     }
 }
 
@@ -556,7 +563,7 @@ template <int PREC, int NB, bool STREAM, bool FACE>
 __global__ void __launch_bounds__(256) phase_kernel(StepArgs a) {
     load_args<NB>(a);
     const int i = tile_start(a) + (int)threadIdx.x;
-    if (i < a.N) phase_voxel<PREC, NB, STREAM, FACE>(a, i, *a.fresh != 0);
+    if (i < a.N) phase_voxel<PREC, NB, STREAM, FACE>(a, i, *a.fresh);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -714,10 +721,9 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
     const R seg = (R)a.beta * na * nbv / nt;
     S* M = (S*)a.M;
     const size_t ld = (size_t)a.ld;
-    store_pair<S, STREAM>(M, ld, 0, i, (S)na, (S)nbv);
-    store_pair<S, STREAM>(M, ld, 1, i, (S)ux, (S)(seg * nx));
-    store_pair<S, STREAM>(M, ld, 2, i, (S)uy, (S)(seg * ny));
-    store_pair<S, STREAM>(M, ld, 3, i, (S)uz, (S)(seg * nz));
+    store_pair<S, STREAM>(M, ld, 0, i, (S)ux, (S)(seg * nx));
+    store_pair<S, STREAM>(M, ld, 1, i, (S)uy, (S)(seg * ny));
+    store_pair<S, STREAM>(M, ld, 2, i, (S)uz, (S)(seg * nz));
 
     const R nu = fused((R)0.5 * ((R)1 + phi_i), (R)a.nu_a, (R)0.5 * ((R)1 - phi_i) * (R)a.nu_b);
     const R sp = (R)1 / fused((R)3, nu, (R)0.5);
@@ -807,6 +813,17 @@ __device__ __forceinline__ T load_const(const T* p) {
     return out;
 }
 
+// Arguments of slot d at the step's parity.
+__device__ __forceinline__ StepArgs batch_args(const BatchArgs& b, int d) {
+    StepArgs a = load_const(b.doms + d);
+    void *phi = a.phi, *ntot = a.ntot;
+    a.phi = b.odd ? a.phi_prev : phi;
+    a.ntot = b.odd ? a.ntot_prev : ntot;
+    a.phi_prev = b.odd ? phi : a.phi_prev;
+    a.ntot_prev = b.odd ? ntot : a.ntot_prev;
+    return a;
+}
+
 template <int PREC, int NB, bool FACE>
 __global__ void __launch_bounds__(256) phase_batched(BatchArgs b) {
     const int nt = *as_const(b.ntiles);
@@ -814,9 +831,9 @@ __global__ void __launch_bounds__(256) phase_batched(BatchArgs b) {
                             : (int)blockIdx.x;
     for (int t = first; t < nt; t += gridDim.x) {
         const int d = as_const(b.tile_dom)[t];
-        const StepArgs a = load_const(b.doms + d);
+        const StepArgs a = batch_args(b, d);
         const int i = (t - as_const(b.tile_first)[d]) * blockDim.x + threadIdx.x;
-        if (i < a.N) phase_voxel<PREC, NB, false, FACE>(a, i, *a.fresh != 0);
+        if (i < a.N) phase_voxel<PREC, NB, false, FACE>(a, i, *a.fresh);
     }
 }
 
@@ -827,7 +844,7 @@ __global__ void __launch_bounds__(256) collide_batched(BatchArgs b) {
                             : (int)blockIdx.x;
     for (int t = first; t < nt; t += gridDim.x) {
         const int d = as_const(b.tile_dom)[t];
-        const StepArgs a = load_const(b.doms + d);
+        const StepArgs a = batch_args(b, d);
         const int i = (t - as_const(b.tile_first)[d]) * blockDim.x + threadIdx.x;
         if (i < a.N) collide_voxel<PREC, ODD, NB, false, false, FACE>(a, i);
     }
@@ -864,7 +881,7 @@ template <int PREC, bool ODD>
 __device__ __forceinline__ void voxel_state(const StepArgs& a, int i, double& na, double& nbv,
                                             double& rho, double& jx, double& jy, double& jz) {
     int ghost;
-    densities<PREC>(a, i, *a.fresh != 0, na, nbv, ghost);   // callers' waves are aligned
+    densities<PREC>(a, i, *a.fresh, na, nbv, ghost);   // callers' waves are aligned
     voxel_flow<PREC, ODD>(a, i, rho, jx, jy, jz);
 }
 
@@ -948,7 +965,7 @@ template <int PREC, bool ODD>
 __global__ void __launch_bounds__(kRedThreads) reduce_batched(BatchArgs b,
                                                               double* __restrict__ partials) {
     const int slot = blockIdx.x / kRedBlocks;
-    const StepArgs a = b.doms[slot];
+    const StepArgs a = batch_args(b, slot);
     reduce_block<PREC, ODD>(a, blockIdx.x % kRedBlocks,
                             partials + (size_t)slot * kRedBlocks * kNRed);
 }
@@ -996,7 +1013,7 @@ __global__ void __launch_bounds__(256) field_kernel(StepArgs a, int field,
     if (field <= LBM_FIELD_PHI) {   // N_a, N_b, phi: the components alone (a third of the bytes)
         double na, nbv;
         int ghost;
-        densities<PREC>(a, i, *a.fresh != 0, na, nbv, ghost);
+        densities<PREC>(a, i, *a.fresh, na, nbv, ghost);
         out[i] = field == LBM_FIELD_NA   ? na
                  : field == LBM_FIELD_NB ? nbv
                                          : (na - nbv) / (na + nbv);
@@ -1320,6 +1337,52 @@ hipError_t launch_field(const StepArgs& a, bool odd, int field, double* out, int
                         hipStream_t s) {
     (void)block;
     LBM_DISPATCH(field_kernel, dim3(grid_for(a, 256)), dim3(256), a, field, out);
+    return hipGetLastError();
+}
+
+// ---- Densities of a saved state
+namespace {
+template <typename S>
+__global__ void __launch_bounds__(256) densities_out_kernel(StepArgs a, int i0, int n,
+                                                            S* __restrict__ pairs) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    S na, nb;
+    sent<S>(((const S*)a.phi_prev)[i0 + k], ((const S*)a.ntot_prev)[i0 + k], *a.fresh != 0, na, nb);
+    store_pair<S>(pairs, 0, 0, k, na, nb);
+}
+
+template <typename S>
+__global__ void __launch_bounds__(256) densities_in_kernel(StepArgs a, int i0, int n,
+                                                           const S* __restrict__ pairs) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    ((S*)a.phi_prev)[i0 + k] = pairs[2 * (size_t)k];
+    ((S*)a.ntot_prev)[i0 + k] = pairs[2 * (size_t)k + 1];
+}
+}  // namespace
+
+hipError_t launch_densities_out(const StepArgs& a, int32_t i0, int32_t n, void* pairs,
+                                hipStream_t s) {
+    const dim3 grid((n + 255) / 256);
+    if (a.prec == LBM_FP32_DEV)
+        hipLaunchKernelGGL(densities_out_kernel<float>, grid, dim3(256), 0, s, a, i0, n,
+                           (float*)pairs);
+    else
+        hipLaunchKernelGGL(densities_out_kernel<double>, grid, dim3(256), 0, s, a, i0, n,
+                           (double*)pairs);
+    return hipGetLastError();
+}
+
+hipError_t launch_densities_in(const StepArgs& a, int32_t i0, int32_t n, const void* pairs,
+                               hipStream_t s) {
+    const dim3 grid((n + 255) / 256);
+    if (a.prec == LBM_FP32_DEV)
+        hipLaunchKernelGGL(densities_in_kernel<float>, grid, dim3(256), 0, s, a, i0, n,
+                           (const float*)pairs);
+    else
+        hipLaunchKernelGGL(densities_in_kernel<double>, grid, dim3(256), 0, s, a, i0, n,
+                           (const double*)pairs);
     return hipGetLastError();
 }
 

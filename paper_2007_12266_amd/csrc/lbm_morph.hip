@@ -118,8 +118,8 @@ __global__ void __launch_bounds__(kMorphThreads) phase_count_kernel(
 
 template <typename S>
 __global__ void __launch_bounds__(256) morph_apply_kernel(
-    int n, int64_t ld, S* __restrict__ M, const S* __restrict__ phi, const S* __restrict__ ntot,
-    const double* __restrict__ dist, const int8_t* __restrict__ far, double beta, double delta) {
+    int n, int64_t ld, S* __restrict__ M, S* __restrict__ na_out, S* __restrict__ nb_out,
+    const S* __restrict__ phi, const S* __restrict__ ntot, const double* __restrict__ dist, const int8_t* __restrict__ far, double beta, double delta) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     double p = (double)phi[i];
@@ -130,10 +130,10 @@ __global__ void __launch_bounds__(256) morph_apply_kernel(
     const double nt = (double)ntot[i];
     const double na = nt * (1.0 + p) * 0.5;
     const double nb = nt * (1.0 - p) * 0.5;
-    // Moment slot pairs (N_a, N_b), (u_x, G_x), (u_y, G_y), (u_z, G_z): the rest state.
-    M[2 * i] = (S)na;
-    M[2 * i + 1] = (S)nb;
-    for (int k = 1; k < 4; ++k) {
+    // The rest state: the densities, and moment slot pairs (u_x, G_x), (u_y, G_y), (u_z, G_z) of 0.
+    na_out[i] = (S)na;
+    nb_out[i] = (S)nb;
+    for (int k = 0; k < 3; ++k) {
         M[2 * ((size_t)k * ld + i)] = (S)0;
         M[2 * ((size_t)k * ld + i) + 1] = (S)0;
     }
@@ -167,12 +167,12 @@ lbm_status ensure_buffers(lbm_domain* d) {
     return LBM_OK;
 }
 
-// Current phase indicator and N of every pore voxel into d->phi and d->ntot (the step's own
-// first kernel, run on the current state; it changes no state).
+// Current phase indicator and N of every pore voxel into d->phi and d->ntot of the next step's
+// parity (the step's own first kernel, run on the current state; it changes no state).
 lbm_status current_phase(lbm_domain* d) {
     const lbm_tuning& tu = d->tune;
     const bool odd = (d->step & 1) != 0;
-    const StepArgs a = d->args(tu.phase_block, tu.phase_schedule, tu.phase_run[odd ? 1 : 0]);
+    const StepArgs a = d->args(odd, tu.phase_block, tu.phase_schedule, tu.phase_run[odd ? 1 : 0]);
     HIP_TRY(launch_phase(a, odd, tu.phase_block, tu.phase_stream != 0, d->lds[0],
                          d->stream));
     return LBM_OK;
@@ -200,10 +200,10 @@ lbm_status count_phase(lbm_domain* d, int64_t* out) {
     const int n = (int)d->pre.n_pore;
     if (d->p.precision == LBM_FP32_DEV)
         hipLaunchKernelGGL(phase_count_kernel<float>, dim3(kMorphBlocks), dim3(kMorphThreads), 0,
-                           d->stream, n, (const float*)d->phi, d->morph_count);
+                           d->stream, n, (const float*)d->phi[d->step & 1], d->morph_count);
     else
         hipLaunchKernelGGL(phase_count_kernel<double>, dim3(kMorphBlocks), dim3(kMorphThreads),
-                           0, d->stream, n, (const double*)d->phi, d->morph_count);
+                           0, d->stream, n, (const double*)d->phi[d->step & 1], d->morph_count);
     HIP_TRY(hipGetLastError());
     return sum_counts(d, out);
 }
@@ -214,7 +214,7 @@ lbm_status distance_map(lbm_domain* d, const lbm_morph_params& mp) {
     const int64_t nvox = (int64_t)d->p.nx * d->p.ny * d->p.nz;
     HIP_TRY(hipMemsetAsync(d->morph_label, 0, (size_t)nvox, d->stream));
     hipLaunchKernelGGL(morph_label_kernel<S>, dim3(blocks_for(n)), dim3(256), 0, d->stream, n,
-                       d->morph_vox, (const S*)d->phi, d->morph_label);
+                       d->morph_vox, (const S*)d->phi[d->step & 1], d->morph_label);
     HIP_TRY(hipGetLastError());
     const int periodic =
         (d->p.periodic[0] ? 1 : 0) | (d->p.periodic[1] ? 2 : 0) | (d->p.periodic[2] ? 4 : 0);
@@ -228,7 +228,7 @@ lbm_status distance_map(lbm_domain* d, const lbm_morph_params& mp) {
                                        d->morph_to_a, d->morph_to_b, d->stream))
         return st;
     hipLaunchKernelGGL(morph_distance_kernel<S>, dim3(blocks_for(n)), dim3(256), 0, d->stream,
-                       n, d->morph_vox, (const S*)d->phi, (const uint8_t*)d->morph_to_a,
+                       n, d->morph_vox, (const S*)d->phi[d->step & 1], (const uint8_t*)d->morph_to_a,
                        (const uint8_t*)d->morph_to_b, d->p.beta, std::tanh(mp.band * d->p.beta),
                        mp.radius, d->morph_dist, d->morph_far);
     HIP_TRY(hipGetLastError());
@@ -275,15 +275,17 @@ lbm_status lbm_morph(lbm_domain* d, const lbm_morph_params* mp, lbm_morph_result
     }
     if (lbm_status s = count_inside(d, delta, &r.volume_after)) return s;
     const int n = (int)d->pre.n_pore;
+    const StepArgs a = d->args((d->step & 1) != 0);
     if (fp32)
         hipLaunchKernelGGL(morph_apply_kernel<float>, dim3(blocks_for(n)), dim3(256), 0,
-                           d->stream, n, d->pre.ld, (float*)d->M, (const float*)d->phi,
-                           (const float*)d->ntot, d->morph_dist, d->morph_far, d->p.beta, delta);
+                           d->stream, n, d->pre.ld, (float*)d->M, (float*)a.phi_prev,
+                           (float*)a.ntot_prev, (const float*)a.phi, (const float*)a.ntot,
+                           d->morph_dist, d->morph_far, d->p.beta, delta);
     else
         hipLaunchKernelGGL(morph_apply_kernel<double>, dim3(blocks_for(n)), dim3(256), 0,
-                           d->stream, n, d->pre.ld, (double*)d->M, (const double*)d->phi,
-                           (const double*)d->ntot, d->morph_dist, d->morph_far, d->p.beta,
-                           delta);
+                           d->stream, n, d->pre.ld, (double*)d->M, (double*)a.phi_prev,
+                           (double*)a.ntot_prev, (const double*)a.phi, (const double*)a.ntot,
+                           d->morph_dist, d->morph_far, d->p.beta, delta);
     HIP_TRY(hipGetLastError());
     d->one = 1;   // the D3Q7 populations restart at rest from the new densities
     HIP_TRY(hipMemcpyAsync(d->fresh, &d->one, sizeof(int32_t), hipMemcpyHostToDevice,

@@ -76,11 +76,11 @@ struct lbm_pool {
     size_t group_cap = 0;             // groups the two device arrays hold
 
     BatchArgs batch() const {
-        return BatchArgs{d_doms, d_tile_dom, d_tile_first, d_ntiles, order};
+        return BatchArgs{d_doms, d_tile_dom, d_tile_first, d_ntiles, order, 0};
     }
     BatchArgs group_batch(size_t g) const {
         return BatchArgs{d_doms, d_tile_dom + groups[g].first,
-                         d_group_first + g * (size_t)max_slots, d_group_ntiles + g, order};
+                         d_group_first + g * (size_t)max_slots, d_group_ntiles + g, order, 0};
     }
     // Workgroups of the batched launch: the XCD-aware order needs whole runs on every XCD.
     int32_t launch_grid() const {
@@ -188,7 +188,7 @@ lbm_status upload_tables(lbm_pool* p) {
         lbm_domain* d = p->slots[s];
         p->h_tile_first[s] = (int32_t)p->h_tile_dom.size();
         if (!d) continue;
-        p->h_doms[s] = d->args(kPoolBlock, 1);
+        p->h_doms[s] = d->args(false, kPoolBlock, 1);
         const int64_t nt = (d->pre.n_pore + kPoolBlock - 1) / kPoolBlock;
         p->h_tile_dom.insert(p->h_tile_dom.end(), (size_t)nt, s);
     }
@@ -246,18 +246,19 @@ lbm_status launch_face_work(lbm_pool* p, const std::vector<int32_t>& members, bo
     for (int32_t s : members) {
         lbm_domain* d = p->slots[s];
         if (d && d->p.bc_z == 1)
-            if (lbm_status st = launch_faces(d, d->args(), odd, settle, p->stream)) return st;
+            if (lbm_status st = launch_faces(d, d->args(odd), odd, settle, p->stream)) return st;
     }
     return LBM_OK;
 }
 
 // n steps of the members in `members` over the tiles that b covers.
-lbm_status launch_steps_of(lbm_pool* p, const BatchArgs& b, const std::vector<int32_t>& members,
+lbm_status launch_steps_of(lbm_pool* p, BatchArgs b, const std::vector<int32_t>& members,
                            int64_t first_step, int64_t n) {
     bool face = false;
     for (int32_t s : members) face = face || (p->slots[s] && p->slots[s]->p.bc_z == 1);
     for (int64_t k = 0; k < n; ++k) {
         const bool odd = ((first_step + k) & 1) != 0;
+        b.odd = odd ? 1 : 0;
         HIP_TRY(launch_phase_batched(b, p->precision, p->lookup, face, p->launch_grid(),
                                      kPoolBlock, p->stream));
         HIP_TRY(launch_collide_batched(b, p->precision, odd, p->lookup, face, p->launch_grid(),
@@ -478,8 +479,10 @@ lbm_status lbm_pool_reduce_all(lbm_pool* p, lbm_reduction* out, int32_t max_coun
     if (n > 0) {
         const size_t bytes = sizeof(double) * kNRed * n;
         PinnedOut sums(bytes);
+        BatchArgs b = p->batch();
+        b.odd = (p->step & 1) ? 1 : 0;
         const hipError_t e =
-            launch_reduce_batched(p->batch(), p->precision, (p->step & 1) != 0, n, p->d_partials,
+            launch_reduce_batched(b, p->precision, (p->step & 1) != 0, n, p->d_partials,
                                   sums.ptr() ? (double*)sums.ptr() : p->d_red, p->stream);
         if (e != hipSuccess) (void)hipStreamSynchronize(p->stream);
         HIP_TRY(e);
@@ -555,21 +558,18 @@ lbm_status lbm_pool_autotune(lbm_pool* p, int32_t trial_steps, int32_t* grid) {
     lbm_status st = LBM_OK;
     for (lbm_domain* d : p->slots) {
         if (!d) continue;
-        const size_t fb = d->f_bytes(), eb = d->m_bytes(), ld = (size_t)d->pre.ld;
-        Snap sn{d, nullptr, (fb * 19 + eb * 8) * ld + sizeof(int32_t)};
+        Snap sn{d, nullptr, d->state_bytes()};
         if (p->dmalloc(&sn.buf, sn.bytes) != hipSuccess) {
             st = fail(LBM_ERR_OOM, "no device memory for the autotuner's snapshot");
             break;
         }
         snaps.push_back(sn);
         size_t off = 0;
-        void* arr[3] = {d->f, d->M, d->fresh};
-        const size_t sizes[3] = {fb * 19 * ld, eb * 8 * ld, sizeof(int32_t)};
-        for (int k = 0; k < 3 && st == LBM_OK; ++k) {
-            if (hipMemcpyAsync((char*)sn.buf + off, arr[k], sizes[k], hipMemcpyDeviceToDevice,
-                               p->stream) != hipSuccess)
+        for (const lbm_domain::StateArray& arr : d->state_arrays()) {
+            if (st == LBM_OK && hipMemcpyAsync((char*)sn.buf + off, arr.ptr, arr.bytes,
+                                               hipMemcpyDeviceToDevice, p->stream) != hipSuccess)
                 st = fail(LBM_ERR_DEVICE, "snapshot copy failed");
-            off += sizes[k];
+            off += arr.bytes;
         }
     }
     const int64_t step0 = p->step;
@@ -640,18 +640,15 @@ lbm_status lbm_pool_autotune(lbm_pool* p, int32_t trial_steps, int32_t* grid) {
     // Restore states; the trial steps came in even numbers, so parities are unchanged.
     for (size_t k = 0; k < snaps.size(); ++k) {
         lbm_domain* d = snaps[k].d;
-        const size_t fb = d->f_bytes(), eb = d->m_bytes(), ld = (size_t)d->pre.ld;
         size_t off = 0;
-        void* arr[3] = {d->f, d->M, d->fresh};
-        const size_t sizes[3] = {fb * 19 * ld, eb * 8 * ld, sizeof(int32_t)};
-        for (int a = 0; a < 3; ++a) {
-            if (hipMemcpyAsync(arr[a], (char*)snaps[k].buf + off, sizes[a],
+        d->step = dstep0[k];
+        for (const lbm_domain::StateArray& arr : d->state_arrays()) {
+            if (hipMemcpyAsync(arr.ptr, (char*)snaps[k].buf + off, arr.bytes,
                                hipMemcpyDeviceToDevice, p->stream) != hipSuccess &&
                 st == LBM_OK)
                 st = fail(LBM_ERR_DEVICE, "restore copy failed");
-            off += sizes[a];
+            off += arr.bytes;
         }
-        d->step = dstep0[k];
     }
     p->step = step0;
     if (hipStreamSynchronize(p->stream) != hipSuccess && st == LBM_OK)

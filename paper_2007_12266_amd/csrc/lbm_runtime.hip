@@ -44,8 +44,8 @@ struct StateHeader {
 namespace {
 
 lbm_status record_reduction(lbm_domain* d, double* out) {
-    const StepArgs a = d->args();
-    HIP_TRY(launch_reduce(a, (d->step & 1) != 0, d->red_partials, out, d->stream));
+    const bool odd = (d->step & 1) != 0;
+    HIP_TRY(launch_reduce(d->args(odd), odd, d->red_partials, out, d->stream));
     return LBM_OK;
 }
 
@@ -94,8 +94,8 @@ template <typename Mark>
 lbm_status launch_step(lbm_domain* d, bool odd, bool settle, Mark mark) {
     const lbm_tuning& tu = d->tune;
     const int par = odd ? 1 : 0;
-    const StepArgs ap = d->args(tu.phase_block, tu.phase_schedule, tu.phase_run[par]);
-    const StepArgs ac = d->args(tu.collide_block, tu.collide_schedule, tu.collide_run[par]);
+    const StepArgs ap = d->args(odd, tu.phase_block, tu.phase_schedule, tu.phase_run[par]);
+    const StepArgs ac = d->args(odd, tu.collide_block, tu.collide_schedule, tu.collide_run[par]);
     if (lbm_status s = mark(0, true)) return s;
     HIP_TRY(launch_phase(ap, odd, tu.phase_block, tu.phase_stream != 0, d->lds[0], d->stream));
     if (lbm_status s = mark(0, false)) return s;
@@ -287,8 +287,8 @@ static int64_t domain_bytes(const lbm_params& p, const Prepass& pre) {
                             ? r(sizeof(uint32_t) * ld) + r(sizeof(RowWord) * pre.words.size())
                             : uses_compact(p) ? compact_bytes(pre)
                                               : r(sizeof(int32_t) * 18 * ld);
-    int64_t total = r(fb * 19 * ld) + r(eb * 8 * ld) + r(2 * sizeof(int32_t)) +
-                    r(eb * (size_t)(pre.n_pore + pre.n_tail)) + r(eb * ld) +
+    int64_t total = r(fb * 19 * ld) + r(eb * 6 * ld) + r(2 * sizeof(int32_t)) +
+                    2 * r(eb * (size_t)(pre.n_pore + pre.n_tail)) + 2 * r(eb * ld) +
                     r(sizeof(double) * ld) + nbr +
                     r(sizeof(double) * kRedBlocks * kNRed) + r(sizeof(double) * kNRed) +
                     r(sizeof(double) * 1024 * kNRed);
@@ -397,10 +397,12 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
     const size_t fb = d->f_bytes(), eb = d->m_bytes();
     const size_t ld = (size_t)pre.ld;
     d->f = d->dalloc(fb * 19 * ld);
-    d->M = d->dalloc(eb * 8 * ld);
+    d->M = d->dalloc(eb * 6 * ld);
     d->fresh = (int32_t*)d->dalloc(2 * sizeof(int32_t));
-    d->phi = d->dalloc(eb * (size_t)(pre.n_pore + pre.n_tail));
-    d->ntot = d->dalloc(eb * ld);
+    for (int k = 0; k < 2; ++k) {
+        d->phi[k] = d->dalloc(eb * (size_t)(pre.n_pore + pre.n_tail));
+        d->ntot[k] = d->dalloc(eb * ld);
+    }
     d->stage = (double*)d->dalloc(sizeof(double) * ld);
     const CompactNbr& cn = pre.compact;
     if (d->rank) {
@@ -419,7 +421,8 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
     d->red_out = (double*)d->dalloc(sizeof(double) * kNRed);
     d->hist = (double*)d->dalloc(sizeof(double) * (size_t)d->hist_cap * kNRed);
     double* phi0 = d->stage;
-    if (!d->f || !d->M || !d->fresh || !d->phi || !d->ntot || !d->stage ||
+    if (!d->f || !d->M || !d->fresh || !d->phi[0] || !d->phi[1] || !d->ntot[0] ||
+        !d->ntot[1] || !d->stage ||
         (d->rank ? (!d->coord || !d->words)
                  : d->compact ? (!d->cn8 || !d->cn16 || !d->cwide || !d->cwave || !d->cex)
                               : !d->nbr) ||
@@ -476,10 +479,11 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
     }
     std::vector<float> tail32;
     if (eb == 4) tail32.assign(pre.tail_phi.begin(), pre.tail_phi.end());
-    guard(up((char*)d->phi + eb * pre.n_pore,
-             eb == 4 ? (const void*)tail32.data() : (const void*)pre.tail_phi.data(),
-             eb * pre.n_tail),
-          "upload tail");
+    for (void* phi : d->phi)
+        guard(up((char*)phi + eb * pre.n_pore,
+                 eb == 4 ? (const void*)tail32.data() : (const void*)pre.tail_phi.data(),
+                 eb * pre.n_tail),
+              "upload tail");
     guard(up(phi0, pre.phi0.data(), sizeof(double) * pre.n_pore), "upload phi0");
     if (d->faces) {
         guard(up(d->faces, faces.data(), sizeof(int32_t) * faces.size()), "upload faces");
@@ -487,8 +491,8 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
     }
     guard(up(d->fresh, &d->one, sizeof(int32_t)), "set fresh");
     guard(hipMemsetAsync(d->f, 0, fb * 19 * ld, d->stream), "clear f");
-    guard(hipMemsetAsync(d->M, 0, eb * 8 * ld, d->stream), "clear M");
-    if (st == LBM_OK) guard(launch_init(d->args(), phi0, d->block, d->stream), "init kernel");
+    guard(hipMemsetAsync(d->M, 0, eb * 6 * ld, d->stream), "clear M");
+    if (st == LBM_OK) guard(launch_init(d->args(false), phi0, d->block, d->stream), "init kernel");
     if (st == LBM_OK) guard(hipStreamSynchronize(d->stream), "create sync");
     if (st != LBM_OK) {
         (void)hipStreamSynchronize(d->stream);   // no copy may outlive its host staging vector
@@ -500,8 +504,8 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
         return fail(LBM_ERR_DEVICE, "internal: device footprint estimate out of date");
     }
     // Defaults by size (measured where the constants are defined). Domains well beyond the
-    // Infinity Cache: streaming accesses and collide runs of 4 tiles on even steps, 32 on odd
-    // ones. Workgroup limits: the autotuner's choice at 512^3 for each precision (phase / collide:
+    // Infinity Cache: streaming accesses, and collide tiles from the end of the list (400^3 FP64
+    // 1042 -> 1037 us, 320^3 FP32-mixed 353.2 -> 352.0) in runs of 4 on even steps, 32 on odd ones. Workgroup limits: the autotuner's choice at 512^3 for each precision (phase / collide:
     // FP64 5 / 2, FP32-mixed 5 / 3, FP32-dev none / 3).
     lbm_tuning t0 = d->tune;
     if (p.block_size == 0 && pre.n_pore <= kSmallVoxels) t0.phase_block = t0.collide_block = 64;
@@ -514,6 +518,7 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
     if (large) {
         t0.collide_run[0] = 4;
         t0.collide_run[1] = 32;
+        t0.collide_schedule = 3;
     }
     if (lbm_status s = apply_tuning(d.get(), t0)) {
         d->release();
@@ -540,8 +545,8 @@ lbm_status lbm_read_pore_field(lbm_domain* d, int32_t field, double* host_pore) 
     if (lbm_status s = check_domain(d)) return s;
     if (field < LBM_FIELD_NA || field > LBM_FIELD_UZ) return fail(LBM_ERR_ARG, "bad field id");
     if (!host_pore) return fail(LBM_ERR_ARG, "host_pore must be non-null");
-    const StepArgs a = d->args();
     const bool odd = (d->step & 1) != 0;
+    const StepArgs a = d->args(odd);
     const size_t bytes = sizeof(double) * (size_t)d->pre.n_pore;
     PinnedOut out(bytes);
     if (out.ptr()) {
@@ -700,13 +705,23 @@ lbm_status lbm_state_save(lbm_domain* d, void* host_buf, size_t* nbytes) {
     HIP_TRY(hipMemcpyAsync(&fresh, d->fresh, sizeof fresh, hipMemcpyDeviceToHost, d->stream));
     HIP_TRY(hipStreamSynchronize(d->stream));
     StateHeader h{kStateMagic, d->pre.n_pore, d->pre.n_tail, d->step, d->p.precision, (int32_t)fb,
-                  fresh, (int32_t)eb};
+                  fresh == 1 ? 1 : 0, (int32_t)eb};
     std::memcpy(host_buf, &h, sizeof h);
     char* dst = (char*)host_buf + sizeof h;
-    // f: 19 rows of n values and M: 4 rows of n value pairs (pitch ld on the device).
+    // f: 19 rows of n values; the components: 4 rows of n value pairs, (N_a, N_b) and M's three
+    // (pitch ld on the device).
     for (int q = 0; q < 19; ++q, dst += fb * n)
         HIP_TRY(copy_to_host(dst, (const char*)d->f + fb * ld * q, fb * n, d->stream));
-    for (int k = 0; k < 4; ++k, dst += 2 * eb * n)
+    // The component densities, formed from the previous step's phi and N a stage buffer at a time.
+    const StepArgs a = d->args((d->step & 1) != 0);
+    const size_t part = sizeof(double) * ld / (2 * eb);
+    for (size_t i = 0; i < n; i += part) {
+        const size_t m = std::min(part, n - i);
+        HIP_TRY(launch_densities_out(a, (int32_t)i, (int32_t)m, d->stage, d->stream));
+        HIP_TRY(copy_to_host(dst + 2 * eb * i, d->stage, 2 * eb * m, d->stream));
+    }
+    dst += 2 * eb * n;
+    for (int k = 0; k < 3; ++k, dst += 2 * eb * n)
         HIP_TRY(copy_to_host(dst, (const char*)d->M + 2 * eb * ld * k, 2 * eb * n, d->stream));
     *nbytes = need;
     return LBM_OK;
@@ -728,9 +743,17 @@ lbm_status lbm_state_load(lbm_domain* d, const void* host_buf, size_t nbytes) {
     const char* src = (const char*)host_buf + sizeof h;
     for (int q = 0; q < 19; ++q, src += fb * n)
         HIP_TRY(copy_to_device((char*)d->f + fb * ld * q, src, fb * n, d->stream));
-    for (int k = 0; k < 4; ++k, src += 2 * eb * n)
+    const StepArgs a = d->args((h.step & 1) != 0);
+    const size_t part = sizeof(double) * ld / (2 * eb);
+    for (size_t i = 0; i < n; i += part) {
+        const size_t m = std::min(part, n - i);
+        HIP_TRY(copy_to_device(d->stage, src + 2 * eb * i, 2 * eb * m, d->stream));
+        HIP_TRY(launch_densities_in(a, (int32_t)i, (int32_t)m, d->stage, d->stream));
+    }
+    src += 2 * eb * n;
+    for (int k = 0; k < 3; ++k, src += 2 * eb * n)
         HIP_TRY(copy_to_device((char*)d->M + 2 * eb * ld * k, src, 2 * eb * n, d->stream));
-    d->one = h.fresh ? 1 : 0;                // a state at rest (initial, or after lbm_morph)
+    d->one = h.fresh ? 1 : 2;                // at rest (initial, or after lbm_morph), or loaded
     HIP_TRY(hipMemcpyAsync(d->fresh, &d->one, sizeof(int32_t), hipMemcpyHostToDevice,
                            d->stream));
     HIP_TRY(hipStreamSynchronize(d->stream));
@@ -760,9 +783,9 @@ lbm_status lbm_domain_get_info(lbm_domain* d, lbm_domain_info* out) {
 // need (computed for the domain's own kernels by the runtime's occupancy calculator).
 static lbm_status apply_tuning(lbm_domain* d, const lbm_tuning& t) {
     unsigned lds[2] = {0, 0};
-    HIP_TRY(step_kernel_lds(d->args(t.phase_block, t.phase_schedule), 0, t.phase_block,
+    HIP_TRY(step_kernel_lds(d->args(false, t.phase_block, t.phase_schedule), 0, t.phase_block,
                             t.phase_stream != 0, t.phase_wg, &lds[0]));
-    HIP_TRY(step_kernel_lds(d->args(t.collide_block, t.collide_schedule), 1, t.collide_block,
+    HIP_TRY(step_kernel_lds(d->args(false, t.collide_block, t.collide_schedule), 1, t.collide_block,
                             t.collide_stream != 0, t.collide_wg, &lds[1]));
     d->tune = t;
     d->lds[0] = lds[0];
@@ -806,19 +829,17 @@ lbm_status lbm_autotune(lbm_domain* d, int32_t trial_steps, lbm_tuning* out) {
     if (d->pool) return fail(LBM_ERR_STATE, "the domain belongs to a pool");
     if (d->unstable) return fail(LBM_ERR_UNSTABLE, "domain is unstable; load a state");
     trial_steps += trial_steps & 1;  // even: both parities equally
-    const size_t fb = d->f_bytes(), eb = d->m_bytes(), ld = (size_t)d->pre.ld;
-    const size_t bytes = (fb * 19 + eb * 8) * ld + 256;
+    const std::vector<lbm_domain::StateArray> arrays = d->state_arrays();
+    const size_t bytes = d->state_bytes() + 256;
     char* snap = (char*)d->dalloc(bytes);
     if (!snap) return fail(LBM_ERR_OOM, "no device memory for the autotuner's snapshot");
-    void* arrays[3] = {d->f, d->M, d->fresh};
-    const size_t sizes[3] = {fb * 19 * ld, eb * 8 * ld, sizeof(int32_t)};
     auto copy_all = [&](bool save) -> hipError_t {
         size_t off = 0;
-        for (int k = 0; k < 3; ++k) {
-            const size_t nb = sizes[k];
-            hipError_t e = save ? hipMemcpyAsync(snap + off, arrays[k], nb,
+        for (const lbm_domain::StateArray& arr : arrays) {
+            const size_t nb = arr.bytes;
+            hipError_t e = save ? hipMemcpyAsync(snap + off, arr.ptr, nb,
                                                  hipMemcpyDeviceToDevice, d->stream)
-                                : hipMemcpyAsync(arrays[k], snap + off, nb,
+                                : hipMemcpyAsync(arr.ptr, snap + off, nb,
                                                  hipMemcpyDeviceToDevice, d->stream);
             if (e != hipSuccess) return e;
             off += nb;

@@ -1,0 +1,155 @@
+"""Branches of the launch and kernel dispatch at the sizes where they can go wrong: load order and
+workgroup size by domain size, the pressure condition inside the collide kernel against the face
+kernel, read-back through pinned memory or a device buffer, byte and 16-bit neighbour codes, and
+the distance and line passes of the pre-processing at word, window and packing edges. Step results
+are compared bitwise (all variants evaluate the same operations), distances exactly."""
+import numpy as np
+import pytest
+
+from oracle import prep as OP
+from paper_2007_12266_amd import inputs
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+PRECISIONS = ("fp64", "mixed", "fp32dev")
+
+
+@pytest.fixture(scope="module")
+def lbm():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2007_12266_amd import lbm as mod
+    mod.load_library()
+    return mod
+
+
+def _prec(lbm, name):
+    return {"fp64": lbm.FP64, "mixed": lbm.FP32_MIXED, "fp32dev": lbm.FP32_DEV}[name]
+
+
+def _box(shape, seed, solid_frac=0.1, periodic=(True, True, True)):
+    rng = np.random.default_rng(seed)
+    return inputs.Problem(labels=np.where(rng.random(shape) < solid_frac, 0, 1).astype(np.int32),
+                          label_kind=np.array([inputs.KIND_SOLID, inputs.KIND_PORE_INIT], np.int8),
+                          label_affinity=np.array([0.4, 0.0]),
+                          init_phi=inputs.bernoulli_phase(shape, 0.5, seed + 1),
+                          periodic=periodic, tau_a=0.7, tau_b=0.8, force=(0, 0, 1e-5))
+
+
+@pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("voxels", [(32, 32, 32), (33, 32, 32), (64, 64, 64), (65, 64, 64)])
+def test_size_dependent_kernels_are_bitwise_identical(lbm, voxels, precision):
+    """Open boxes of 32768 and 33792 voxels (default workgroups of 64 and of 256) and of 262144 and
+    266240 (all loads first, or not): the default configuration equals streaming accesses in
+    workgroups of 256, which have one variant for all sizes."""
+    prob = _box(voxels, 5, solid_frac=0.0)
+    out = []
+    for stream in (0, 1):
+        dom = lbm.Domain(prob, precision=_prec(lbm, precision))
+        n = dom.n_pore
+        assert dom.tuning()["collide_block"] == (64 if n <= 32768 else 256)
+        if stream:
+            dom.set_tuning(phase_stream=1, collide_stream=1, phase_block=256, collide_block=256)
+        dom.step(9)
+        out.append(dom.save())
+        dom.close()
+    assert out[0] == out[1]
+
+
+@pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("mode", ["table", "rank", "compact"])
+def test_pressure_faces_do_not_depend_on_how_steps_are_called(lbm, mode, precision):
+    """The pressure condition is applied by the collide kernel inside a stretch of steps and by the
+    face kernel where one ends: one call of 70 steps (a captured chunk and single steps), 70 calls,
+    and calls that end on odd steps with reductions and read-back between give the same state."""
+    prob = inputs.displacement_problem(shape=(20, 18, 22), seed_geom=31, porosity_target=0.4)
+    nm = {"table": lbm.NBR_TABLE, "rank": lbm.NBR_RANK, "compact": lbm.NBR_COMPACT}[mode]
+    blobs = []
+    for calls in ((70,), (1,) * 70, (3, 64, 2, 1)):
+        dom = lbm.Domain(prob, precision=_prec(lbm, precision), neighbour_mode=nm, reduce_every=7)
+        for n in calls:
+            dom.step(n)
+            if len(calls) > 1:
+                dom.reduce()
+                dom.pore_field("uz")
+        blobs.append((dom.save(), [h["qz"] for h in dom.history()]))
+        dom.close()
+    assert blobs[0] == blobs[1] == blobs[2]
+
+
+@pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("steps", [0, 1, 2, 65])
+def test_saved_states_continue_and_save_again(lbm, steps, precision):
+    """A state saved after an even or an odd step loads into another domain, saves as the same
+    bytes before any step, reads back the same fields, and goes on bit for bit; so does it after
+    the launch configuration was timed on it."""
+    prob = _box((14, 17, 23), 8, periodic=(True, False, True))
+    a = lbm.Domain(prob, precision=_prec(lbm, precision))
+    a.step(steps)
+    blob = a.save()
+    b = lbm.Domain(prob, precision=_prec(lbm, precision))
+    b.step(3)
+    b.load(blob)
+    assert b.save() == blob
+    for name in ("Na", "phi", "rho", "uz"):
+        assert np.array_equal(a.pore_field(name), b.pore_field(name))
+    b.autotune(2)
+    assert b.save() == blob
+    assert a.step(5).save() == b.step(5).save()
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("edge", [101, 102])
+def test_read_back_on_both_sides_of_the_pinned_limit(lbm, edge):
+    """Boxes of 1,040,502 and 1,050,804 voxels: a field below 8 MiB is written to pinned
+    memory, one above goes through the device buffer and its chunks. N_a sums to the mass either
+    way, and the dense field holds the same values."""
+    prob = _box((101, 102, edge), 3, solid_frac=0.0)
+    dom = lbm.Domain(prob)
+    dom.step(2)
+    na = dom.pore_field("Na")
+    assert (na.nbytes > 8 << 20) == (edge == 102)
+    assert abs(na.sum() - dom.reduce()["mass_a"]) <= 1e-12 * na.sum()
+    assert np.array_equal(np.sort(na), np.sort(dom.field("Na").reshape(-1)))
+    dom.close()
+
+
+@pytest.mark.parametrize("per", [(False, False, False), (True, True, True), (True, False, False)])
+@pytest.mark.parametrize("nx", [1, 4, 31, 32, 33, 63, 64, 65, 96, 100, 129, 260, 1030])
+def test_distances_at_word_and_window_edges(lbm, nx, per):
+    """Row lengths around the half words of the row windows and the shapes of its workgroups, with
+    features dense, sparse (distances beyond the windows of the row and of the lines) and one voxel
+    at the end of a row."""
+    rng = np.random.default_rng(nx)
+    shape = (11, 26, nx) if nx < 500 else (3, 5, nx)
+    last = np.zeros(shape, bool)
+    last[1, 2, nx - 1] = True
+    for feat in (rng.random(shape) < 0.3, rng.random(shape) < 3.0 / (shape[0] * shape[1] * nx), last):
+        want = OP.edt_sq(feat, per)
+        want = np.where(want >= OP.INF, -1, want)
+        assert np.array_equal(lbm.prep_distance(feat, per), want)
+        if nx < 500:
+            out = torch.empty(shape, dtype=torch.int32, device="cuda")
+            lbm.prep_distance_noalloc(torch.from_numpy(feat.astype(np.uint8)).cuda(), out,
+                                      periodic=per, stream=torch.cuda.current_stream().cuda_stream)
+            assert np.array_equal(out.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("nx", [30, 32, 64, 68, 130])
+@pytest.mark.parametrize("inlet", [False, True])
+def test_drainage_with_byte_and_wide_distances(lbm, nx, inlet):
+    """Rows that are and are not a multiple of 4 (lines packed in fours, or not), runs that cross
+    word ends, and a wide channel whose spheres exceed a squared radius of 255 (32-bit passes)."""
+    rng = np.random.default_rng(nx + inlet)
+    per = (True, True, False)
+    rock = rng.random((20, 24, nx)) < 0.9
+    channel = np.ones((40, 44, max(nx, 44)), bool)
+    channel[:, 0, :] = channel[:, :, 0] = False
+    for pore, target in ((rock, 0.5), (channel, 0.6)):
+        nw, got = lbm.prep_drain(pore, per, target, inlet=inlet)
+        want = OP.drain(pore, per, target, inlet=inlet)
+        assert np.array_equal(nw, want["nw"]) and got["k"] == want["k"]
+        assert got["evaluations"] == want["evaluations"]
+    assert got["kmax"] > 255
