@@ -73,11 +73,6 @@ __device__ __forceinline__ VoxelIdx voxel_of(const Box& b) {
     return r;
 }
 
-__device__ __forceinline__ bool bit_at(const uint64_t* __restrict__ bits, const Box& b, int row,
-                                       int x) {
-    return (bits[(int64_t)row * b.W + (x >> 6)] >> (x & 63)) & 1ull;
-}
-
 struct FeatureNonzero {
     const uint8_t* m;
     __device__ bool operator()(int64_t v) const { return m[v] != 0; }
@@ -622,94 +617,149 @@ __device__ void unite(int32_t* L, int32_t a, int32_t b) {
     }
 }
 
-// First voxel of the run of consecutive centres along x (within the row, no wrap) that
-// holds x: one past the last non-centre before x, or 0.
-__device__ __forceinline__ int run_start(const uint64_t* __restrict__ r, int x) {
-    int w = x >> 6;
-    const int sh = x & 63;
-    uint64_t m = sh ? (~r[w] & ((1ull << sh) - 1ull)) : 0ull;
-    while (!m && w > 0) m = ~r[--w];
-    if (!m) return 0;
-    return (w << 6) + 64 - __clzll((long long)m);
+// The labelling works on the runs of consecutive centres within a 64-voxel word of a row: a run's
+// label lies at its first voxel, and no other entry is touched. A workgroup first labels a tile of
+// 16 x 16 words (y by z) in LDS and writes each run's label as the tile's root, so that only runs
+// that meet across a face of a tile (or the edge of a word) are united in memory, and chains there
+// are short. (256^3, mean over the radii of a drainage: with every pair of runs united in memory
+// the merge took 171 us, up to 750 at the widest radii, in chains of labels that other XCDs
+// change, and the initial labels 8; now 17 for the tiles and 35, at most 59, for the rest.)
+constexpr int kTile = 16;                        // words of a tile along y and along z
+constexpr int kTileRuns = 32, kTileLd = 33;      // runs of a word at most; padded against conflicts
+
+// Bits of the word that start a run, and the first voxel of the run of the word that holds bit x.
+__device__ __forceinline__ uint64_t run_starts(uint64_t m) { return m & ~(m << 1); }
+__device__ __forceinline__ int run_start(uint64_t m, int x) {
+    const uint64_t gap = ~m & ((1ull << x) - 1ull);
+    return gap ? 64 - __clzll((long long)gap) : 0;
 }
 
-// The labelling works on runs: a run's label lies at its first voxel, and no other entry is
-// touched. One thread takes one 64-voxel word of a row and loops over the few runs in it. (With
-// a thread per voxel, most of them idle, and a label per voxel the merge was bound by rounds of
-// waves that each waited for a chain of labels: 256^3, mean over the radii of a drainage,
-// merge 221 us, init 29, compress 49, pack 28; now 171, 8, none and 18: what is left is the
-// merge of the widest radii, up to 750 us, in chains of labels that other XCDs change.)
-struct WordIdx {
-    int64_t k;       // word
-    int row, w;
-    bool active;
-};
-__device__ __forceinline__ WordIdx word_of(const Box& b) {
-    WordIdx t;
-    t.k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    t.active = t.k < b.nwords;
-    t.row = (int)(t.k / b.W);
-    t.w = (int)(t.k - (int64_t)t.row * b.W);
-    return t;
-}
-
-// Bits of word w of row r that start a run.
-__device__ __forceinline__ uint64_t run_starts(const uint64_t* __restrict__ r, int w) {
-    const uint64_t m = r[w], before = w > 0 ? r[w - 1] >> 63 : 0ull;
-    return m & ~((m << 1) | before);
-}
-
-// Every run is its own component, not reached.
-__global__ void __launch_bounds__(256) ccl_init_kernel(Box b, const uint64_t* __restrict__ centre,
-                                                       int32_t* __restrict__ L,
-                                                       uint8_t* __restrict__ flag) {
-    const WordIdx t = word_of(b);
-    if (!t.active) return;
-    const int32_t v0 = (int32_t)((int64_t)t.row * b.nx + 64 * t.w);
-    for (uint64_t m = run_starts(centre + (int64_t)t.row * b.W, t.w); m; m &= m - 1) {
-        const int32_t v = v0 + __ffsll((long long)m) - 1;
-        L[v] = v;
-        flag[v] = 0;
+// Labels of the runs of one tile: a run's own slot in LDS is 32 * (its word in the tile) + (its
+// first bit / 2), which no two runs share and which orders as the voxels do. flag: not reached.
+__global__ void __launch_bounds__(kTile * kTile) ccl_tile_kernel(Box b,
+                                                                 const uint64_t* __restrict__ centre,
+                                                                 int32_t* __restrict__ L,
+                                                                 uint8_t* __restrict__ flag) {
+    __shared__ int32_t lab[kTile * kTile * kTileLd];
+    __shared__ uint64_t word[kTile * kTile];
+    const int t = (int)threadIdx.x, yl = t & (kTile - 1), zl = t / kTile;
+    const int nty = (b.ny + kTile - 1) / kTile;
+    const int w = (int)(blockIdx.x % (unsigned)b.W), tile = (int)(blockIdx.x / (unsigned)b.W);
+    const int y0 = (tile % nty) * kTile, z0 = (tile / nty) * kTile;
+    const bool in = y0 + yl < b.ny && z0 + zl < b.nz;
+    const uint64_t m = in ? centre[((int64_t)(z0 + zl) * b.ny + y0 + yl) * b.W + w] : 0ull;
+    const uint64_t starts = run_starts(m);
+    word[t] = m;
+    for (uint64_t s = starts; s; s &= s - 1) {
+        const int k = (__ffsll((long long)s) - 1) >> 1;
+        lab[t * kTileLd + k] = t * kTileRuns + k;
+    }
+    __syncthreads();
+    // As find_root and unite, over slots.
+    auto at = [&](int v) { return lab + (v / kTileRuns) * kTileLd + (v & (kTileRuns - 1)); };
+    auto load = [&](int v) {
+        return __hip_atomic_load(at(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto root = [&](int v) {
+        for (int p = load(v); p != v;) {
+            const int g = load(p);
+            if (g != p) __hip_atomic_store(at(v), g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            v = p;
+            p = g;
+        }
+        return v;
+    };
+    for (int side = 0; side < 2; ++side) {
+        if ((side ? zl : yl) == 0) continue;
+        const int u = side ? t - kTile : t - 1;
+        const uint64_t q = word[u];
+        for (uint64_t f = run_starts(m & q); f; f &= f - 1) {
+            const int x = __ffsll((long long)f) - 1;
+            int i = t * kTileRuns + (run_start(m, x) >> 1);
+            int j = u * kTileRuns + (run_start(q, x) >> 1);
+            while (true) {
+                i = root(i);
+                j = root(j);
+                if (i == j) break;
+                const int hi = max(i, j), lo = min(i, j), old = atomicMin(at(hi), lo);
+                if (old == hi) break;
+                i = old;
+                j = lo;
+            }
+        }
+    }
+    __syncthreads();
+    for (uint64_t s = starts; s; s &= s - 1) {
+        const int x = __ffsll((long long)s) - 1, own = t * kTileRuns + (x >> 1), r = root(own);
+        // The root's first voxel: its word in the tile, and which bit of the pair starts a run.
+        const int rt = r / kTileRuns, pair = 2 * (r & (kTileRuns - 1));
+        const int bit = pair + ((run_starts(word[rt]) >> pair) & 1ull ? 0 : 1);
+        const int64_t row = (int64_t)(z0 + zl) * b.ny + y0 + yl;
+        const int64_t rr = (int64_t)(z0 + rt / kTile) * b.ny + y0 + (rt & (kTile - 1));
+        L[row * b.nx + 64 * w + x] = (int32_t)(rr * b.nx + 64 * w + bit);
+        if (r == own) flag[row * b.nx + 64 * w + x] = 0;
     }
 }
 
-// Unions across the -y (blockIdx.y 0) and -z (1) faces, and the periodic x face (with 0). Two
-// runs that overlap are united once, at the first overlapping x: where both left neighbours are
-// centres too, the pair to the left has already linked the same two runs.
-__global__ void __launch_bounds__(256) ccl_merge_kernel(Box b, const uint64_t* __restrict__ centre,
-                                                        int32_t* L) {
-    const WordIdx t = word_of(b);
-    if (!t.active) return;
-    const uint64_t* r = centre + (int64_t)t.row * b.W;
-    const uint64_t m = r[t.w];
-    if (!m) return;
-    const int y = t.row % b.ny, z = t.row / b.ny;
-    const int64_t base = (int64_t)t.row * b.nx;
-    const bool along_z = blockIdx.y != 0;
-    if (!along_z && t.w == 0 && (b.per & 1) && b.nx > 1 && (m & 1ull) &&
-        bit_at(centre, b, t.row, b.nx - 1))
-        unite(L, (int32_t)base, (int32_t)(base + run_start(r, b.nx - 1)));
-    int c = (along_z ? z : y) - 1;
-    if (c < 0 && (b.per & (along_z ? 4 : 2))) c = (along_z ? b.nz : b.ny) - 1;
-    if (c < 0 || c == (along_z ? z : y)) return;
-    const int rn = along_z ? c * b.ny + y : z * b.ny + c;
-    const uint64_t* q = centre + (int64_t)rn * b.W;
-    const uint64_t o = m & q[t.w];
-    const uint64_t before = t.w > 0 ? (r[t.w - 1] & q[t.w - 1]) >> 63 : 0ull;
+// Unions that no tile holds: blockIdx.y 0 across the edges of words along x (and the periodic x
+// face), 1 across the -y faces of the tiles, 2 across the -z faces. Two rows' runs that overlap are
+// united once, at the first overlapping x: where both left neighbours are centres too, the pair to
+// the left has linked the same runs, which continue across the edge of the word.
+__global__ void __launch_bounds__(256) ccl_join_kernel(Box b, const uint64_t* __restrict__ centre,
+                                                       int32_t* L) {
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int w = (int)(k % b.W);
+    const int64_t line = k / b.W;
+    int y, z, c;
+    if (blockIdx.y == 0) {
+        if (line >= (int64_t)b.ny * b.nz) return;
+        const uint64_t* r = centre + line * b.W;
+        if (!(r[w] & 1ull)) return;
+        const int64_t base = line * b.nx;
+        if (w > 0) {
+            if (r[w - 1] >> 63)
+                unite(L, (int32_t)(base + 64 * w),
+                      (int32_t)(base + 64 * (w - 1) + run_start(r[w - 1], 63)));
+        } else if ((b.per & 1) && b.nx > 1) {
+            const int e = b.nx - 1;
+            const uint64_t last = r[e >> 6];
+            if ((last >> (e & 63)) & 1ull)
+                unite(L, (int32_t)base, (int32_t)(base + 64 * (e >> 6) + run_start(last, e & 63)));
+        }
+        return;
+    }
+    if (blockIdx.y == 1) {
+        const int nty = (b.ny + kTile - 1) / kTile;
+        if (line >= (int64_t)nty * b.nz) return;
+        y = (int)(line % nty) * kTile;
+        z = (int)(line / nty);
+        c = y > 0 ? y - 1 : (b.per & 2) ? b.ny - 1 : -1;
+        if (c < 0 || c == y) return;
+    } else {
+        if (line >= (int64_t)b.ny * ((b.nz + kTile - 1) / kTile)) return;
+        y = (int)(line % b.ny);
+        z = (int)(line / b.ny) * kTile;
+        c = z > 0 ? z - 1 : (b.per & 4) ? b.nz - 1 : -1;
+        if (c < 0 || c == z) return;
+    }
+    const int64_t row = (int64_t)z * b.ny + y;
+    const int64_t rn = blockIdx.y == 1 ? (int64_t)z * b.ny + c : (int64_t)c * b.ny + y;
+    const uint64_t *r = centre + row * b.W, *q = centre + rn * b.W;
+    const uint64_t o = r[w] & q[w], before = w > 0 ? (r[w - 1] & q[w - 1]) >> 63 : 0ull;
     for (uint64_t f = o & ~((o << 1) | before); f; f &= f - 1) {
-        const int x = 64 * t.w + __ffsll((long long)f) - 1;
-        unite(L, (int32_t)(base + run_start(r, x)),
-              (int32_t)((int64_t)rn * b.nx + run_start(q, x)));
+        const int x = __ffsll((long long)f) - 1;
+        unite(L, (int32_t)(row * b.nx + 64 * w + run_start(r[w], x)),
+              (int32_t)(rn * b.nx + 64 * w + run_start(q[w], x)));
     }
 }
 
 // Flag the roots of the runs in the z = 0 plane (rows 0 .. ny-1). Every writer stores 1.
 __global__ void __launch_bounds__(256) ccl_mark_kernel(Box b, const uint64_t* __restrict__ centre,
                                                        int32_t* L, uint8_t* __restrict__ flag) {
-    const WordIdx t = word_of(b);
-    if (!t.active || t.row >= b.ny) return;
-    const int32_t v0 = (int32_t)((int64_t)t.row * b.nx + 64 * t.w);
-    for (uint64_t m = run_starts(centre + (int64_t)t.row * b.W, t.w); m; m &= m - 1)
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= (int64_t)b.ny * b.W) return;
+    const int32_t v0 = (int32_t)(k / b.W * b.nx + k % b.W * 64);
+    for (uint64_t m = run_starts(centre[k]); m; m &= m - 1)
         flag[find_root(L, v0 + __ffsll((long long)m) - 1)] = 1;
 }
 
@@ -718,18 +768,16 @@ __global__ void __launch_bounds__(256) ccl_reach_kernel(Box b, const uint64_t* _
                                                         int32_t* L,
                                                         const uint8_t* __restrict__ flag,
                                                         uint64_t* __restrict__ reach) {
-    const WordIdx t = word_of(b);
-    if (!t.active) return;
-    const uint64_t* r = centre + (int64_t)t.row * b.W;
-    const int32_t base = (int32_t)((int64_t)t.row * b.nx);
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= b.nwords) return;
+    const int32_t v0 = (int32_t)(k / b.W * b.nx + k % b.W * 64);
     uint64_t out = 0;
-    for (uint64_t m = r[t.w]; m;) {
+    for (uint64_t m = centre[k]; m;) {
         const uint64_t low = m & (0ull - m), run = m & ~(m + low);   // the lowest run in the word
-        const int x = 64 * t.w + __ffsll((long long)low) - 1;
-        if (flag[find_root(L, base + run_start(r, x))]) out |= run;
+        if (flag[find_root(L, v0 + __ffsll((long long)low) - 1)]) out |= run;
         m &= ~run;
     }
-    reach[t.k] = out;
+    reach[k] = out;
 }
 
 // Largest d2 over pore voxels and the pore count: eight consecutive voxels per thread (wide
@@ -1033,10 +1081,11 @@ struct DrainBuffers {
 lbm_status connect_to_inlet(const Box& b, const DrainBuffers& db, hipStream_t s) {
     const unsigned blocks = (unsigned)((b.nwords + 255) / 256);
     const uint64_t* centre = db.centre;
-    hipLaunchKernelGGL(ccl_init_kernel, dim3(blocks), dim3(256), 0, s, b, centre, db.label,
-                       db.flag);
+    const int64_t nty = (b.ny + kTile - 1) / kTile, ntz = (b.nz + kTile - 1) / kTile;
+    hipLaunchKernelGGL(ccl_tile_kernel, dim3((unsigned)(nty * ntz * b.W)), dim3(kTile * kTile), 0, s,
+                       b, centre, db.label, db.flag);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(ccl_merge_kernel, dim3(blocks, 2), dim3(256), 0, s, b, centre, db.label);
+    hipLaunchKernelGGL(ccl_join_kernel, dim3(blocks, 3), dim3(256), 0, s, b, centre, db.label);
     HIP_TRY(hipGetLastError());
     const int64_t plane = (int64_t)b.ny * b.W;
     hipLaunchKernelGGL(ccl_mark_kernel, dim3((unsigned)((plane + 255) / 256)), dim3(256), 0, s, b,

@@ -1,8 +1,9 @@
 """Branches of the launch and kernel dispatch at the sizes where they can go wrong: load order and
 workgroup size by domain size, the pressure condition inside the collide kernel against the face
 kernel, read-back through pinned memory or a device buffer, byte and 16-bit neighbour codes, and
-the distance and line passes of the pre-processing at word, window and packing edges. Step results
-are compared bitwise (all variants evaluate the same operations), distances exactly."""
+the distance, line and labelling passes of the pre-processing at word, window, packing and tile
+edges. Step results are compared bitwise (all variants evaluate the same operations), distances
+and masks exactly."""
 import numpy as np
 import pytest
 
@@ -153,3 +154,17 @@ def test_drainage_with_byte_and_wide_distances(lbm, nx, inlet):
         assert np.array_equal(nw, want["nw"]) and got["k"] == want["k"]
         assert got["evaluations"] == want["evaluations"]
     assert got["kmax"] > 255
+
+
+@pytest.mark.parametrize("shape", [(17, 16, 65), (16, 33, 64), (33, 15, 130), (1, 17, 63)])
+@pytest.mark.parametrize("per", [(False, False, False), (True, True, False)])
+def test_invasion_through_winding_pores_across_tiles(lbm, shape, per):
+    """Pores just above the percolation threshold, whose components wind across the tiles of 16 x 16
+    words, the words of a row and the periodic faces."""
+    rng = np.random.default_rng(shape[1])
+    for porosity in (0.33, 0.38):
+        pore = rng.random(shape) < porosity
+        pore[0, 0, 0] = True
+        nw, got = lbm.prep_drain(pore, per, 0.0, inlet=True)
+        want = OP.drain(pore, per, 0.0, inlet=True)
+        assert np.array_equal(nw, want["nw"]) and got["k"] == want["k"]
