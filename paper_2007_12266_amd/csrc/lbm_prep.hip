@@ -274,17 +274,10 @@ __device__ __forceinline__ int row_dist(const uint64_t* __restrict__ r, int W, i
     return d;
 }
 
-// A workgroup takes 256 >> qshift rows, with 1 << qshift threads (at least the row's quads, at
-// most 256) for each: one row to a workgroup left most of its threads idle and was bound by the
-// rate at which workgroups start (128^3: 16384 of one wave, 10.3 us; now 2048, 5.9 us).
-template <typename T>
-__global__ void __launch_bounds__(256) edt_row_kernel(Box b, const uint64_t* __restrict__ bits,
-                                                      int qshift, int lim, int32_t cap,
-                                                      T* __restrict__ out) {
-    const int row = (int)blockIdx.x * (256 >> qshift) + ((int)threadIdx.x >> qshift);
-    const int x0 = 4 * (((int)blockIdx.y << qshift) + ((int)threadIdx.x & ((1 << qshift) - 1)));
-    if (x0 >= b.nx || row >= b.ny * b.nz) return;
-    const uint64_t* r = bits + (int64_t)row * b.W;
+// Squared distances along x, at most cap, of the four voxels from x0 (a multiple of 4) of the row
+// whose words are r.
+__device__ __forceinline__ void row_quad(const Box& b, const uint64_t* __restrict__ r, int x0,
+                                         int lim, int32_t cap, int (&res)[4]) {
     const bool per = (b.per & 1) != 0;
     // The half words at and beside the four voxels (which share one) settle every distance below
     // 32, in about fifteen instructions without a branch; row_dist with its three words and
@@ -302,7 +295,6 @@ __global__ void __launch_bounds__(256) edt_row_kernel(Box b, const uint64_t* __r
         head = h[0];
         last = (uint32_t)(((uint64_t)h[e] << 32 | h[e - 1]) >> (((b.nx - 1) & 31) + 1));
     }
-    int res[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int x = x0 + j, sh = x & 31;
@@ -322,6 +314,20 @@ __global__ void __launch_bounds__(256) edt_row_kernel(Box b, const uint64_t* __r
         }
         res[j] = d >= kInf ? cap : min(d * d, cap);
     }
+}
+
+// A workgroup takes 256 >> qshift rows, with 1 << qshift threads (at least the row's quads, at
+// most 256) for each: one row to a workgroup left most of its threads idle and was bound by the
+// rate at which workgroups start (128^3: 16384 of one wave, 10.3 us; now 2048, 5.9 us).
+template <typename T>
+__global__ void __launch_bounds__(256) edt_row_kernel(Box b, const uint64_t* __restrict__ bits,
+                                                      int qshift, int lim, int32_t cap,
+                                                      T* __restrict__ out) {
+    const int row = (int)blockIdx.x * (256 >> qshift) + ((int)threadIdx.x >> qshift);
+    const int x0 = 4 * (((int)blockIdx.y << qshift) + ((int)threadIdx.x & ((1 << qshift) - 1)));
+    if (x0 >= b.nx || row >= b.ny * b.nz) return;
+    int res[4];
+    row_quad(b, bits + (int64_t)row * b.W, x0, lim, cap, res);
     const int64_t v = (int64_t)row * b.nx + x0;
     if ((b.nx & 3) == 0) {
         if constexpr (sizeof(T) == 4)
@@ -397,6 +403,14 @@ __device__ __forceinline__ int wall_min(const Box& b, int walls, int x, int y, i
 constexpr int kSeg = 8;
 constexpr int kWin = 8;
 
+// The least of a window's values seen from its place i, with best.
+__device__ __forceinline__ int window_min(const int (&win)[kSeg + 2 * kWin], int i, int best) {
+#pragma unroll
+    for (int d = 1; d <= kWin; ++d)
+        best = min(best, min(win[i + kWin + d], win[i + kWin - d]) + d * d);
+    return best;
+}
+
 template <int MODE, typename T>
 __global__ void __launch_bounds__(256) edt_seg_kernel(Box b, int ax, int32_t cap, int walls,
                                                       const T* __restrict__ in,
@@ -439,9 +453,7 @@ __global__ void __launch_bounds__(256) edt_seg_kernel(Box b, int ax, int32_t cap
             }
             int best = win[i + kWin];
             if (walls) best = wall_min(b, walls, x, ax == 1 ? c : o, ax == 1 ? o : c, best);
-#pragma unroll
-            for (int d = 1; d <= kWin; ++d)
-                best = min(best, min(win[i + kWin + d], win[i + kWin - d]) + d * d);
+            best = window_min(win, i, best);
             if (best > (kWin + 1) * (kWin + 1))
                 best = line_min_from(in, base, stride, c, n, per, best, kWin + 1);
             if (MODE == 0) {
@@ -464,6 +476,72 @@ __global__ void __launch_bounds__(256) edt_seg_kernel(Box b, int ax, int32_t cap
             int t = 0;
             for (int i = 0; i < kPrepThreads / 64; ++i) t += ws[i];
             part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = t;
+        }
+    }
+}
+
+// The row and y passes of int32 distances in one: a workgroup takes 64 columns of a plane, whose
+// row distances stay in LDS for the y pass, so they are neither written nor read again, and the
+// second pass has no launch. kWin rows before and after the plane's hold what lies beyond its
+// faces, so that the windows need no tests. Bound by the latency of its few workgroups at 128^3 (one
+// of 16 waves a CU), by instructions from 256^3. Row pass and y pass against this, 10% features:
+// 128^3 5.9 + 10 us and a launch, now 10 (a whole transform 26.5 -> 21.8); 256^3 25 + 44, now 44;
+// 352^3 67 + 112, now 127; 480^3 141 + 253, now 287.
+constexpr int kPlaneThreads = 1024, kPlaneCols = 64, kPlaneLd = 68, kPlaneRows = 480;
+// Whether the passes are taken in one (the tile fits the LDS to 480 rows):
+//  * up to one workgroup a CU, planes of at most 128 rows: the launch that is saved counts (whole
+//    transforms: 64^3 15.0 -> 11.5 us, 256 planes of 64 x 8 13.9 -> 11.0, of 60 x 64 23.2 -> 17.1),
+//    while a single plane of 480 rows would take 20 us against 6;
+//  * more of them, planes of at least 96 rows, which give each of the 16 waves its rows: 240 planes'
+//    columns of 256 rows 16 us against 20, 1000 of 96 rows 47.2 against 48.4. With fewer rows most
+//    waves idle (1000 planes of 124 x 32 50 us against 42.5, 8192 of 60 x 8 89 against 44).
+bool plane_pass(const Box& b) {
+    const int64_t groups = (int64_t)b.nz * ((b.nx + kPlaneCols - 1) / kPlaneCols);
+    return groups <= 256 ? b.ny <= 128 || (b.ny <= kPlaneRows && groups >= 240)
+                         : b.ny >= 96 && b.ny <= kPlaneRows;
+}
+size_t plane_lds(const Box& b) {
+    return sizeof(int32_t) * kPlaneLd * (size_t)((b.ny + kSeg - 1) / kSeg * kSeg + 2 * kWin);
+}
+__global__ void __launch_bounds__(kPlaneThreads) edt_plane_kernel(Box b, const uint64_t* __restrict__ bits,
+                                                        int lim, int32_t cap,
+                                                        int32_t* __restrict__ out) {
+    extern __shared__ int4 plane[];
+    int32_t* val = reinterpret_cast<int32_t*>(plane) + kWin * kPlaneLd;   // row y = 0
+    const int t = (int)threadIdx.x, chunks = (b.nx + kPlaneCols - 1) / kPlaneCols;
+    const int z = (int)blockIdx.x / chunks, xc = ((int)blockIdx.x - z * chunks) * kPlaneCols;
+    const int q = 4 * (t & 15), rows = (b.ny + kSeg - 1) / kSeg * kSeg;
+    const bool per = (b.per & 2) != 0;
+    if (xc + q < b.nx) {
+        for (int y = (t >> 4) - kWin; y < rows + kWin; y += kPlaneThreads / 16) {
+            const bool beyond = y < 0 || y >= b.ny;
+            int res[4] = {kInf, kInf, kInf, kInf};
+            int x0 = xc + q;
+            asm volatile("" : "+v"(x0));   // or what depends on x alone is held over all rows
+            if (!beyond || per) {
+                const int c = beyond ? ((y % b.ny) + b.ny) % b.ny : y;
+                row_quad(b, bits + ((int64_t)z * b.ny + c) * b.W, x0, lim, cap, res);
+            }
+            *reinterpret_cast<int4*>(val + y * kPlaneLd + q) =
+                make_int4(res[0], res[1], res[2], res[3]);
+        }
+    }
+    __syncthreads();
+    const int col = t & 63, x = xc + col;
+    if (x >= b.nx) return;
+    for (int c0 = kSeg * __builtin_amdgcn_readfirstlane(t >> 6); c0 < b.ny;
+         c0 += kSeg * (kPlaneThreads / 64)) {
+        int win[kSeg + 2 * kWin];
+#pragma unroll
+        for (int j = 0; j < kSeg + 2 * kWin; ++j) win[j] = val[(c0 - kWin + j) * kPlaneLd + col];
+#pragma unroll
+        for (int i = 0; i < kSeg; ++i) {
+            const int c = c0 + i;
+            if (c >= b.ny) break;
+            int best = window_min(win, i, win[i + kWin]);
+            if (best > (kWin + 1) * (kWin + 1))
+                best = line_min_from(val, col, kPlaneLd, c, b.ny, per, best, kWin + 1);
+            out[((int64_t)z * b.ny + c) * b.nx + x] = min(best, cap);
         }
     }
 }
@@ -1042,6 +1120,16 @@ lbm_status line_pass(const Box& b, int ax, int32_t cap, int walls, const T* in, 
 template <typename T>
 lbm_status edt_xy(const Box& b, const uint64_t* bits, int32_t cap, T* tmp, T* mid,
                   hipStream_t s) {
+    if constexpr (sizeof(T) == 4) {
+        if (plane_pass(b)) {
+            const int chunks = (b.nx + kPlaneCols - 1) / kPlaneCols;
+            hipLaunchKernelGGL(edt_plane_kernel, dim3((unsigned)((int64_t)b.nz * chunks)),
+                               dim3(kPlaneThreads), plane_lds(b), s, b, bits,
+                               row_limit(b, cap), cap, mid);
+            HIP_TRY(hipGetLastError());
+            return LBM_OK;
+        }
+    }
     hipLaunchKernelGGL(edt_row_kernel<T>, row_grid(b), dim3(256), 0, s, b, bits,
                        row_shift(b), row_limit(b, cap), cap, tmp);
     HIP_TRY(hipGetLastError());

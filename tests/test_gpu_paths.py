@@ -138,6 +138,20 @@ def test_distances_at_word_and_window_edges(lbm, nx, per):
             assert np.array_equal(out.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("shape", [(3, 128, 70), (3, 129, 70), (239, 137, 9), (240, 137, 9),
+                                   (240, 480, 4), (240, 481, 4), (256, 20, 6), (257, 95, 6),
+                                   (257, 96, 6)])
+@pytest.mark.parametrize("per", [(False, False, False), (True, True, False)])
+def test_distances_with_row_and_line_passes_in_one_and_apart(lbm, shape, per):
+    """Plane heights and counts on both sides of the rule, dense and sparse features, walls."""
+    rng = np.random.default_rng(shape[1])
+    for density, walls in ((0.2, 0), (0.0005, 0), (0.002, 7)):
+        feat = rng.random(shape) < density
+        want = OP.edt_sq(feat, per, [bool(walls >> a & 1) for a in range(3)])
+        want = np.where(want >= OP.INF, -1, want)
+        assert np.array_equal(lbm.prep_distance(feat, per, wall_axes=walls), want)
+
+
 @pytest.mark.parametrize("nx", [30, 32, 64, 68, 130])
 @pytest.mark.parametrize("inlet", [False, True])
 def test_drainage_with_byte_and_wide_distances(lbm, nx, inlet):
