@@ -140,10 +140,12 @@ def test_distances_at_word_and_window_edges(lbm, nx, per):
 
 @pytest.mark.parametrize("shape", [(3, 128, 70), (3, 129, 70), (239, 137, 9), (240, 137, 9),
                                    (240, 480, 4), (240, 481, 4), (256, 20, 6), (257, 95, 6),
-                                   (257, 96, 6)])
+                                   (257, 96, 6), (3, 128, 72), (240, 137, 8), (5, 20, 256),
+                                   (5, 20, 264), (3, 9, 40)])
 @pytest.mark.parametrize("per", [(False, False, False), (True, True, False)])
 def test_distances_with_row_and_line_passes_in_one_and_apart(lbm, shape, per):
-    """Plane heights and counts on both sides of the rule, dense and sparse features, walls."""
+    """Plane heights, counts and row lengths (words packed within the pass, or before) on both sides
+    of the rules, dense and sparse features, walls."""
     rng = np.random.default_rng(shape[1])
     for density, walls in ((0.2, 0), (0.0005, 0), (0.002, 7)):
         feat = rng.random(shape) < density
