@@ -35,10 +35,12 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak
 
 # Algorithmic bytes per pore voxel and step, by storage precision (F = bytes per stored D3Q19
 # population, S = bytes per stored moment slot, phi or N value) and neighbour lookup. The
-# collide kernel reads 19 f, writes 19 f and the 8 D3Q7 moment slots (N_a, N_b, u, G), reads phi
-# and N at the voxel (neighbour phi is reuse) and its neighbours' indices; the phase kernel
-# reads the 8 moment slots (each voxel's once; the six neighbours' are reuse), its neighbours'
-# indices, and writes phi and N. The indices cost 4*18 (collide) and 4*6 (phase) bytes per voxel
+# collide kernel reads 19 f, writes 19 f and the 6 D3Q7 moment slots (u, G), reads phi and N at the
+# voxel (neighbour phi is reuse) and its neighbours' indices; the phase kernel reads the 6 moment
+# slots and the previous phi and N, which give N_a and N_b (each voxel's once; the six neighbours'
+# are reuse), its neighbours' indices, and writes phi and N. launch_bytes counts by default a
+# layout that also stores N_a and N_b (8 slots) and holds compact codes in 16 bits, in which
+# the figures below are quoted; MOMENTS and CODE_BYTES are what the kernels now move. The indices cost 4*18 (collide) and 4*6 (phase) bytes per voxel
 # with the int32 table; with the rank lookup, 4 bytes of packed coordinates per voxel plus one
 # pass over the 32-byte row segments (nz*ny*ceil(nx/64) of them, counted per launch, about
 # 0.5/porosity bytes per pore voxel); with the compact lookup, the 16-byte axis record (phase) or
@@ -53,9 +55,12 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak
 # the 72-byte table once per step: 632 B per step and 504 B for the collide kernel in FP64
 # (FP32-dev 352 / 288, FP32-mixed 480 / 352).
 STORE = {"fp64": (8, 8), "fp32dev": (4, 4), "mixed": (4, 8)}
+MOMENTS = 6             # moment slots the collide kernel writes
+CODE_BYTES = (24, 8)    # compact records of a voxel read by collide and phase (byte codes; the few
+#                         waves with 16-bit codes read more and are counted as these)
 
 
-def _index_bytes(neighbours, n_pore, ex_waves):
+def _index_bytes(neighbours, n_pore, ex_waves, code_bytes):
     """Neighbour-lookup bytes per pore voxel read by one collide and one phase launch (the rank
     lookup's row segments are counted per launch by launch_bytes)."""
     if neighbours == "rank":
@@ -65,16 +70,18 @@ def _index_bytes(neighbours, n_pore, ex_waves):
     waves = -(-n_pore // 64)
     ex = min(ex_waves * 64, n_pore)
     reg = n_pore - ex
-    coll = (reg * 40 + ex * 72 + waves * 37 * 4) / n_pore
-    phase = (reg * 16 + ex * 24 + waves * 13 * 4) / n_pore
+    coll = (reg * code_bytes[0] + ex * 72 + waves * 37 * 4) / n_pore
+    phase = (reg * code_bytes[1] + ex * 24 + waves * 13 * 4) / n_pore
     return coll, phase
 
 
-def launch_bytes(precision, neighbours, n_pore, shape, ex_waves=0):
-    """Algorithmic bytes of one collide launch, one phase launch and one whole step."""
+def launch_bytes(precision, neighbours, n_pore, shape, ex_waves=0, moments=8,
+                 code_bytes=(40, 16)):
+    """Algorithmic bytes of one collide launch, one phase launch and one whole step. The phase
+    kernel reads 8 numbers a voxel whether N_a and N_b come from slots or from phi and N."""
     F, S = STORE[precision]
-    ic, ip = _index_bytes(neighbours, n_pore, ex_waves)
-    per = {"collide": F * 38 + S * (8 + 2) + ic, "phase": S * (8 + 2) + ip}
+    ic, ip = _index_bytes(neighbours, n_pore, ex_waves, code_bytes)
+    per = {"collide": F * 38 + S * (moments + 2) + ic, "phase": S * (8 + 2) + ip}
     per["step"] = per["collide"] + per["phase"]
     nz, ny, nx = shape
     rows = nz * ny * ((nx + 63) // 64) * 32 if neighbours == "rank" else 0
@@ -603,7 +610,7 @@ def main():
                     help="rows of y per block of the pore numbering (0: the library's 16)")
     ap.add_argument("--neighbours", default="auto", choices=["auto", "table", "rank", "compact"],
                     help="neighbour lookup: int32 table, rank of row-segment bit masks or "
-                         "16-bit codes above per-wave bases")
+                         "codes above per-wave bases")
     ap.add_argument("--tuning", default=None,
                     help="fixed launch shape PHASE_BLOCK,PHASE_SCHEDULE,COLLIDE_BLOCK,"
                          "COLLIDE_SCHEDULE[,PHASE_STREAM,COLLIDE_STREAM[,PHASE_WG,COLLIDE_WG"
@@ -733,7 +740,7 @@ def main():
     nb_name = {lbm.NBR_TABLE: "table", lbm.NBR_RANK: "rank",
                lbm.NBR_COMPACT: "compact"}[dinfo["neighbour_mode"]]
     nbytes = launch_bytes(args.precision, nb_name, n_pore, prob.shape,
-                          dinfo["compact_ex_waves"])
+                          dinfo["compact_ex_waves"], MOMENTS, CODE_BYTES)
     sbytes = survey_bytes(args.precision)
     achieved = nbytes["collide"] / coll_s / 1e9
     tb = _profiled_traffic(args.workload, args.precision, nb_name)

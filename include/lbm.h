@@ -62,9 +62,9 @@ typedef enum { LBM_FP64 = 0, LBM_FP32_DEV = 1, LBM_FP32_MIXED = 2 } lbm_precisio
  * indices: about 0.5 byte per image voxel, read through the caches), 4 bytes per voxel and step
  * and 68 bytes less device memory per pore voxel, but slower on MI355X (the lookup adds a
  * dependent load to every gather); needs nx <= 1024 and ny, nz <= 2048. COMPACT: the table's
- * entries as 16-bit codes above per-wave bases (64 consecutive pore voxels share a base per
+ * entries as 8- or 16-bit codes above per-wave bases (64 consecutive pore voxels share a base per
  * direction) with an 18-bit solid mask: 40 bytes per voxel plus 160 bytes per 64 voxels, the
- * few waves whose targets spread beyond 16 bits keeping int32 entries: about 37 bytes per
+ * few waves whose targets spread beyond 16 bits keeping int32 entries: about 50 bytes per
  * voxel and step less to read than TABLE, and the fastest of the three on MI355X. AUTO takes
  * COMPACT.
  * Results are bitwise identical. */

@@ -417,7 +417,7 @@ __device__ __forceinline__ double add_rounded(double s, double v) {
 }
 
 // Outgoing D3Q7 populations along an axis direction of sign sgn (+1 or -1), from one voxel's
-// moment slots (N_a, N_b, u_c, G_c for the direction's axis c):
+// densities N_a, N_b and moment slots u_c, G_c of the direction's axis c:
 // A* = w [N_a (1 + sgn u_c / cs^2) + sgn G_c], B* = w [N_b (1 + sgn u_c / cs^2) - sgn G_c],
 // w = 1/9, cs^2 = 2/9.
 template <typename R>
@@ -713,7 +713,8 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
     const R nt = (R)n_own;
     // Recolouring with the flow velocity u = j + F/2 (rho0 = 1): the outgoing D3Q7 populations
     // are w_q [N_a (1 + u.xi_q/cs^2) + G.xi_q] and w_q [N_b (1 + u.xi_q/cs^2) - G.xi_q] with
-    // G = beta (N_a N_b / N) n; their 8 defining numbers go to the voxel's own moment slots.
+    // G = beta (N_a N_b / N) n. Of their 8 defining numbers u and G go to the voxel's own moment
+    // slots; N_a and N_b follow from phi and N, which the phase kernel reads again.
     const R ux = jx + (R)(0.5 * a.F[0]), uy = jy + (R)(0.5 * a.F[1]);
     const R uz = jz + (R)(0.5 * a.F[2]);
     const R na = (R)0.5 * nt * ((R)1 + phi_i);

@@ -505,7 +505,8 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
     }
     // Defaults by size (measured where the constants are defined). Domains well beyond the
     // Infinity Cache: streaming accesses, and collide tiles from the end of the list (400^3 FP64
-    // 1042 -> 1037 us, 320^3 FP32-mixed 353.2 -> 352.0) in runs of 4 on even steps, 32 on odd ones. Workgroup limits: the autotuner's choice at 512^3 for each precision (phase / collide:
+    // 1042 -> 1037 us, 320^3 FP32-mixed 353.2 -> 352.0) in runs of 4 on even steps, 32 on odd
+    // ones. Workgroup limits: the autotuner's choice at 512^3 for each precision (phase / collide:
     // FP64 5 / 2, FP32-mixed 5 / 3, FP32-dev none / 3).
     lbm_tuning t0 = d->tune;
     if (p.block_size == 0 && pre.n_pore <= kSmallVoxels) t0.phase_block = t0.collide_block = 64;

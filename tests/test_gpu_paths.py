@@ -141,7 +141,7 @@ def test_distances_at_word_and_window_edges(lbm, nx, per):
 @pytest.mark.parametrize("shape", [(3, 128, 70), (3, 129, 70), (239, 137, 9), (240, 137, 9),
                                    (240, 480, 4), (240, 481, 4), (256, 20, 6), (257, 95, 6),
                                    (257, 96, 6), (3, 128, 72), (240, 137, 8), (5, 20, 256),
-                                   (5, 20, 264), (3, 9, 40)])
+                                   (5, 20, 264), (3, 9, 40), (240, 480, 8)])
 @pytest.mark.parametrize("per", [(False, False, False), (True, True, False)])
 def test_distances_with_row_and_line_passes_in_one_and_apart(lbm, shape, per):
     """Plane heights, counts and row lengths (words packed within the pass, or before) on both sides
