@@ -347,7 +347,8 @@ lbm_status lbm_read_history(lbm_domain* d, lbm_reduction* out, int32_t max_count
 lbm_status lbm_state_save(lbm_domain* d, void* host_buf, size_t* nbytes);
 
 /* Restore a state written by lbm_state_save of a domain with the same geometry and precision.
- * Clears the sticky unstable flag. Errors: LBM_ERR_STATE on a size or header mismatch. */
+ * Pressure faces: the next step starts from the face populations in the state, and this domain's
+ * densities or flux hold from the end of that step. Clears the sticky unstable flag. Errors: LBM_ERR_STATE on a size or header mismatch. */
 lbm_status lbm_state_load(lbm_domain* d, const void* host_buf, size_t nbytes);
 
 lbm_status lbm_domain_get_info(lbm_domain* d, lbm_domain_info* out);

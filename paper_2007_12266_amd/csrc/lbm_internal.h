@@ -37,8 +37,9 @@ struct StepArgs {
     void* M;            // [3][ld][2] D3Q7 moment slot pairs: (u_x, G_x), (u_y, G_y), (u_z, G_z)
     int32_t* fresh;     // device flags: [0] 0 while phi_prev and ntot_prev are a step's; else they
                         // hold N_a and N_b themselves: 1 in a state at rest (initial, or after a
-                        // morphological step), 2 in a state that was loaded; [1] whether [0] was 1
-                        // at the step's phase kernel, for the collide kernel that clears [0]
+                        // morphological step), 2 in a state that was loaded; [1] whether [0] was
+                        // set at the step's phase kernel, for the collide kernel that clears [0]
+                        // and takes the face populations of such a state as they are
     const int8_t* face; // per pore voxel: 0, 1 (inlet face), 2 (outlet face); null without faces
     double nu_a, nu_b;  // kinematic viscosities
     double alpha, beta;

@@ -555,7 +555,7 @@ __device__ __forceinline__ void phase_voxel(const StepArgs& a, int i, int fresh)
     store_once<STREAM>((S)nt, (S*)a.ntot + i);
     if (FACE) {
         if (ghost >= 0) ((S*)a.phi)[ghost] = phi;
-        if (i == 0) a.fresh[1] = fresh == 1 ? 1 : 0;
+        if (i == 0) a.fresh[1] = fresh != 0 ? 1 : 0;
     }
 }
 
@@ -1040,7 +1040,10 @@ __global__ void __launch_bounds__(256) field_kernel(StepArgs a, int field,
 // where a stretch of steps ends, and after every step of a flux inlet, whose density is known
 // only then. (With a kernel of their own each, ghosts and faces took 10 of 128^3's 55 us a step.)
 // The kernel reads and writes in the layout of the next step (parity ODD); the unknowns always
-// sit in the voxel's own slot q, because their upstream neighbour is outside.
+// sit in the voxel's own slot q, because their upstream neighbour is outside. The first collide
+// kernel on a state that no step of this domain has made takes its face populations as they are
+// (fresh[1]): at rest there is no condition yet, and a loaded state was settled where it was saved,
+// perhaps under other densities than this domain's.
 // ------------------------------------------------------------------------------------------
 template <int PREC, bool ODD>
 __global__ void __launch_bounds__(256) pressure_bc_kernel(StepArgs a,
