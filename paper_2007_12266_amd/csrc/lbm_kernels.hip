@@ -693,7 +693,13 @@ __device__ __forceinline__ void collide_voxel(const StepArgs& a, int i) {
         phi_own = ph[i];
         n_own = ((const S*)a.ntot)[i];
     }
-    if (FACE && fc && !a.fresh[1]) pressure_face<PREC>(fraw, fc, a.rho_face[fc - 1]);
+    // A select, not rho_face[fc - 1]: a pool's kernels hold their arguments in registers, and an
+    // index known only at run time puts all 280 bytes of them in scratch for every lane (us a step of
+    // 15 periodic members of 64^3 and one with faces, index / select: FP64 204 / 108, FP32-mixed
+    // 166 / 67.5, FP32-dev 139 / 57.9; of 16 with faces 281 / 154, 252 / 109, 227 / 76.4). The
+    // domain's own kernels lose 8 (FP64) and 18 registers with it.
+    if (FACE && fc && !a.fresh[1])
+        pressure_face<PREC>(fraw, fc, fc == 1 ? a.rho_face[0] : a.rho_face[1]);
     R fl[19];
 #pragma unroll
     for (int q = 0; q < 19; ++q) fl[q] = (R)fraw[q];
@@ -1184,8 +1190,9 @@ hipError_t launch_init(const StepArgs& a, const double* phi0, int block, hipStre
 }
 
 // The step kernel (0: phase, 1: collide) of a domain, by precision, parity, neighbour lookup,
-// streaming accesses, load order and pressure faces (whose code costs the collide kernel 20 to 40
-// registers). The phase kernel is the same at both parities.
+// streaming accesses, load order and pressure faces (whose code costs the collide kernel registers:
+// with the compact lookup 158 for 120 to 128 in FP64, 140 for 120 to 124 in FP32-mixed, 120 for 77
+// to 113 in FP32-dev). The phase kernel is the same at both parities.
 using StepKernel = void (*)(StepArgs);
 
 template <int P, int NB, bool ST, bool FACE>
