@@ -175,12 +175,12 @@ typedef struct {
  * next. wg: at most this many workgroups of the kernel resident per CU (0: as many as its
  * registers allow; up to 16), enforced by reserving LDS the kernel does not use; fewer resident
  * waves keep more of the lines that neighbouring voxels share in the L2. lbm_domain_create chooses
- * by size. Device memory above 384 MiB (FP32-dev 512 MiB): stream = 1 and the collide kernel in
- * schedule 3 with runs of 4 (even) / 32 (odd) tiles; else stream 0, schedule 2 and runs of 16. The same domains and those of more than 786432
- * pore voxels: the limits the autotuner picks at 512^3 (phase / collide wg: FP64 5 / 2, FP32-mixed
- * 5 / 3, FP32-dev 0 / 3); else none. Up to 32768 pore voxels and with lbm_params.block_size 0:
- * workgroups of 64; else 256. Results do not depend on the
- * configuration (bitwise). */
+ * by size. Device memory above 384 MiB (FP32-dev and the rank lookup: 512 MiB): stream = 1 and the
+ * collide kernel in schedule 3 with runs of 4 (even) / 32 (odd) tiles; else stream 0, schedule 2
+ * and runs of 16. The same domains and, but for the rank lookup, those of more than 786432 pore
+ * voxels: the limits the autotuner picks at 512^3 (phase / collide wg: FP64 5 / 2, FP32-mixed 5 / 3,
+ * FP32-dev 0 / 3); else none. Up to 32768 pore voxels and with lbm_params.block_size 0: workgroups
+ * of 64; else 256. Results do not depend on the configuration (bitwise). */
 typedef struct {
     int32_t phase_block, phase_schedule;
     int32_t collide_block, collide_schedule;

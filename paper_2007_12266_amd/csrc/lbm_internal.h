@@ -88,13 +88,18 @@ constexpr int64_t kStepGraphChunk = 64;
 // cache holds from one step to the next keeps that reuse. us a step without / with, porosity 0.2:
 // FP64 302 MB 105.1 / 105.2, 370 MB 134.3 / 134.5, 447 MB 166.3 / 153.2, 541 MB 206 / 186;
 // FP32-mixed 336 MB 118.6 / 118.2, 406 MB 148.1 / 142.5, 500 MB 186 / 169; FP32-dev 329 MB
-// 111.7 / 115.1, 405 MB 136.0 / 137.6.
-constexpr int64_t stream_bytes(int32_t precision) {
-    return int64_t(precision == LBM_FP32_DEV ? 512 : 384) << 20;
+// 111.7 / 115.1, 405 MB 136.0 / 137.6. With the rank lookup, whose row records are read again and
+// again, twice the cache in every precision, and no workgroup limits below it: their dependent
+// loads need the waves. us a step without / with what the other lookups get, porosity 0.25: 1.0 M
+// voxels FP64 104.9 / 122.4, FP32-mixed 88.9 / 97.6, FP32-dev 80.1 / 89.2; 2.0 M voxels FP64
+// 277.7 / 298.5, FP32-mixed 223.2 / 236.6, FP32-dev 144.4 / 166.0; 4.1 M (both stream) 623.2 / 625.3,
+// 500.8 / 493.8, 426.2 / 417.5.
+constexpr int64_t stream_bytes(int32_t precision, bool rank) {
+    return int64_t(precision == LBM_FP32_DEV || rank ? 512 : 384) << 20;
 }
 
-// Fewest pore voxels of a domain whose kernels get the per-CU workgroup limits of a large one
-// without its streaming. us a step without / with limits: FP64 0.79 M voxels 68.5 / 68.5, 0.98 M
+// Fewest pore voxels of a domain (not with the rank lookup) whose kernels get the per-CU workgroup
+// limits of a large one without its streaming. us a step without / with limits: FP64 0.79 M voxels 68.5 / 68.5, 0.98 M
 // 105.1 / 101.9, 1.2 M 134.3 / 131.3; FP32-mixed 0.79 M 51.1 / 50.3, 1.2 M 89.1 / 87.0; FP32-dev
 // 0.98 M 51.8 / 51.4. Below, they gain nothing in FP64 (0.6 M: 54.1 / 54.1) and cost a 524
 // thousand voxel domain in FP32-dev a percent.

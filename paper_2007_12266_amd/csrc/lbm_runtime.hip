@@ -510,9 +510,9 @@ lbm_status lbm_domain_create(const lbm_params* params, const int32_t* labels, in
     // FP64 5 / 2, FP32-mixed 5 / 3, FP32-dev none / 3).
     lbm_tuning t0 = d->tune;
     if (p.block_size == 0 && pre.n_pore <= kSmallVoxels) t0.phase_block = t0.collide_block = 64;
-    const bool large = d->device_bytes > stream_bytes(p.precision);
+    const bool large = d->device_bytes > stream_bytes(p.precision, d->rank);
     t0.phase_stream = t0.collide_stream = large ? 1 : 0;
-    if (large || pre.n_pore > kLimitVoxels) {
+    if (large || (!d->rank && pre.n_pore > kLimitVoxels)) {
         t0.phase_wg = p.precision == LBM_FP32_DEV ? 0 : 5;
         t0.collide_wg = p.precision == LBM_FP64 ? 2 : 3;
     }

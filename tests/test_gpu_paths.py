@@ -218,3 +218,20 @@ def test_pool_member_with_faces_costs_the_others_nothing(lbm, precision):
         for d in doms:
             d.close()
     assert took[1] <= 1.6 * took[0]
+
+
+@pytest.mark.parametrize("mode,edge,stream,limited", [("rank", 93, 0, False), ("table", 93, 0, True),
+                                                      ("compact", 93, 0, True), ("rank", 122, 0, False),
+                                                      ("compact", 122, 1, True),
+                                                      ("rank", 140, 1, True)])
+def test_default_launch_configuration_by_size_and_lookup(lbm, mode, edge, stream, limited):
+    """Open boxes above 786432 voxels, of 384 to 512 MiB and above 512 MiB in FP64: streaming and
+    workgroup limits begin later with the rank lookup, whose dependent loads need the waves."""
+    nm = {"table": lbm.NBR_TABLE, "rank": lbm.NBR_RANK, "compact": lbm.NBR_COMPACT}[mode]
+    dom = lbm.Domain(_box((edge, edge, edge), 1, solid_frac=0.0), neighbour_mode=nm)
+    tuned = dom.tuning()
+    assert (dom.info()["device_bytes"] > 384 << 20) == (edge > 93)
+    assert (dom.info()["device_bytes"] > 512 << 20) == (edge == 140)
+    assert tuned["phase_stream"] == tuned["collide_stream"] == stream
+    assert (tuned["phase_wg"], tuned["collide_wg"]) == ((5, 2) if limited else (0, 0))
+    dom.close()
