@@ -153,7 +153,8 @@ hipError_t launch_reduce(const StepArgs& a, bool odd, double* partials, double* 
                          hipStream_t s);
 // lookup: LBM_NBR_TABLE or LBM_NBR_RANK when every member uses that neighbour lookup, else
 // LBM_NBR_AUTO (each tile tests its domain's lookup at run time).
-// face: whether any member has pressure faces.
+// face: whether any member has pressure faces; for the collide kernel, faces whose condition it
+// applies itself.
 hipError_t launch_phase_batched(const BatchArgs& b, int prec, int lookup, bool face, int grid,
                                 int block, hipStream_t s);
 hipError_t launch_collide_batched(const BatchArgs& b, int prec, bool odd, int lookup, bool face,

@@ -1205,10 +1205,13 @@ static StepKernel step_kernel_fn(const StepArgs& a, int kernel, bool odd) {
                : collide_kernel<P, false, NB, ST, false, FACE>;
 }
 
+// The collide kernel needs its face code only where it applies the condition itself (a flux inlet
+// and a single plane have kernels for that after every step); the phase kernel for any face.
 template <int P, int NB, bool ST>
 static StepKernel step_kernel_fn(const StepArgs& a, int kernel, bool odd) {
-    return a.face ? step_kernel_fn<P, NB, ST, true>(a, kernel, odd)
-                  : step_kernel_fn<P, NB, ST, false>(a, kernel, odd);
+    return (kernel == 0 ? a.face != nullptr : a.face_bc != 0)
+               ? step_kernel_fn<P, NB, ST, true>(a, kernel, odd)
+               : step_kernel_fn<P, NB, ST, false>(a, kernel, odd);
 }
 
 template <int P, bool ST>

@@ -254,14 +254,20 @@ lbm_status launch_face_work(lbm_pool* p, const std::vector<int32_t>& members, bo
 // n steps of the members in `members` over the tiles that b covers.
 lbm_status launch_steps_of(lbm_pool* p, BatchArgs b, const std::vector<int32_t>& members,
                            int64_t first_step, int64_t n) {
-    bool face = false;
-    for (int32_t s : members) face = face || (p->slots[s] && p->slots[s]->p.bc_z == 1);
+    // Whether any member has pressure faces, and whether any has them in the collide kernel.
+    bool face = false, inside = false;
+    for (int32_t s : members) {
+        const lbm_domain* d = p->slots[s];
+        if (!d || d->p.bc_z != 1) continue;
+        face = true;
+        inside = inside || !d->faces_each_step();
+    }
     for (int64_t k = 0; k < n; ++k) {
         const bool odd = ((first_step + k) & 1) != 0;
         b.odd = odd ? 1 : 0;
         HIP_TRY(launch_phase_batched(b, p->precision, p->lookup, face, p->launch_grid(),
                                      kPoolBlock, p->stream));
-        HIP_TRY(launch_collide_batched(b, p->precision, odd, p->lookup, face, p->launch_grid(),
+        HIP_TRY(launch_collide_batched(b, p->precision, odd, p->lookup, inside, p->launch_grid(),
                                        kPoolBlock, p->stream));
         if (lbm_status st = launch_face_work(p, members, odd, k + 1 == n)) return st;
     }
