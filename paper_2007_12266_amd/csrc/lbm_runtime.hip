@@ -251,9 +251,15 @@ lbm_status launch_faces(lbm_domain* d, const StepArgs& a, bool odd, bool settle,
     if (d->inlet_rho)
         HIP_TRY(launch_inlet_density(a, !odd, d->faces, (int32_t)d->pre.inlet.size(),
                                      d->p.flux_in, d->inlet_rho, d->red_partials, s));
-    HIP_TRY(launch_pressure_bc(a, !odd, d->faces, (int32_t)d->pre.inlet.size(),
-                               (int32_t)d->pre.outlet.size(), d->p.rho_in, d->p.rho_out,
+    const int32_t n_in = (int32_t)d->pre.inlet.size(), n_out = (int32_t)d->pre.outlet.size();
+    // A single plane's voxels are in both lists, and the outlet's condition reads what the inlet's
+    // writes: a launch for each.
+    const bool both = d->p.nz == 1;
+    HIP_TRY(launch_pressure_bc(a, !odd, d->faces, n_in, both ? 0 : n_out, d->p.rho_in, d->p.rho_out,
                                d->inlet_rho, s));
+    if (both)
+        HIP_TRY(launch_pressure_bc(a, !odd, d->faces + n_in, 0, n_out, d->p.rho_in, d->p.rho_out,
+                                   nullptr, s));
     return LBM_OK;
 }
 }  // namespace lbm
