@@ -283,29 +283,29 @@ __device__ __forceinline__ void row_quad(const Box& b, const uint64_t* __restric
     // 32, in about fifteen instructions without a branch; row_dist with its three words and
     // searches takes over five times as many, and was what bound this pass (256^3, bytes: 56 us;
     // now 22). On a periodic row the windows near the ends go on with the first and the last
-    // 32 voxels of the row; a row shorter than 64 leaves its wraps to row_dist.
+    // 32 voxels of the row, which settles every distance on a row shorter than 64 (left to row_dist,
+    // such rows took the byte pass of 48^3 from 6.9 to 8.5 us).
     const uint32_t* h = reinterpret_cast<const uint32_t*>(r);
     const int k = x0 >> 5;
     const uint64_t cur = h[k], lo = k > 0 ? h[k - 1] : 0u, hi = k + 1 < 2 * b.W ? h[k + 1] : 0u;
     const uint64_t right = hi << 32 | cur, left = cur << 32 | lo;
-    const bool wrap = per && b.nx >= 64;
     uint32_t head = 0, last = 0;
-    if (wrap) {
+    if (per) {
         const int e = (b.nx - 1) >> 5;
         head = h[0];
-        last = (uint32_t)(((uint64_t)h[e] << 32 | h[e - 1]) >> (((b.nx - 1) & 31) + 1));
+        last = (uint32_t)(((uint64_t)h[e] << 32 | (e > 0 ? h[e - 1] : 0u)) >>
+                          (((b.nx - 1) & 31) + 1));
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int x = x0 + j, sh = x & 31;
         uint32_t R = (uint32_t)(right >> sh), L = (uint32_t)(left >> (sh + 1));
-        if (wrap) {
+        if (per) {
             if (b.nx - x < 32) R |= head << max(0, b.nx - x);
             if (x < 31) L |= last >> (x + 1);
         }
         int d = min(R ? __ffs((int)R) - 1 : 32, L ? __clz((int)L) : 32);
-        const int edge = per && !wrap ? min(x + 1, b.nx - x) : kInf;
-        const bool more = (d == 32 && lim >= 32) || (d > edge && edge <= lim);
+        const bool more = d == 32 && lim >= 32;
         if (d == 32) d = kInf;
         if (more && x < b.nx) {
             const int w = x0 >> 6;
@@ -1110,6 +1110,13 @@ dim3 seg8_grid(const Box& b, int ax) {
     return dim3((unsigned)((segs + per - 1) / per), (unsigned)((b.nx + span - 1) / span));
 }
 
+// Fewest voxels for which a thread of a pass on bytes takes four lines: below, too few waves are left
+// (512 at 2^20 voxels) to hide the longer thread, and each line has a thread of its own
+// (edt_seg_kernel). us a drainage of a rock, one line / four: 32^3 318 / 352, 64^3 403 / 440, 80^3
+// 441 / 462, 96^3 503 / 506, 112^3 599 / 598, 128^3 681 / 680, 160^3 1102 / 1047; a growth in 48^3
+// 124 / 135, 100^3 144 / 151, 128^3 160 / 152.
+constexpr int64_t kQuadVoxels = int64_t(1) << 20;
+
 // One line pass in MODE 0 or 1 (see edt_seg_kernel); *blocks receives the workgroups of the
 // launch, one partial count each in MODE 1.
 template <int MODE, typename T>
@@ -1117,7 +1124,7 @@ lbm_status line_pass(const Box& b, int ax, int32_t cap, int walls, const T* in, 
                      const uint8_t* pore, uint8_t* nw, int* part, int64_t* blocks,
                      hipStream_t s) {
     if constexpr (sizeof(T) == 1) {
-        if ((b.nx & 3) == 0) {
+        if ((b.nx & 3) == 0 && b.nvox >= kQuadVoxels) {
             const dim3 g = seg8_grid(b, ax);
             hipLaunchKernelGGL((edt_seg8_kernel<MODE>), g, dim3(256), 0, s, b, ax, row_shift(b),
                                cap, walls, in, out, pore, nw, part);

@@ -235,3 +235,29 @@ def test_default_launch_configuration_by_size_and_lookup(lbm, mode, edge, stream
     assert tuned["phase_stream"] == tuned["collide_stream"] == stream
     assert (tuned["phase_wg"], tuned["collide_wg"]) == ((5, 2) if limited else (0, 0))
     dom.close()
+
+
+@pytest.mark.parametrize("shape", [(101, 103, 100), (104, 101, 100), (33, 130, 260)])
+@pytest.mark.parametrize("per", [(False, False, False), (False, True, False)])
+def test_byte_passes_on_both_sides_of_the_four_line_rule(lbm, shape, per):
+    """Images just below and above 2^20 voxels (a line to a thread, four to a thread) whose rows and
+    lines leave remainders: pores so open that most searches go beyond the windows (squared radii of
+    82 to 255), and narrow ones."""
+    rng = np.random.default_rng(shape[1])
+    for density, target in ((0.0004, 0.5), (0.08, 0.4)):
+        pore = rng.random(shape) >= density
+        nw, got = lbm.prep_drain(pore, per, target)
+        want = OP.drain(pore, per, target)
+        assert np.array_equal(nw, want["nw"]) and got["k"] == want["k"]
+        assert density > 0.01 or 81 < got["k"] <= 255
+
+
+@pytest.mark.parametrize("nx", [1, 2, 4, 5, 16, 31, 32, 33, 48, 63, 64, 65])
+def test_distances_in_short_periodic_rows(lbm, nx):
+    """Periodic rows around one and two half words, whose windows go on with the row's own ends."""
+    rng = np.random.default_rng(nx)
+    for density in (0.5, 0.08, 1.5 / nx, 0.2 / nx):
+        feat = rng.random((3, 40, nx)) < density
+        want = OP.edt_sq(feat, (True, False, False))
+        want = np.where(want >= OP.INF, -1, want)
+        assert np.array_equal(lbm.prep_distance(feat, (True, False, False)), want)
