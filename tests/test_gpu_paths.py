@@ -261,3 +261,21 @@ def test_distances_in_short_periodic_rows(lbm, nx):
         want = OP.edt_sq(feat, (True, False, False))
         want = np.where(want >= OP.INF, -1, want)
         assert np.array_equal(lbm.prep_distance(feat, (True, False, False)), want)
+
+
+@pytest.mark.parametrize("shape", [(2, 3, 4), (64, 64, 127), (64, 64, 128), (64, 65, 128), (128, 128, 128)])
+def test_call_buffers_on_both_sides_of_the_block_limit(lbm, shape):
+    """Images whose 4-byte buffers are below, at and above 2 MiB, and whose 1-byte buffers reach it:
+    some, none or all of a call's buffers share an allocation."""
+    rng = np.random.default_rng(shape[2])
+    pore = rng.random(shape) < 0.4
+    nw = pore & (rng.random(shape) < 0.02)
+    kind = np.array([inputs.KIND_SOLID, inputs.KIND_PORE_INIT, inputs.KIND_SOLID], np.int8)
+    lab = pore.astype(np.int32)
+    per = (False, False, False)
+    assert np.array_equal(lbm.prep_relabel(lab, kind, nw, per, 2.0, 2),
+                          OP.relabel(lab, kind, nw, per, 2.0, 2))
+    assert np.array_equal(lbm.prep_mixing_layer(lab, kind, 2, 1), OP.mixing_layer(lab, kind, 2, 1))
+    mask, got = lbm.prep_drain(pore, per, 0.6, inlet=True)
+    want = OP.drain(pore, per, 0.6, inlet=True)
+    assert np.array_equal(mask, want["nw"]) and got["k"] == want["k"]
