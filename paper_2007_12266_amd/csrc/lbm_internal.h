@@ -165,10 +165,9 @@ hipError_t launch_reduce_batched(const BatchArgs& b, int prec, bool odd, int nsl
 hipError_t launch_field(const StepArgs& a, bool odd, int field, double* out, int block,
                         hipStream_t s);
 // The densities (N_a, N_b) that the components of voxels i0 .. i0 + n - 1 left with, as pairs in
-// the storage type (saved states hold them), and back (flag 2 of `fresh`).
+// the storage type (saved states hold them), and back for all voxels (flag 2 of `fresh`).
 hipError_t launch_densities_out(const StepArgs& a, int32_t i0, int32_t n, void* pairs, hipStream_t s);
-hipError_t launch_densities_in(const StepArgs& a, int32_t i0, int32_t n, const void* pairs,
-                               hipStream_t s);
+hipError_t launch_densities_in(const StepArgs& a, const void* pairs, hipStream_t s);
 
 // Host <-> device copies of large caller buffers (lbm_transfer.hip): staged through pinned
 // memory by several host threads while the previous chunk's DMA runs. Ordered on stream s after

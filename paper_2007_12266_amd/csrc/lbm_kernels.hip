@@ -1367,12 +1367,13 @@ __global__ void __launch_bounds__(256) densities_out_kernel(StepArgs a, int i0, 
 }
 
 template <typename S>
-__global__ void __launch_bounds__(256) densities_in_kernel(StepArgs a, int i0, int n,
+__global__ void __launch_bounds__(256) densities_in_kernel(StepArgs a,
                                                            const S* __restrict__ pairs) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    ((S*)a.phi_prev)[i0 + k] = pairs[2 * (size_t)k];
-    ((S*)a.ntot_prev)[i0 + k] = pairs[2 * (size_t)k + 1];
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= a.N) return;
+    const auto v = load_pair<S>(pairs, 0, 0, i);
+    ((S*)a.phi_prev)[i] = v.x;
+    ((S*)a.ntot_prev)[i] = v.y;
 }
 }  // namespace
 
@@ -1388,14 +1389,13 @@ hipError_t launch_densities_out(const StepArgs& a, int32_t i0, int32_t n, void* 
     return hipGetLastError();
 }
 
-hipError_t launch_densities_in(const StepArgs& a, int32_t i0, int32_t n, const void* pairs,
-                               hipStream_t s) {
-    const dim3 grid((n + 255) / 256);
+hipError_t launch_densities_in(const StepArgs& a, const void* pairs, hipStream_t s) {
+    const dim3 grid(grid_for(a, 256));
     if (a.prec == LBM_FP32_DEV)
-        hipLaunchKernelGGL(densities_in_kernel<float>, grid, dim3(256), 0, s, a, i0, n,
+        hipLaunchKernelGGL(densities_in_kernel<float>, grid, dim3(256), 0, s, a,
                            (const float*)pairs);
     else
-        hipLaunchKernelGGL(densities_in_kernel<double>, grid, dim3(256), 0, s, a, i0, n,
+        hipLaunchKernelGGL(densities_in_kernel<double>, grid, dim3(256), 0, s, a,
                            (const double*)pairs);
     return hipGetLastError();
 }

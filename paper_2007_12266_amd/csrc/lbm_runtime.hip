@@ -719,13 +719,21 @@ lbm_status lbm_state_save(lbm_domain* d, void* host_buf, size_t* nbytes) {
     // (pitch ld on the device).
     for (int q = 0; q < 19; ++q, dst += fb * n)
         HIP_TRY(copy_to_host(dst, (const char*)d->f + fb * ld * q, fb * n, d->stream));
-    // The component densities, formed from the previous step's phi and N a stage buffer at a time.
+    // The component densities, formed from the previous step's phi and N: in pinned memory where
+    // they fit, else a stage buffer at a time.
     const StepArgs a = d->args((d->step & 1) != 0);
-    const size_t part = sizeof(double) * ld / (2 * eb);
-    for (size_t i = 0; i < n; i += part) {
-        const size_t m = std::min(part, n - i);
-        HIP_TRY(launch_densities_out(a, (int32_t)i, (int32_t)m, d->stage, d->stream));
-        HIP_TRY(copy_to_host(dst + 2 * eb * i, d->stage, 2 * eb * m, d->stream));
+    const size_t bytes = 2 * eb * n;
+    PinnedOut pairs(bytes);
+    if (pairs.ptr()) {
+        HIP_TRY(launch_densities_out(a, 0, (int32_t)n, pairs.ptr(), d->stream));
+        HIP_TRY(pairs.take(dst, bytes, d->stream));
+    } else {
+        const size_t part = sizeof(double) * ld / (2 * eb);
+        for (size_t i = 0; i < n; i += part) {
+            const size_t m = std::min(part, n - i);
+            HIP_TRY(launch_densities_out(a, (int32_t)i, (int32_t)m, d->stage, d->stream));
+            HIP_TRY(copy_to_host(dst + 2 * eb * i, d->stage, 2 * eb * m, d->stream));
+        }
     }
     dst += 2 * eb * n;
     for (int k = 0; k < 3; ++k, dst += 2 * eb * n)
@@ -750,13 +758,9 @@ lbm_status lbm_state_load(lbm_domain* d, const void* host_buf, size_t nbytes) {
     const char* src = (const char*)host_buf + sizeof h;
     for (int q = 0; q < 19; ++q, src += fb * n)
         HIP_TRY(copy_to_device((char*)d->f + fb * ld * q, src, fb * n, d->stream));
-    const StepArgs a = d->args((h.step & 1) != 0);
-    const size_t part = sizeof(double) * ld / (2 * eb);
-    for (size_t i = 0; i < n; i += part) {
-        const size_t m = std::min(part, n - i);
-        HIP_TRY(copy_to_device(d->stage, src + 2 * eb * i, 2 * eb * m, d->stream));
-        HIP_TRY(launch_densities_in(a, (int32_t)i, (int32_t)m, d->stage, d->stream));
-    }
+    // The densities by way of M, whose own rows follow.
+    HIP_TRY(copy_to_device(d->M, src, 2 * eb * n, d->stream));
+    HIP_TRY(launch_densities_in(d->args((h.step & 1) != 0), d->M, d->stream));
     src += 2 * eb * n;
     for (int k = 0; k < 3; ++k, src += 2 * eb * n)
         HIP_TRY(copy_to_device((char*)d->M + 2 * eb * ld * k, src, 2 * eb * n, d->stream));

@@ -279,3 +279,20 @@ def test_call_buffers_on_both_sides_of_the_block_limit(lbm, shape):
     mask, got = lbm.prep_drain(pore, per, 0.6, inlet=True)
     want = OP.drain(pore, per, 0.6, inlet=True)
     assert np.array_equal(mask, want["nw"]) and got["k"] == want["k"]
+
+
+@pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("edge", [80, 81, 102])
+def test_large_states_save_and_load(lbm, edge, precision):
+    """Boxes of 512,000, 531,441 and 1,061,208 voxels: the component densities of a saved state go
+    through pinned memory up to 8 MiB and in parts above (first in FP64 and FP32-mixed, then in
+    FP32-dev). The state loads, saves as the same bytes and goes on bit for bit."""
+    prob = _box((edge, edge, edge), 6, solid_frac=0.0)
+    a, b = (lbm.Domain(prob, precision=_prec(lbm, precision)) for _ in range(2))
+    blob = a.step(3).save()
+    b.load(blob)
+    assert b.save() == blob
+    assert np.array_equal(a.pore_field("Nb"), b.pore_field("Nb"))
+    assert a.step(2).save() == b.step(2).save()
+    a.close()
+    b.close()
