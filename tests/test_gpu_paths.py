@@ -6,6 +6,7 @@ edges. Step results are compared bitwise (all variants evaluate the same operati
 and masks exactly."""
 import dataclasses
 import time
+from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
 import pytest
@@ -296,3 +297,28 @@ def test_large_states_save_and_load(lbm, edge, precision):
     assert a.step(2).save() == b.step(2).save()
     a.close()
     b.close()
+
+
+def test_read_back_by_more_threads_than_pinned_buffers(lbm):
+    """Ten threads, each with a domain on a stream of its own, step, reduce and read at once: some
+    read through pinned memory and some through their device buffers, all what one thread reads."""
+    probs = [_box((20, 22, 24 + k), 60 + k) for k in range(10)]
+
+    def work(dom):
+        out = []
+        for _ in range(12):
+            dom.step(3)
+            out.append((dom.reduce(), dom.pore_field("phi").tobytes(), dom.save()))
+        return out
+
+    want = []
+    for p in probs:
+        dom = lbm.Domain(p)
+        want.append(work(dom))
+        dom.close()
+    streams = [torch.cuda.Stream() for _ in probs]
+    doms = [lbm.Domain(p, stream=s.cuda_stream) for p, s in zip(probs, streams)]
+    with ThreadPoolExecutor(len(doms)) as pool:
+        assert list(pool.map(work, doms)) == want
+    for d in doms:
+        d.close()
