@@ -322,3 +322,16 @@ def test_read_back_by_more_threads_than_pinned_buffers(lbm):
         assert list(pool.map(work, doms)) == want
     for d in doms:
         d.close()
+
+
+@pytest.mark.parametrize("edge", [50, 52, 57, 65, 80])
+def test_read_back_in_one_to_eight_parts(lbm, edge):
+    """Fields of 0.95 to 3.9 MiB, copied out of pinned memory by one thread for each 512 KiB: in pore
+    order the values of the dense field, which is formed from a copy of its own."""
+    dom = lbm.Domain(_box((edge, edge, edge), 9, solid_frac=0.0))
+    dom.step(2)
+    for name in ("Na", "uz"):
+        got = dom.pore_field(name)
+        assert np.array_equal(got, dom.field(name).reshape(-1)[dom.pore_index()])
+    assert abs(dom.pore_field("Na").sum() - dom.reduce()["mass_a"]) <= 1e-12 * got.size
+    dom.close()
