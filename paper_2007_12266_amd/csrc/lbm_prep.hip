@@ -403,6 +403,27 @@ __device__ __forceinline__ int wall_min(const Box& b, int walls, int x, int y, i
 constexpr int kSeg = 8;
 constexpr int kWin = 8;
 
+// The places of a window's entries, each given to `load` with its index. A periodic line is walked
+// from where the window begins: one remainder for the window, where one for each entry beyond the
+// ends took a fifth of a short line's pass. Any place (c0) stands for one outside another line.
+template <typename Load>
+__device__ __forceinline__ void window_places(int c0, int n, bool per, Load load) {
+    if (per) {
+        int c = c0 < kWin ? (n - (kWin - c0) % n) % n : c0 - kWin;
+#pragma unroll
+        for (int j = 0; j < kSeg + 2 * kWin; ++j) {
+            load(j, c);
+            c = c + 1 < n ? c + 1 : 0;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kSeg + 2 * kWin; ++j) {
+            const int c = c0 - kWin + j;
+            load(j, c < 0 || c >= n ? c0 : c);
+        }
+    }
+}
+
 // The least of a window's values seen from its place i, with best.
 __device__ __forceinline__ int window_min(const int (&win)[kSeg + 2 * kWin], int i, int best) {
 #pragma unroll
@@ -431,12 +452,9 @@ __global__ void __launch_bounds__(256) edt_seg_kernel(Box b, int ax, int32_t cap
     int cnt = 0;
     if (active) {
         int win[kSeg + 2 * kWin];
-#pragma unroll
-        for (int j = 0; j < kSeg + 2 * kWin; ++j) {
-            int c = c0 - kWin + j;
-            if (c < 0 || c >= n) c = per ? ((c % n) + n) % n : c0;   // c0: any place of the line
+        window_places(c0, n, per, [&](int j, int c) {
             win[j] = (int)in[base + (int64_t)c * stride];
-        }
+        });
         if (!per) {
 #pragma unroll
             for (int j = 0; j < kSeg + 2 * kWin; ++j)
@@ -595,12 +613,9 @@ __global__ void __launch_bounds__(256) edt_seg8_kernel(Box b, int ax, int qshift
     int cnt = 0;
     if (x0 < b.nx && at < other * nseg) {
         uint32_t raw[kSeg + 2 * kWin];
-#pragma unroll
-        for (int j = 0; j < kSeg + 2 * kWin; ++j) {
-            int c = c0 - kWin + j;
-            if (c < 0 || c >= n) c = per ? ((c % n) + n) % n : c0;
+        window_places(c0, n, per, [&](int j, int c) {
             raw[j] = *reinterpret_cast<const uint32_t*>(in + base + (int64_t)c * stride);
-        }
+        });
         Pair16 even[kSeg + 2 * kWin], odd[kSeg + 2 * kWin];   // lines x0, x0 + 2 and x0 + 1, x0 + 3
 #pragma unroll
         for (int j = 0; j < kSeg + 2 * kWin; ++j) {
@@ -1186,9 +1201,11 @@ lbm_status edt_xy(const Box& b, const uint64_t* bits, int32_t cap, T* tmp, T* mi
                   hipStream_t s) {
     if constexpr (sizeof(T) == 4)
         if (plane_pass(b)) return edt_plane<false>(b, bits, nullptr, cap, mid, s);
+    const bool flat = b.ny == 1;   // no line along y: the row pass is both
     hipLaunchKernelGGL(edt_row_kernel<T>, row_grid(b), dim3(256), 0, s, b, bits,
-                       row_shift(b), row_limit(b, cap), cap, tmp);
+                       row_shift(b), row_limit(b, cap), cap, flat ? mid : tmp);
     HIP_TRY(hipGetLastError());
+    if (flat) return LBM_OK;
     return line_pass<0, T>(b, 1, cap, 0, tmp, mid, nullptr, nullptr, nullptr, nullptr, s);
 }
 

@@ -335,3 +335,24 @@ def test_read_back_in_one_to_eight_parts(lbm, edge):
         assert np.array_equal(got, dom.field(name).reshape(-1)[dom.pore_index()])
     assert abs(dom.pore_field("Na").sum() - dom.reduce()["mass_a"]) <= 1e-12 * got.size
     dom.close()
+
+
+@pytest.mark.parametrize("thin", [1, 2, 3, 7, 8, 9, 15, 16, 17])
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("per", [(False, False, False), (True, True, True)])
+def test_thin_images_in_each_axis(lbm, axis, thin, per):
+    """Lines along y or z of 1 to 17 voxels, around the segments and the windows, which on a periodic
+    line wrap more than once, in rows packed in eights and not, on planes of few and of many rows:
+    distances, with walls, and (bytes) a drainage."""
+    rng = np.random.default_rng(10 * thin + axis)
+    for nx, other in ((40, 70), (37, 130), (300, 12)):
+        shape = (thin, other, nx) if axis == 0 else (other, thin, nx)
+        for density, walls in ((0.1, 0), (3.0 / (thin * other * nx), 7)):
+            feat = rng.random(shape) < density
+            want = OP.edt_sq(feat, per, [bool(walls >> a & 1) for a in range(3)])
+            want = np.where(want >= OP.INF, -1, want)
+            assert np.array_equal(lbm.prep_distance(feat, per, wall_axes=walls), want)
+        pore = rng.random(shape) < 0.9
+        mask, got = lbm.prep_drain(pore, per, 0.5)
+        want = OP.drain(pore, per, 0.5)
+        assert np.array_equal(mask, want["nw"]) and got["k"] == want["k"]
