@@ -7,13 +7,13 @@
 //
 // Distance transform, separable: the squared distance to the nearest feature voxel is
 // min over (y', z') of [g(x; y', z')^2 + (y - y')^2 + (z - z')^2], g the distance along the
-// row. The row pass finds g from the rows packed as 64-voxel bit words (find-first-set on whole
-// words); the y and z passes search outward from each voxel and stop once d^2 reaches the best
-// value so far, which is exact because every candidate at offset d costs at least d^2. A thread
-// of those passes takes 8 positions of a line and reads the 16 values of their offsets up to 4
-// at once, so the common short search is one round trip. With a cap c (only distances below c
-// matter) every value is clipped at c and the searches stop at c. Squared distances are int32
-// with kInf = 2^30 - 1 for "none": sizes up to 16384 keep kInf + n^2 below 2^31.
+// row. The row pass finds g from the rows packed as 64-voxel bit words (windows of 32 voxels to each
+// side, then find-first-set on whole words); the y and z passes search outward from each voxel and
+// stop once d^2 reaches the best value so far, which is exact because every candidate at offset d
+// costs at least d^2. A thread of those passes takes 8 positions of a line and reads the 24 values of
+// their offsets up to 8 at once, so the common short search is one round trip. With a cap c (only
+// distances below c matter) every value is clipped at c and the searches stop at c. Squared
+// distances are int32 with kInf = 2^30 - 1 for "none": sizes up to 16384 keep kInf + n^2 below 2^31.
 //
 // Per-voxel kernels run on a 2-D grid: blockIdx.x is the image row (y, z), blockIdx.y the
 // chunk of x, so no thread divides a 64-bit index. Bit rows are packed with wide loads and
@@ -585,7 +585,8 @@ __global__ void __launch_bounds__(kPlaneThreads) edt_plane_kernel(Box b,
     }
 }
 
-// The line pass for distances held in bytes (cap <= 255) and rows of a multiple of 4: a thread
+// The line pass for distances held in bytes (cap <= 255), rows of a multiple of 4 and images of
+// kQuadVoxels and more: a thread
 // takes four neighbouring lines, a window entry is one 4-byte load, and the minima run on pairs
 // of 16-bit values. With a byte per load and a minimum per value the passes took as long as with
 // int32 (256^3: 43 us each, bound by their loads and instructions); now 23. The lines'

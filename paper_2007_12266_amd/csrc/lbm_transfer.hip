@@ -10,7 +10,7 @@
 // Small results (a field of a small domain, the sums of a reduction) need no device buffer at
 // all: their kernels write into pinned host memory (PinnedOut), the host waits for the stream and
 // copies them out. A device-to-host copy of pageable memory costs 40 us and more before its first
-// byte (a field of 20 thousand voxels took 95 us, now 25; one of 524 thousand 285, now 195; a
+// byte (a field of 20 thousand voxels took 95 us, now 25; one of 512 thousand 259, now 158; a
 // reduction 60, now 45).
 #include <algorithm>
 #include <condition_variable>
