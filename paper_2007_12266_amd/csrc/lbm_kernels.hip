@@ -464,16 +464,36 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, int fresh, d
     for (int q = 1; q < 7; ++q) up[q] = nb_stream<NB, STREAM>(a, OPP[q], i, pos);  // i - xi_q
     const int fc = FACE ? face_of<NB>(a, i) : 0;
     ghost = fc && !use_rank<NB>(a) ? (fc == 1 ? up[5] : up[6]) : -1;   // along -z, along +z
-    R sna[7], snb[7], suc[7], sgc[7];
+    // In a state at rest the neighbours' numbers count for nothing (see below), and a large domain's
+    // kernel does not fetch them: us a count of the phase right after a growth (which is a launch of
+    // the phase kernel), fetched / not, 256^3 FP64 118 / 75, 320^3 220 / 120. The lookup stays ahead of
+    // this wait for the flag (behind it the rest count takes 59 and 89, but every step 0.5 to 1.2% at
+    // 128^3), and a domain of few waves does not wait at all (EARLY below).
+    constexpr bool kFloat = sizeof(S) == sizeof(float);
+    R sna[7], snb[7], suc[7], sgc[7], ouc[3], ogc[3];
+    if (a.N > kEarlyVoxels && fresh == 1) {
 #pragma unroll
-    for (int q = 1; q < 7; ++q) {
-        const int c = (q - 1) >> 1;
-        const int y = up[q] < a.N ? up[q] : i;
-        sna[q] = (R)pp[y];
-        snb[q] = (R)np[y];
-        const auto g = load_pair<S>(M, a.ld, c, y);
-        suc[q] = (R)g.x;
-        sgc[q] = (R)g.y;
+        for (int q = 1; q < 7; ++q) sna[q] = snb[q] = suc[q] = sgc[q] = (R)0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) ouc[c] = ogc[c] = (R)0;
+    } else {
+#pragma unroll
+        for (int q = 1; q < 7; ++q) {
+            const int c = (q - 1) >> 1;
+            const int y = up[q] < a.N ? up[q] : i;
+            sna[q] = (R)pp[y];
+            snb[q] = (R)np[y];
+            const auto g = load_pair<S>(M, a.ld, c, y);
+            suc[q] = (R)g.x;
+            sgc[q] = (R)g.y;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (kFloat) {
+                const auto g = load_pair<S>(M, a.ld, c, i);
+                ouc[c] = (R)g.x;
+                ogc[c] = (R)g.y;
+            }
     }
 #pragma unroll
     for (int q = 1; q < 7; ++q) {
@@ -483,15 +503,15 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, int fresh, d
     }
     R own_a, own_b;
     sent<R>((R)own_p, (R)own_n, fresh != 0, own_a, own_b);
-    if (sizeof(S) == sizeof(float)) {
+    if (kFloat) {
         // The rest population is what the six moving ones leave of N (the rounded float weights
         // would otherwise add 1.5e-8 of mass per step); sums in double, see below.
         double sa = 0.0, sb = 0.0;
 #pragma unroll
         for (int q = 1; q < 7; ++q) {
             R ao, bo;
-            const auto g = load_pair<S>(M, a.ld, (q - 1) >> 1, i);
-            ab_out<R>(own_a, own_b, (R)g.x, (R)g.y, (q & 1) ? (R)1 : (R)-1, ao, bo);
+            const int c = (q - 1) >> 1;
+            ab_out<R>(own_a, own_b, ouc[c], ogc[c], (q & 1) ? (R)1 : (R)-1, ao, bo);
             sa += (double)ao;
             sb += (double)bo;
         }
