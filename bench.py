@@ -40,8 +40,8 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak
 # slots and the previous phi and N, which give N_a and N_b (each voxel's once; the six neighbours'
 # are reuse), its neighbours' indices, and writes phi and N. launch_bytes counts by default a
 # layout that also stores N_a and N_b (8 slots) and holds compact codes in 16 bits, in which
-# the figures below are quoted; MOMENTS and CODE_BYTES are what the kernels now move. The indices cost 4*18 (collide) and 4*6 (phase) bytes per voxel
-# with the int32 table; with the rank lookup, 4 bytes of packed coordinates per voxel plus one
+# the figures below are quoted; MOMENTS and CODE_BYTES are what the kernels now move. The indices
+# cost 4*18 (collide) and 4*6 (phase) bytes per voxel with the int32 table; with the rank lookup, 4 bytes of packed coordinates per voxel plus one
 # pass over the 32-byte row segments (nz*ny*ceil(nx/64) of them, counted per launch, about
 # 0.5/porosity bytes per pore voxel); with the compact lookup, the 16-byte axis record (phase) or
 # all 40 bytes of records (collide) per voxel, plus the wave bases each kernel reads (13 or 37
@@ -56,8 +56,9 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E peak
 # (FP32-dev 352 / 288, FP32-mixed 480 / 352).
 STORE = {"fp64": (8, 8), "fp32dev": (4, 4), "mixed": (4, 8)}
 MOMENTS = 6             # moment slots the collide kernel writes
-CODE_BYTES = (24, 8)    # compact records of a voxel read by collide and phase (byte codes; the few
-#                         waves with 16-bit codes read more and are counted as these)
+CODE_BYTES = (24, 8)    # compact records of a voxel read by collide and phase in waves of byte codes;
+#                         waves of 16-bit codes, which read 40 and 16, are counted as these, so the
+#                         published bytes are a lower bound
 
 
 def _index_bytes(neighbours, n_pore, ex_waves, code_bytes):
@@ -216,8 +217,10 @@ def steady_study(prob, args, lbm, plain_ms: float) -> dict:
 def flux_study(prob, args, lbm) -> dict:
     """The flux inlet on a pressure-face workload: the same geometry stepped with the imposed
     inlet density and with the imposed total flow rate (inlet_mode 1, flux = the flow rate the
-    density inlet carries after 200 steps); per-step device time of the boundary kernels
-    (inlet density + pressure faces) and of the whole step from HIP events."""
+    density inlet carries after 200 steps); device time of the boundary kernels (inlet density +
+    pressure faces) over the steps that run them, how many of the 100 do (all with the flux inlet;
+    the density inlet's condition is part of the collide kernel), and of the whole step, from HIP
+    events."""
     import dataclasses
     P = prec_of(lbm, args.precision)
     out = {}
@@ -228,7 +231,8 @@ def flux_study(prob, args, lbm) -> dict:
     plane = prob.shape[1] * prob.shape[2]
     flux = float(uz[pv < plane].sum())
     t = dom.step_timed(100)
-    out["density_inlet"] = {"bc_ms": round(t["bc_ms"], 5), "step_ms": round(t["step_ms"], 5)}
+    out["density_inlet"] = {"bc_ms": round(t["bc_ms"], 5), "bc_launches": t["bc_launches"],
+                            "step_ms": round(t["step_ms"], 5)}
     dom.close()
     fprob = dataclasses.replace(prob, inlet_mode=1, flux_in=flux)
     dom = lbm.Domain(fprob, precision=P, allocator="hip")
@@ -236,6 +240,7 @@ def flux_study(prob, args, lbm) -> dict:
     t = dom.step_timed(100)
     uz = dom.pore_field("uz")
     out["flux_inlet"] = {"flux_in": flux, "bc_ms": round(t["bc_ms"], 5),
+                         "bc_launches": t["bc_launches"],
                          "step_ms": round(t["step_ms"], 5),
                          "inlet_flux_after": float(uz[pv < plane].sum())}
     dom.close()
@@ -789,7 +794,8 @@ def main():
                   "survey_bytes_per_voxel": sbytes["step"],
                   "frac_survey_bytes": round(sbytes["step"] * n_pore / (ms_per_step / 1e3)
                                              / 1e9 / HBM_PEAK_GBS, 4),
-                  "phase_ms": round(timing["phase_ms"], 5), "bc_ms": round(timing["bc_ms"], 5)},
+                  "phase_ms": round(timing["phase_ms"], 5), "bc_ms": round(timing["bc_ms"], 5),
+                  "bc_launches": timing["bc_launches"]},
         reductions={"every": every, "recorded_in_timed_steps": len(hist),
                     "interval_ms": round(ms_every, 4), "recorded_in_interval": n_red,
                     "ms_per_step_with_reductions": round(ms_every / every, 5),

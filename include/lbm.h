@@ -64,9 +64,9 @@ typedef enum { LBM_FP64 = 0, LBM_FP32_DEV = 1, LBM_FP32_MIXED = 2 } lbm_precisio
  * dependent load to every gather); needs nx <= 1024 and ny, nz <= 2048. COMPACT: the table's
  * entries as 8- or 16-bit codes above per-wave bases (64 consecutive pore voxels share a base per
  * direction) with an 18-bit solid mask: 40 bytes per voxel plus 160 bytes per 64 voxels, the
- * few waves whose targets spread beyond 16 bits keeping int32 entries: about 50 bytes per
- * voxel and step less to read than TABLE, and the fastest of the three on MI355X. AUTO takes
- * COMPACT.
+ * waves whose targets spread beyond 16 bits (11 to 20% in rocks) keeping int32 entries: about 50
+ * bytes per voxel and step less to read than TABLE, and the fastest of the three on MI355X. AUTO
+ * takes COMPACT.
  * Results are bitwise identical. */
 typedef enum {
     LBM_NBR_AUTO = 0, LBM_NBR_TABLE = 1, LBM_NBR_RANK = 2, LBM_NBR_COMPACT = 3
@@ -154,7 +154,10 @@ typedef struct {
 typedef struct {
     double phase_ms;          /* densities + phase indicator kernel                         */
     double collide_ms;        /* fused gradient + collision + recolour + stream kernel       */
-    double bc_ms;             /* pressure-face kernel (0 if unused)                          */
+    double bc_ms;             /* pressure-face kernels, mean over the bc_launches steps that ran */
+                              /* them (0 if none): every step with a flux inlet; with fixed      */
+                              /* densities the condition is part of collide_ms, and only the     */
+                              /* last step of a call or one a reduction follows runs them        */
     double step_ms;           /* wall time per step between the first and last event         */
     int64_t phase_launches, collide_launches, bc_launches;
     double collide_parity_ms[2]; /* collide_ms over the even [0] and odd [1] AA steps alone    */

@@ -58,3 +58,23 @@ def test_committed_profile_describes_the_current_kernels():
         "per_voxel"]["collide"] * 0.9
     assert bench._profiled_traffic("disp512", "fp64", "rank") is None
     assert bench._profiled_traffic("disp512", "fp64", "table") is None
+
+
+def test_algorithmic_bytes_of_the_present_kernels():
+    """What the bench line counts: the collide kernel writes 6 moment slots (N_a and N_b follow from
+    phi and N), and compact records are 24 B (collide) and 8 B (phase) per voxel, of waves with byte
+    codes; exception waves read int32 entries as before. FP64 without exceptions: 8 * (38 + 6 + 2) + 24
+    + 37 * 4 / 64 and 8 * (8 + 2) + 8 + 13 * 4 / 64."""
+    assert bench.MOMENTS == 6 and bench.CODE_BYTES == (24, 8)
+    now = dict(moments=bench.MOMENTS, code_bytes=bench.CODE_BYTES)
+    c = bench.launch_bytes("fp64", "compact", 640, (8, 8, 10), **now)
+    assert c["collide"] == 640 * (368 + 24) + 10 * 148
+    assert c["phase"] == 640 * (80 + 8) + 10 * 52
+    e = bench.launch_bytes("mixed", "compact", 640, (8, 8, 10), ex_waves=2, **now)
+    assert e["collide"] == 640 * (152 + 64) + 512 * 24 + 128 * 72 + 10 * 148
+    assert e["phase"] == 640 * 80 + 512 * 8 + 128 * 24 + 10 * 52
+    t = bench.launch_bytes("fp32dev", "table", 1000, (8, 8, 8), **now)
+    assert (t["per_voxel"]["collide"], t["per_voxel"]["phase"]) == (4 * 46 + 72, 40 + 24)
+    # The 512^3 displacement: 27,684,590 voxels, 47,993 exception waves.
+    d = bench.launch_bytes("fp64", "compact", 27684590, (512, 512, 512), ex_waves=47993, **now)
+    assert (d["per_voxel"]["collide"], d["per_voxel"]["step"]) == (399.64, 490.23)
