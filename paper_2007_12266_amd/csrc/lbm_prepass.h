@@ -39,7 +39,7 @@ constexpr int kCoordXBits = 10, kCoordYBits = 11, kCoordZBits = 11;
 //  * 16-bit waves (kind 0): wide holds the mask and the codes of q = 1..6 (16 bytes read by the
 //    densities), n16 the codes of q = 7..14 and n8 those of q = 15..18 (40 in all).
 //  * exception waves, whose targets spread beyond 16 bits (where the pore list jumps between
-//    blocks of rows; 15-20% of the waves of those rocks): their 18 x 64 targets as int32 in
+//    blocks of rows; 11-20% of the waves of those rocks): their 18 x 64 targets as int32 in
 //    exception row r, ex[(r * 18 + q - 1) * 64 + lane].
 // Per wave: kCompactWaveInts ints: pore bases of q = 1..18, tail bases of q = 1..18, the wave's
 // exception row or -1, its kind, and the face mark.

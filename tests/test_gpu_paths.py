@@ -1,7 +1,8 @@
-"""Branches of the launch and kernel dispatch at the sizes where they can go wrong: load order and
-workgroup size by domain size, the pressure condition inside the collide kernel against the face
-kernel, read-back through pinned memory or a device buffer, byte and 16-bit neighbour codes, and
-the distance, line and labelling passes of the pre-processing at word, window, packing and tile
+"""Branches of the launch and kernel dispatch at the sizes where they can go wrong: load order,
+workgroup size and defaults by domain size and lookup, states at rest, pools with face members, the
+pressure condition inside the collide kernel against the face kernel, read-back through pinned
+memory or a device buffer, byte and 16-bit neighbour codes, call buffers on both sides of a block,
+and the distance, line and labelling passes of the pre-processing at word, window, packing and tile
 edges. Step results are compared bitwise (all variants evaluate the same operations), distances
 and masks exactly."""
 import dataclasses
@@ -194,8 +195,8 @@ def test_invasion_through_winding_pores_across_tiles(lbm, shape, per):
 @pytest.mark.parametrize("precision", PRECISIONS)
 def test_pool_member_with_faces_costs_the_others_nothing(lbm, precision):
     """A pool of 15 periodic members and one with pressure faces steps in at most 1.6 times what
-    one of 16 periodic members takes: 1.08 to 1.2 are the face member's own launches and voxels,
-    while the whole pool in kernels that hold the face code took 1.9 to 2.6 times."""
+    one of 16 periodic members takes: 1.02 to 1.06 with the kernels as they are, 1.9 to 2.6 with a
+    kernel that holds its arguments in scratch memory."""
     rocks = []
     for k in range(16):
         solid, _ = inputs.grf_rock((64, 64, 64), 4.0, 0.25, 40 + k)
