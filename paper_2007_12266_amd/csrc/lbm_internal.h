@@ -130,8 +130,9 @@ struct BatchArgs {
 
 // Kernel launchers (lbm_kernels.hip). `odd` is the parity of the step being taken.
 hipError_t launch_init(const StepArgs& a, const double* phi0, int block, hipStream_t s);
+// in_step false: the phase of the current state for a reader, which may find it at rest.
 hipError_t launch_phase(const StepArgs& a, bool odd, int block, bool stream, unsigned lds,
-                        hipStream_t s);
+                        hipStream_t s, bool in_step = true);
 hipError_t launch_collide(const StepArgs& a, bool odd, int block, bool stream, unsigned lds,
                           hipStream_t s);
 // Dynamic LDS that bounds a step kernel (0: phase, 1: collide) to `wg` workgroups per CU.

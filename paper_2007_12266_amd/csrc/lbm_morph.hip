@@ -173,8 +173,8 @@ lbm_status current_phase(lbm_domain* d) {
     const lbm_tuning& tu = d->tune;
     const bool odd = (d->step & 1) != 0;
     const StepArgs a = d->args(odd, tu.phase_block, tu.phase_schedule, tu.phase_run[odd ? 1 : 0]);
-    HIP_TRY(launch_phase(a, odd, tu.phase_block, tu.phase_stream != 0, d->lds[0],
-                         d->stream));
+    HIP_TRY(launch_phase(a, odd, tu.phase_block, tu.phase_stream != 0, d->lds[0], d->stream,
+                         false));
     return LBM_OK;
 }
 
