@@ -450,7 +450,8 @@ __device__ __forceinline__ void sent(R p, R n, bool raw, R& na, R& nb) {
 // REST: the state may be at rest, where the neighbours' numbers count for nothing and are not
 // fetched (us a count of the phase right after a growth, fetched / not, 256^3 FP64 118 / 59, 320^3
 // 220 / 89). The kernels of a step have no such test: its wait for the flag ahead of the fetches
-// costs them 1% up to 150^3, and a step from rest is the first of many.
+// costs them 1% up to 150^3, and a step from rest is the first of many. Nor have the reductions and
+// fields, which would take 1 to 10% longer for every state (320^3 FP32-dev 263 -> 291 us).
 template <int PREC, int NB = NB_DYN, bool STREAM = false, bool FACE = true, bool REST = false>
 __device__ __forceinline__ void densities(const StepArgs& a, int i, int fresh, double& na,
                                           double& nbv, int& ghost) {
@@ -472,10 +473,13 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, int fresh, d
     }
     if (!REST && FACE) fc = face_of<NB>(a, i);
     ghost = fc && !use_rank<NB>(a) ? (fc == 1 ? up[5] : up[6]) : -1;   // along -z, along +z
-    R sna[7], snb[7], suc[7], sgc[7];
+    R sna[7], snb[7], suc[7], sgc[7], ouc[3], ogc[3];   // ouc, ogc: the voxel's own
+    constexpr bool kFloat = sizeof(S) == sizeof(float);
     if (rest) {
 #pragma unroll
         for (int q = 1; q < 7; ++q) sna[q] = snb[q] = suc[q] = sgc[q] = (R)0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) ouc[c] = ogc[c] = (R)0;
     } else {
 #pragma unroll
         for (int q = 1; q < 7; ++q) {
@@ -487,6 +491,13 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, int fresh, d
             suc[q] = (R)g.x;
             sgc[q] = (R)g.y;
         }
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (kFloat) {
+                const auto g = load_pair<S>(M, a.ld, c, i);
+                ouc[c] = (R)g.x;
+                ogc[c] = (R)g.y;
+            }
     }
 #pragma unroll
     for (int q = 1; q < 7; ++q) {
@@ -496,15 +507,15 @@ __device__ __forceinline__ void densities(const StepArgs& a, int i, int fresh, d
     }
     R own_a, own_b;
     sent<R>((R)own_p, (R)own_n, fresh != 0, own_a, own_b);
-    if (sizeof(S) == sizeof(float) && !rest) {
+    if (kFloat) {
         // The rest population is what the six moving ones leave of N (the rounded float weights
         // would otherwise add 1.5e-8 of mass per step); sums in double, see below.
         double sa = 0.0, sb = 0.0;
 #pragma unroll
         for (int q = 1; q < 7; ++q) {
             R ao, bo;
-            const auto g = load_pair<S>(M, a.ld, (q - 1) >> 1, i);
-            ab_out<R>(own_a, own_b, (R)g.x, (R)g.y, (q & 1) ? (R)1 : (R)-1, ao, bo);
+            const int c = (q - 1) >> 1;
+            ab_out<R>(own_a, own_b, ouc[c], ogc[c], (q & 1) ? (R)1 : (R)-1, ao, bo);
             sa += (double)ao;
             sb += (double)bo;
         }
@@ -897,12 +908,11 @@ __device__ __forceinline__ void voxel_flow(const StepArgs& a, int i, double& rho
     if (P::kDev) rho += 1.0;
 }
 
-template <int PREC, bool ODD, bool REST>
+template <int PREC, bool ODD>
 __device__ __forceinline__ void voxel_state(const StepArgs& a, int i, double& na, double& nbv,
                                             double& rho, double& jx, double& jy, double& jz) {
     int ghost;
-    // Callers' waves are aligned.
-    densities<PREC, NB_DYN, false, true, REST>(a, i, *a.fresh, na, nbv, ghost);
+    densities<PREC>(a, i, *a.fresh, na, nbv, ghost);   // callers' waves are aligned
     voxel_flow<PREC, ODD>(a, i, rho, jx, jy, jz);
 }
 
@@ -916,7 +926,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // Partial sums of reduction block `blk` (of kRedBlocks): voxels blk*T + tid + k*kRedBlocks*T.
-template <int PREC, bool ODD, bool REST>
+template <int PREC, bool ODD>
 __device__ __forceinline__ void reduce_block(const StepArgs& a, int blk,
                                              double* __restrict__ partials) {
     if ((int64_t)blk * kRedThreads >= a.N) {   // no voxel: a small domain has few blocks that do
@@ -929,7 +939,7 @@ __device__ __forceinline__ void reduce_block(const StepArgs& a, int blk,
     const int stride = kRedBlocks * kRedThreads;
     for (int i = blk * kRedThreads + threadIdx.x; i < a.N; i += stride) {
         double na, nbv, rho, jx, jy, jz;
-        voxel_state<PREC, ODD, REST>(a, i, na, nbv, rho, jx, jy, jz);
+        voxel_state<PREC, ODD>(a, i, na, nbv, rho, jx, jy, jz);
         const double phi = (na - nbv) / (na + nbv);
         const double u[3] = {jx + 0.5 * a.F[0], jy + 0.5 * a.F[1], jz + 0.5 * a.F[2]};
         const bool bad = !(isfinite(na) && isfinite(nbv) && isfinite(rho) && isfinite(u[0]) &&
@@ -974,10 +984,10 @@ __device__ __forceinline__ void reduce_block(const StepArgs& a, int blk,
     }
 }
 
-template <int PREC, bool ODD, bool REST>
+template <int PREC, bool ODD>
 __global__ void __launch_bounds__(kRedThreads) reduce_kernel(StepArgs a,
                                                              double* __restrict__ partials) {
-    reduce_block<PREC, ODD, REST>(a, blockIdx.x, partials);
+    reduce_block<PREC, ODD>(a, blockIdx.x, partials);
 }
 
 // One group of kRedBlocks blocks per pool slot, with the single-domain decomposition, so a
@@ -987,8 +997,8 @@ __global__ void __launch_bounds__(kRedThreads) reduce_batched(BatchArgs b,
                                                               double* __restrict__ partials) {
     const int slot = blockIdx.x / kRedBlocks;
     const StepArgs a = batch_args(b, slot);
-    reduce_block<PREC, ODD, false>(a, blockIdx.x % kRedBlocks,
-                                   partials + (size_t)slot * kRedBlocks * kNRed);
+    reduce_block<PREC, ODD>(a, blockIdx.x % kRedBlocks,
+                            partials + (size_t)slot * kRedBlocks * kNRed);
 }
 
 // Sum of each group's nblocks partial records (kNRed values each); one workgroup of
@@ -1025,7 +1035,7 @@ __global__ void __launch_bounds__(kFinalThreads) reduce_final_kernel(
 // ------------------------------------------------------------------------------------------
 // Field read-back for pore voxels (pore order), in FP64.
 // ------------------------------------------------------------------------------------------
-template <int PREC, bool ODD, bool REST>
+template <int PREC, bool ODD>
 __global__ void __launch_bounds__(256) field_kernel(StepArgs a, int field,
                                                     double* __restrict__ out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1034,7 +1044,7 @@ __global__ void __launch_bounds__(256) field_kernel(StepArgs a, int field,
     if (field <= LBM_FIELD_PHI) {   // N_a, N_b, phi: the components alone (a third of the bytes)
         double na, nbv;
         int ghost;
-        densities<PREC, NB_DYN, false, true, REST>(a, i, *a.fresh, na, nbv, ghost);
+        densities<PREC>(a, i, *a.fresh, na, nbv, ghost);
         out[i] = field == LBM_FIELD_NA   ? na
                  : field == LBM_FIELD_NB ? nbv
                                          : (na - nbv) / (na + nbv);
@@ -1155,26 +1165,13 @@ int grid_for(const StepArgs& a, int block) { return (a.N + block - 1) / block; }
 // ------------------------------------------------------------------------------------------
 // Launchers: dispatch on precision and step parity (the step kernels also on the lookup).
 // ------------------------------------------------------------------------------------------
-// One launch of KERNEL<P, odd> (or KERNEL<P, odd, NB>) for the precision P of the domain. For
-// read-outs KERNEL<P, odd, REST>: a domain of few waves is read without the test for a state at rest.
+// One launch of KERNEL<P, odd> (or KERNEL<P, odd, NB>) for the precision P of the domain.
 #define LBM_LAUNCH_ODD(KERNEL, P, GRID, BLOCK, ...)                                            \
     do {                                                                                       \
         if (odd)                                                                               \
             hipLaunchKernelGGL((KERNEL<P, true>), GRID, BLOCK, 0, s, __VA_ARGS__);             \
         else                                                                                   \
             hipLaunchKernelGGL((KERNEL<P, false>), GRID, BLOCK, 0, s, __VA_ARGS__);            \
-    } while (0)
-
-#define LBM_LAUNCH_ODD_REST(KERNEL, P, GRID, BLOCK, ...)                                       \
-    do {                                                                                       \
-        if (odd && rest)                                                                       \
-            hipLaunchKernelGGL((KERNEL<P, true, true>), GRID, BLOCK, 0, s, __VA_ARGS__);       \
-        else if (odd)                                                                          \
-            hipLaunchKernelGGL((KERNEL<P, true, false>), GRID, BLOCK, 0, s, __VA_ARGS__);      \
-        else if (rest)                                                                         \
-            hipLaunchKernelGGL((KERNEL<P, false, true>), GRID, BLOCK, 0, s, __VA_ARGS__);      \
-        else                                                                                   \
-            hipLaunchKernelGGL((KERNEL<P, false, false>), GRID, BLOCK, 0, s, __VA_ARGS__);     \
     } while (0)
 
 #define LBM_LAUNCH_ODD_NB(KERNEL, P, NBV, GRID, BLOCK, ...)                                    \
@@ -1216,10 +1213,10 @@ hipError_t launch_init(const StepArgs& a, const double* phi0, int block, hipStre
     return hipGetLastError();
 }
 
-// The step kernel (0: phase, 1: collide, 2: phase outside a step) of a domain, by precision, parity, neighbour lookup,
-// streaming accesses, load order and pressure faces (whose code costs the collide kernel registers:
-// with the compact lookup 158 for 120 to 128 in FP64, 140 for 120 to 124 in FP32-mixed, 120 for 77
-// to 113 in FP32-dev). The phase kernel is the same at both parities.
+// The step kernel (0: phase, 1: collide, 2: phase outside a step) of a domain, by precision, parity,
+// neighbour lookup, streaming accesses, load order and pressure faces (whose code costs the collide
+// kernel registers: with the compact lookup 158 for 120 to 128 in FP64, 140 for 120 to 124 in
+// FP32-mixed, 120 for 77 to 113 in FP32-dev). The phase kernel is the same at both parities.
 using StepKernel = void (*)(StepArgs);
 
 template <int P, int NB, bool ST, bool FACE>
@@ -1320,9 +1317,7 @@ hipError_t step_kernel_lds(const StepArgs& a, int kernel, int block, bool stream
 
 hipError_t launch_reduce(const StepArgs& a, bool odd, double* partials, double* out,
                          hipStream_t s) {
-    const bool rest = a.N > kEarlyVoxels;
-    LBM_PREC_SWITCH(a.prec, LBM_LAUNCH_ODD_REST, reduce_kernel, dim3(kRedBlocks),
-                    dim3(kRedThreads), a, partials);
+    LBM_DISPATCH(reduce_kernel, dim3(kRedBlocks), dim3(kRedThreads), a, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(reduce_final_kernel, dim3(1), dim3(kFinalThreads), 0, s, partials,
@@ -1380,9 +1375,7 @@ hipError_t launch_reduce_batched(const BatchArgs& b, int prec, bool odd, int nsl
 hipError_t launch_field(const StepArgs& a, bool odd, int field, double* out, int block,
                         hipStream_t s) {
     (void)block;
-    const bool rest = a.N > kEarlyVoxels;
-    LBM_PREC_SWITCH(a.prec, LBM_LAUNCH_ODD_REST, field_kernel, dim3(grid_for(a, 256)), dim3(256), a,
-                    field, out);
+    LBM_DISPATCH(field_kernel, dim3(grid_for(a, 256)), dim3(256), a, field, out);
     return hipGetLastError();
 }
 

@@ -364,9 +364,9 @@ def test_thin_images_in_each_axis(lbm, axis, thin, per):
 @pytest.mark.parametrize("mode", ["table", "rank", "compact"])
 @pytest.mark.parametrize("faces", [False, True])
 def test_large_domain_at_rest(lbm, faces, mode, precision):
-    """Domains above 262144 pore voxels read a state at rest without their neighbours: the initial
-    phase is read back as given and summed by the reduction, two steps from it follow the oracle, and
-    the phase counted at rest after a growth is the one the growth reports. Bounds: of each field's
+    """Domains above 262144 pore voxels count the phase of a state at rest without its neighbours: the
+    initial phase is read back as given, counted and summed, two steps from it follow the oracle, and
+    the phase counted at rest after a growth is the one that the fields show. Bounds: of each field's
     largest value 1e-12 in FP64, 1e-6 where populations are float (2e-8 relative to their rest
     values, 0.06, against velocities of 1e-3 and up), 1e-5 where everything is."""
     nm = {"table": lbm.NBR_TABLE, "rank": lbm.NBR_RANK, "compact": lbm.NBR_COMPACT}[mode]
@@ -380,6 +380,7 @@ def test_large_domain_at_rest(lbm, faces, mode, precision):
     phi = prob.phase0()[pore]
     assert np.abs(dom.field("phi")[pore] - phi).max() <= (1e-6 if precision == "fp32dev" else 1e-14)
     assert dom.reduce()["sw_count"] == (phi > 0).mean()
+    assert dom.phase_volume() == int((phi > 0).sum())
     ref = O.state_for(prob).run(2)
     dom.step(2)
     got, want = dom.fields(), ref.fields()
